@@ -222,8 +222,8 @@ double model_ms(int mode, bool grid64, double n, const double box[3], const int 
     const double cells = (double)M[0] * M[1] * M[2];
     const double pairs = 0.5 * n * n / V * (4.0 / 3.0) * M_PI * rc * rc * rc;
     // P2P waves: three per 64-target chunk (about n/64 + tiles/2 chunks), six when the launch
-    // has very few (the rule of launch_p2p in p2p.hip, on its grid of tiles + n/64 chunks: fewer
-    // than 2048)
+    // has very few: the counts that the constants were fitted with.  (launch_p2p gives small launches
+    // more; the model stays as it is, since the grid that a plan resolves to follows from it.)
     const double tiles = cells / ((double)B * B * B);
     const double grid_waves = tiles + std::ceil(n / 64.0);
     const double split = grid_waves < 2048.0 ? 6.0 : 3.0;

@@ -24,6 +24,7 @@
 //      result is added to its target's FP64 accumulator in LDS with ds_add_f64 (the pairs
 //      of one source have distinct targets, so conflicts are few).
 #include "internal.h"
+#include <algorithm>
 #include <type_traits>
 #include "screening.h"
 
@@ -333,23 +334,31 @@ constexpr int kTest = 32;    // sources tested per round (queue <= kTest * 64 pa
 // Count: no pair formula; the wave only counts its accepted (target, source) pairs and adds
 // the count to *pair_count (one integer atomic per wave): the exact number of ordered pairs
 // the near-field sum runs over, for measurement.
-template <typename TF, typename TA, int Lv, bool Count = false>
-__global__ __launch_bounds__(64) void k_p2p(int n, const Rec64* __restrict__ rec,
+// NW waves share a chunk: wave w takes every NW-th batch of 64 candidate sources from batch w on, and
+// their sums are added in wave order (one block per chunk, so that small inputs, whose chunks do not
+// fill the chip, still have a fixed order of summation).
+template <typename TF, typename TA, int Lv, int NW, bool Count = false>
+__global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict__ rec,
                                             const int* __restrict__ start,
                                             const int* __restrict__ chunk_off, Geometry g,
                                             PairArgs a, double* __restrict__ u_near,
                                             unsigned long long* __restrict__ pair_count = nullptr)
 {
-    __shared__ double tgt[3][kWave];
-    __shared__ TA acc[3][kWave];
-    __shared__ double ring[3][kRing];
-    __shared__ TF ringf[3][kRing];
-    __shared__ unsigned short queue[kTest * kWave];
+    __shared__ double tgt_[NW][3][kWave];
+    __shared__ TA acc_[NW][3][kWave];
+    __shared__ double ring_[NW][3][kRing];
+    __shared__ TF ringf_[NW][3][kRing];
+    __shared__ unsigned short queue_[NW][kTest * kWave];
 
     // plain block order: an XCD-aware order (each XCD sweeping a contiguous range) was
     // measured 12% slower here, unlike in G2P
     const int wave = uniform_i((int)blockIdx.x);
-    const int lane = threadIdx.x;
+    const int wid = uniform_i((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    double(&tgt)[3][kWave] = tgt_[wid];
+    TA(&acc)[3][kWave] = acc_[wid];
+    double(&ring)[3][kRing] = ring_[wid];
+    TF(&ringf)[3][kRing] = ringf_[wid];
+    unsigned short(&queue)[kTest * kWave] = queue_[wid];
     const int total = chunk_off[g.ntiles * g.nsys];  // chunks of all systems
     if (wave >= total) return;
 
@@ -380,9 +389,10 @@ __global__ __launch_bounds__(64) void k_p2p(int n, const Rec64* __restrict__ rec
         tgt[d][lane] = tx[d];
         acc[d][lane] = (TA)0;
     }
-    __syncthreads();
+    wave_lds_sync();
 
     int rhead = 0, rcount = 0;
+    int turn = wid;  // batches to pass over before the next of this wave's
     unsigned long long counted = 0;
 
     // test the targets against ring sources [rhead, rhead + cnt), then drain the queue
@@ -399,10 +409,10 @@ __global__ __launch_bounds__(64) void k_p2p(int n, const Rec64* __restrict__ rec
         }
         if (Count) {
             counted += (unsigned long long)qn;
-            __syncthreads();
+            wave_lds_sync();
             return;
         }
-        __syncthreads();
+        wave_lds_sync();
         for (int q0 = 0; q0 < qn; q0 += kWave) {
             const int k = q0 + lane;
             if (k < qn) {
@@ -422,7 +432,7 @@ __global__ __launch_bounds__(64) void k_p2p(int n, const Rec64* __restrict__ rec
                 atomicAdd(&acc[2][tt], (TA)c2);
             }
         }
-        __syncthreads();
+        wave_lds_sync();
     };
 
     for (int dx = -g.S[0]; dx <= g.S[0]; ++dx) {
@@ -448,6 +458,13 @@ __global__ __launch_bounds__(64) void k_p2p(int n, const Rec64* __restrict__ rec
                 const int nt = tbase + (wx * g.NT[1] + wy) * g.NT[2] + wz;
                 const int sa = start[nt * per], sb = start[(nt + 1) * per];
                 for (int base = sa; base < sb; base += kWave) {
+                    if (NW > 1) {
+                        if (turn > 0) {  // another wave of this chunk takes the batch
+                            --turn;
+                            continue;
+                        }
+                        turn = NW - 1;
+                    }
                     const int s = base + lane;
                     bool keep = false;
                     double sx = 0, sy = 0, sz = 0, f0 = 0, f1 = 0, f2 = 0;
@@ -475,7 +492,7 @@ __global__ __launch_bounds__(64) void k_p2p(int n, const Rec64* __restrict__ rec
                         ringf[2][slot] = (TF)f2;
                     }
                     rcount += __popcll(b);
-                    __syncthreads();
+                    wave_lds_sync();
                     while (rcount >= kTest) {
                         process(kTest);
                         rhead = (rhead + kTest) & (kRing - 1);
@@ -495,11 +512,16 @@ __global__ __launch_bounds__(64) void k_p2p(int n, const Rec64* __restrict__ rec
         if (lane == 0 && counted > 0) atomicAdd(pair_count, counted);
         return;
     }
-    if (active) {
+    if (NW > 1) __syncthreads();
+    if (active && wid == 0) {
         const double post = Coef<TF, Lv>::post(a);
-        u_near[i] = post * (double)acc[0][lane];
-        u_near[(int64_t)n + i] = post * (double)acc[1][lane];
-        u_near[2 * (int64_t)n + i] = post * (double)acc[2][lane];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            double v = (double)acc_[0][d][lane];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v += (double)acc_[w][d][lane];
+            u_near[d * (int64_t)n + i] = post * v;
+        }
     }
 }
 
@@ -538,6 +560,7 @@ __global__ __launch_bounds__(64) void k_p2p(int n, const Rec64* __restrict__ rec
 // pairs also need r > 0 and the index order, and the last, shorter batch keep the direct test;
 // the direct difference of repeated positions is exactly 0 also in the centred frame.
 constexpr int kSymRing = 64;
+constexpr int kTileSplit = 3;  // up to so many waves share a chunk by tiles, more by batches of sources
 constexpr int kFar = 1 << 30;  // ring key offset of sources outside the targets' own tile
 // Balanced drain: batches of 32 ring entries and one copy of the source
 // accumulators (a second copy, for lanes 32-63, was measured 2% slower: the LDS it takes
@@ -584,8 +607,9 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
 
     // plain block order: an XCD-aware order (each XCD sweeping a contiguous range) was
     // measured 12% slower here, unlike in G2P
-    // nsplit waves share a chunk, each taking every nsplit-th of its neighbour tiles (shorter
-    // waves: a smaller tail when the last waves of the launch run)
+    // nsplit waves share a chunk, each taking every nsplit-th of its neighbour tiles (shorter waves: a
+    // smaller tail when the last waves of the launch run), or, where small inputs are split further, every
+    // nsplit-th batch of 64 candidate sources (their sources may all lie in a tile or two)
     const int wave = uniform_i((int)blockIdx.x) / nsplit;
     const int part = uniform_i((int)blockIdx.x) % nsplit;
     const int lane = threadIdx.x;
@@ -637,7 +661,13 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
     const double post = ST ? 1.0 : Coef<TF, Lv>::post(a);
 
     int rhead = 0, rcount = 0;
-    int tk = 0;  // neighbour tiles met so far (those within r_c of the targets)
+    const bool by_tile = nsplit <= kTileSplit;
+    int turn = part;  // tiles or batches to pass over before the next of this wave's
+    auto skip = [&]() {
+        const bool other = turn > 0;  // another wave of this chunk takes it
+        turn = other ? turn - 1 : nsplit - 1;
+        return other;
+    };
 
     auto process = [&](int cnt) {
         // 1. test: bit j of m is set when this lane's target pairs with batch entry j (all
@@ -921,13 +951,14 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 const double shz = fz * g.L[2];
                 const double gz = fmax(0.0, fmax(uz * w[2] - bhi[2], blo[2] - (uz + 1) * w[2]));
                 if (gx * gx + gy * gy + gz * gz >= a.rc2) continue;
-                if (tk++ % nsplit != part) continue;  // another wave of this chunk takes it
+                if (by_tile && skip()) continue;
                 const bool own = (dx == 0 && dy == 0 && dz == 0);
                 const int nt = tbase + (wx * g.NT[1] + wy) * g.NT[2] + wz;
                 // own tile: sources below the first target can pair with none of them
                 const int sa = own ? first : start[nt * per], sb = start[(nt + 1) * per];
                 const int koff = own ? 0 : kFar;
                 for (int base = sa; base < sb; base += kWave) {
+                    if (!by_tile && skip()) continue;
                     const int s = base + lane;
                     bool keep = false;
                     double sx = 0, sy = 0, sz = 0, f0 = 0, f1 = 0, f2 = 0;
@@ -1035,7 +1066,7 @@ hipError_t launch_count_pairs(const Plan& pl, const Work& w, int n, unsigned lon
         Geometry g = pl.g;
         g.nsys = nsys;
         const int64_t waves = (int64_t)g.ntiles * nsys + (n + kWave - 1) / kWave;
-        hipLaunchKernelGGL((k_p2p<double, double, 0, true>), dim3((unsigned)waves), dim3(kWave), 0, s, n,
+        hipLaunchKernelGGL((k_p2p<double, double, 0, 1, true>), dim3((unsigned)waves), dim3(kWave), 0, s, n,
                            (const Rec64*)w.rec, w.start, w.chunk_off, g, a, nullptr, count);
     }
     return hipGetLastError();
@@ -1044,12 +1075,24 @@ hipError_t launch_count_pairs(const Plan& pl, const Work& w, int n, unsigned lon
 // the FP64 pair formula's accuracy level for a plan's tolerance (see PairArgs)
 static int pair_level(double tol) { return tol >= 1e-8 ? 2 : tol >= 1e-10 ? 1 : 0; }
 
+// Waves per chunk of the deterministic kernel, by the plan alone (a system's sums must not depend on
+// what else is evaluated with it): more where even the plan's largest input has few chunks.  P2P ms at
+// 1 / 2 / 4 / 8 / 12 waves: 24 chunks (1e3 uniform, FP64) 0.232 / 0.137 / 0.088 / 0.072 / 0.066; 533 (3e4, KB)
+// 1.38 / 0.88 / 0.48 / 0.58 / 0.47; 3637 (2e5) 2.71 / 2.10 / 1.95 / 3.14 / 2.64; 19721 (1e6, 256^3) 6.63 / 6.43 /
+// 7.07 / 12.4 / 10.8, (1e6, 128^3) 35.8 / 33.9 / 34.3 / 56.3 / 47.0.  Four waves take 46 KB of LDS (three
+// blocks per CU), eight 92 KB (one).
 template <typename TF, int Lv>
 void launch_p2p_det(const Plan& pl, const Work& w, int n, hipStream_t s, const Geometry& g, const PairArgs& a,
                     dim3 grid)
 {
-    hipLaunchKernelGGL((k_p2p<TF, double, Lv>), grid, dim3(kWave), 0, s, n, (const Rec64*)w.rec, w.start,
-                       w.chunk_off, g, a, w.u_near);
+    const int64_t chunks = (int64_t)pl.g.ntiles + (pl.p.n_max + kWave - 1) / kWave;
+    auto launch = [&](auto kernel, int nw) {
+        hipLaunchKernelGGL(kernel, grid, dim3(nw * kWave), 0, s, n, (const Rec64*)w.rec, w.start, w.chunk_off, g, a,
+                           w.u_near, nullptr);
+    };
+    if (chunks < 256) launch(k_p2p<TF, double, Lv, 12>, 12);
+    else if (chunks < 8192) launch(k_p2p<TF, double, Lv, 4>, 4);
+    else launch(k_p2p<TF, double, Lv, 2>, 2);
 }
 
 template <typename TF, int Lv, bool ST>
@@ -1080,12 +1123,16 @@ hipError_t launch_p2p(const Plan& pl, const Work& w, int n, hipStream_t s, bool 
         }
         return hipGetLastError();
     }
-    // Symmetric kernel: three waves per chunk (each taking every third neighbour tile) shorten the
-    // waves and so the launch's tail.  Measured P2P ms for 1 / 2 / 3 / 4 / 6 waves per chunk: c2
-    // (17k chunks) 20.1 / 18.7 / 18.5 / 19.5 / 18.7; H 10.8 / 10.4 / 10.1 / 11.6 / 10.4; c4 (63k)
-    // 51.7 / 51.4 / 50.9 / 55.6 / 52.1; clustered c3 (160k) 172.7 / 177.6 / 172.2 / 231.8 / 182.2.
-    // With fewer chunks than wave slots, six (c1, N = 1e3: 0.158 / 0.093 / 0.098 / 0.072 / 0.063).
-    const int kSplit = waves < 2048 ? 6 : 3;
+    // Symmetric kernel: waves per chunk.  Three shorten the launch's tail; more (then dealt batches of
+    // sources instead of tiles) fill the chip where the chunks are few, and even out the chunks of
+    // clustered inputs, until a wave's own start and end outweigh its share.  P2P ms at 3 / 5 / 7 / 13 /
+    // 33 waves per chunk: 24 chunks (1e3 uniform, FP64) 0.081 / 0.066 / 0.068 / 0.049 / 0.039; 441 (2e4 in
+    // 2 clusters, FP32) 1.00 / 0.76 / 0.54 / 0.35 / 0.30 (2.97 with six by tiles); 1536 (6.6e4 uniform, FP32)
+    // 0.61 / 0.55 / 0.51 / 0.54 / 0.66; 3368 (1.5e5, FP64) 0.49 / 0.44 / 0.45 / 0.51 / 0.76; 19721 (1e6, 1e-8,
+    // 256^3) 3.67 / 3.79 / 3.89 / 4.36 / 6.18.  Odd, so that the waves of a chunk, consecutive blocks, spread
+    // over the XCDs (with 8 or 16, all the chunks' first waves, the heaviest, meet on one).
+    const int64_t fill = (23040 / waves - 1) | 1;
+    const int kSplit = (int)std::min<int64_t>(33, std::max<int64_t>(kTileSplit, fill));
     const dim3 sgrid((unsigned)(waves * kSplit));
     const int64_t cnt = 3 * (int64_t)n;
     hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, w.u_near, cnt);

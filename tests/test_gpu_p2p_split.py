@@ -1,0 +1,36 @@
+"""The waves that share a P2P target chunk: inputs with fewer source batches than waves, all sources
+in the targets' own tile, and plans of every size class of the deterministic kernel (12, 4 and 2
+waves per chunk).  The near field is compared with the oracle's real-space sum at 1e-12 of its max
+(full-precision pair formula, FP64 sums in different orders)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2606_19059_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+BOX = (1.0, 1.0, 1.0)
+
+
+def near_error(x, f, n_max, deterministic):
+    import paper_2606_19059_amd as E
+
+    pl = E.Plan(BOX, 1e-11, xi=10.0, r_c=0.45, grid=(32, 32, 32), P=8, window_shape=4.8, n_max=n_max,
+                deterministic=deterministic)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    un = pl.eval_parts(d(x), d(f))[0].cpu().numpy()
+    ref = oracle.real_space(x, f, BOX, 10.0, 0.45)
+    return np.max(np.abs(un - ref)) / max(np.max(np.abs(ref)), 1e-300)
+
+
+@pytest.mark.parametrize("deterministic", [False, True])
+@pytest.mark.parametrize("n,n_max", [(2, 2), (65, 65), (700, 700), (700, 20_000), (1500, 200_000), (1500, 600_000)])
+@pytest.mark.parametrize("one_tile", [False, True])
+def test_split_chunks_match_oracle(n, n_max, one_tile, deterministic):
+    x, f = W.particles(n, BOX, seed=23)
+    if one_tile:
+        x = 0.51 + 0.03 * x  # inside one cell of the 32^3 grid's coarsest and finest tiles
+    assert near_error(x, f, n_max, deterministic) < 1e-12
