@@ -1,24 +1,15 @@
 // P2G: spreading of the 3-vector forces onto the uniform grid, eq. (p2g):
 //   phi(g_l) = sum_j sum_p w(g_l - y_j + p) f_j,  w separable, P points per axis.
 //
-// Atomic-free, owner-computes design for MI355X.  One wavefront owns an 8 x 8 patch of
-// grid lines along x (lane (ly, lz) owns line (y0+ly, z0+lz)) over an x-segment
-// [x0, x1), and sweeps the particle slabs of constant cell-x in increasing order.  Each
-// lane keeps P x-accumulators per component in registers: a particle in cell-x c adds
-// w_x[k] * w_y * w_z * f to the lane's points x = c - P/2 + 1 + k; after slab c has been
-// processed the point x = c - P/2 + 1 receives nothing more from the segment, so it is
-// written once and the register window shifts by one.  The first and last P - 1 points of a
-// segment also receive from the neighbouring segment: both segments write their partial
-// sums to halo planes, which k_p2g_halo_sum adds into the grid.  Every grid point has one
-// writer and a fixed summation order: deterministic, no atomics, no zero-fill.
-// The particles of a slab that can reach the patch (a (8+P-1)^2 window of cells) are
-// contiguous runs of the cell-sorted arrays; they are staged in LDS with their P x weights
-// and, per line of the patch, the y weight and the z weight times f (zero where the line is
-// outside the particle's P x P footprint), so a lane's factor for a particle is
-// w_y[ly] * (w_z f)[lz], read without any dependent index arithmetic.  The x direction is
-// exact (no wasted work); in y and z a lane whose line is outside the footprint multiplies
-// by zero.
-#include <type_traits>
+// Atomic-free, owner-computes design for MI355X.  One wavefront covers an 8 x 8 patch of grid
+// lines along x (lane (ly, lz) owns line (y0+ly, z0+lz)).  A particle in cell-x c adds
+// w_x[k] * w_y * w_z * f to the points x = c - P/2 + 1 + k of every line of its footprint.  The
+// particles of a slab (cell-x constant) that can reach the patch, a (8+P-1)^2 window of cells,
+// are contiguous runs of the cell-sorted arrays.  Every grid point is written once, as a sum in
+// a fixed order: deterministic, no atomics, no zero-fill.  The x direction is exact (no wasted
+// work); in y and z a lane whose line is outside a particle's footprint multiplies by zero.
+#include <algorithm>
+#include <climits>
 
 #include "window.h"
 
@@ -28,111 +19,156 @@ namespace {
 
 constexpr int kPatch = 8;     // lines per patch edge (8 x 8 = 64 lanes)
 constexpr int kWaves = 4;     // waves per block, all owning the block's lines
-constexpr int kPerWave = 32;  // particles staged per wave and round
-constexpr int kChunk = kWaves * kPerWave;
+constexpr int kSlabs = 4;     // slabs a wave spreads between two merges
+constexpr int kWindow = kWaves * kSlabs;  // most slabs whose runs are tabulated at a time
+constexpr int kBatch = 16;    // particles staged per wave and round, four lanes each
 constexpr int kMaxRuns = 320; // runs per slab (window rows x z-tile segments)
+constexpr int kTable = 1536;  // entries of the run table (a window has fewer slabs where runs are many)
+constexpr int kMergeCost = 16;  // cost of one merge of the waves' sums, in particles spread by one wave
+static_assert(kTable >= (kMaxRuns + 1) * kSlabs, "the runs of kSlabs slabs must fit the table");
+static_assert(kSlabs % kWaves == 0, "a carried point stays with its wave");
 
-// T: arithmetic and accumulation precision; TG: grid element type (the FP32 bulk mode
-// accumulates in FP64 -- the same VALU rate as FP32 without packed math -- and stores FP32).
-// A block of kWaves waves owns one (patch, x-segment): every wave keeps accumulators for
-// all 64 lines, takes a contiguous quarter of each slab's particles (staged kPerWave at a
-// time: 32 amortises the load and search latency of a staging round, and an even split
-// keeps the waves of a block equally busy), and at each output step the waves' partial
-// sums are added in a fixed order through LDS.
-template <typename T, typename TG, int P>
-__global__ __launch_bounds__(kWaves * 64) void k_p2g_sweep(const typename RecView<T>::Rec* __restrict__ rec,
+// acc[k][c] += w_x[k] g_c for all k: lane i of every row of 16 lanes holds w_x[i], and the DPP
+// row_newbcast of v_fmac_f64 broadcasts w_x[k] from it, so that a particle's x weights take one LDS
+// read instead of P.  The s_nop covers the two wait states between a VALU write of w (a register copy)
+// and its use as a DPP operand.
+#define EWALD_FMAC3(a0, a1, a2, k)                                                               \
+    "v_fmac_f64_dpp %" #a0 ", %[w], %[g0] row_newbcast:%c[" #k "] row_mask:0xf bank_mask:0xf\n\t" \
+    "v_fmac_f64_dpp %" #a1 ", %[w], %[g1] row_newbcast:%c[" #k "] row_mask:0xf bank_mask:0xf\n\t" \
+    "v_fmac_f64_dpp %" #a2 ", %[w], %[g2] row_newbcast:%c[" #k "] row_mask:0xf bank_mask:0xf\n\t"
+#define EWALD_ACC3(k) "+v"(a[k][0]), "+v"(a[k][1]), "+v"(a[k][2])
+template <int K0, int P>
+__device__ inline void spread(double (*acc)[3], double w, double g0, double g1, double g2)
+{
+    double(*a)[3] = acc + K0;
+    if constexpr (K0 + 4 <= P) {
+        asm("s_nop 1\n\t" EWALD_FMAC3(0, 1, 2, k0) EWALD_FMAC3(3, 4, 5, k1) EWALD_FMAC3(6, 7, 8, k2)
+                EWALD_FMAC3(9, 10, 11, k3)
+            : EWALD_ACC3(0), EWALD_ACC3(1), EWALD_ACC3(2), EWALD_ACC3(3)
+            : [w] "v"(w), [g0] "v"(g0), [g1] "v"(g1), [g2] "v"(g2), [k0] "n"(K0), [k1] "n"(K0 + 1),
+              [k2] "n"(K0 + 2), [k3] "n"(K0 + 3));
+    } else {
+        asm("s_nop 1\n\t" EWALD_FMAC3(0, 1, 2, k0) EWALD_FMAC3(3, 4, 5, k1)
+            : EWALD_ACC3(0), EWALD_ACC3(1)
+            : [w] "v"(w), [g0] "v"(g0), [g1] "v"(g1), [g2] "v"(g2), [k0] "n"(K0), [k1] "n"(K0 + 1));
+    }
+    if constexpr (K0 + 4 < P) spread<K0 + 4, P>(acc, w, g0, g1, g2);
+}
+#undef EWALD_FMAC3
+#undef EWALD_ACC3
+
+// the value of another lane of this lane's four
+template <int kPerm>
+__device__ inline int quad_lane(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, kPerm, 0xf, 0xf, true);
+}
+
+// A block of kWaves waves owns one patch and the x-segment [x0, x0 + seg).  It takes the segment in
+// windows of up to kWindow slabs (their run table in LDS) and a window in passes.  In a pass every
+// wave spreads its share of the particles into a register window of kSlabs + P - 1 points, four slabs
+// wide, without any barrier or output; then the waves' windows are merged through LDS in a fixed order,
+// the points that no later slab reaches are written, and the other P - 1 are carried to the next pass.
+// Either each wave takes four slabs of its own (one pass per window), or, where the slabs' particles
+// are so uneven (clusters) that the waves would wait for one of them, all waves share each group of
+// four slabs (a pass per group), whichever costs less for the window at hand.  The first and last
+// P - 1 points of a segment also receive from the neighbouring segments: they go, as partial sums, to
+// halo planes (head[s][k] and tail[s][k] hold the points x0 - P/2 + 1 + k and x1 - P/2 + 1 + k), and
+// k_p2g_halo_sum adds them into the grid.  Fold (M1 = 8 < P: one segment, shorter than the stencil):
+// the points are added modulo M1 instead, each wave keeping its two of the eight.
+//
+// What bounds it: FP64 FMAs at the patches' lane efficiency where particles are dense (c2: 3P FMAs of
+// 56 instructions per particle and patch, two waves per SIMD by the 6 (kSlabs + P - 1) accumulator
+// registers, VALU 67% busy); latency of the tables and staging where they are sparse.  A form that
+// merged and wrote one point per slab (four waves sharing every slab, four barriers each) spent
+// 14 thousand cycles a slab on 30 particles.  P2G ms with that form and with this one: 1e6 uniform on
+// 256^3, P = 16 3.01 -> 1.75, P = 8 (FP32) 2.17 -> 0.64; 24 systems of 5e3 on 64^3 0.85 -> 0.29; 1.5e5 on
+// 128 x 128 x 256 0.71 -> 0.37; 1e3 on 32^3 0.083 -> 0.032; dense grids: c2 1.46 -> 1.40, H 0.91 -> 0.76, c4
+// 4.38 -> 4.17, c3 8.8 -> 8.5; one loss: 2e4 in two clusters of five cells 0.46 -> 0.53 (few patches hold
+// everything, and a lone wave per SIMD pays the staging's latency).
+//
+// Staging: 16 particles at a time, four lanes each (two halves of the x weights, the y and the z
+// weights of the patch's lines, zero off the footprint), every lane by one recurrence of at most eight
+// steps; the next particles' records are fetched while these are spread.
+template <typename TG, int P, bool Fold>
+__global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(const Rec64* __restrict__ rec,
                                                            const int* __restrict__ start, Geometry g,
-                                                           WinArgs<T> wa, int seg, int npy, int npz,
+                                                           WinArgs<double> wa, int seg, int npy, int npz,
                                                            const double* __restrict__ sv, int sv_off,
                                                            TG* __restrict__ grid, double* __restrict__ halo,
                                                            int64_t grid_stride, int64_t halo_stride)
 {
+    constexpr int W = kPatch + P - 1;
+    constexpr int kPts = kSlabs + P - 1;                             // points of a wave's register window
+    constexpr int kOut = (kWindow + P - 1 + kWaves - 1) / kWaves;    // points a wave merges, at most
+    constexpr int kCarry = (P - 1 + kWaves - 1) / kWaves;            // points a wave carries
+    // staged particle: P x weights, 8 y weights, 8 z weights, f (an odd row length: the rows of
+    // consecutive particles start in different banks)
+    constexpr int kRow = P + 2 * kPatch + 3;
+    constexpr int kStage = kWaves * kBatch * kRow, kMerge = kWaves * kPts * kWave;
+    __shared__ double smem[kStage > kMerge ? kStage : kMerge];
+    __shared__ int run_start[kTable], run_pre[kTable];
+    __shared__ int slab_n[kWindow];
+
     // system blockIdx.y of a batch: its cell list, grid and halo planes
     start += (int64_t)blockIdx.y * g.ncells;
     grid += (int64_t)blockIdx.y * grid_stride;
-    if (halo) halo += (int64_t)blockIdx.y * halo_stride;
-    constexpr int W = kPatch + P - 1;
-    __shared__ int run_start[kMaxRuns];
-    __shared__ int run_pre[kMaxRuns + 1];
-    __shared__ T swx[kChunk][P];             // x weights of the staged particles
-    __shared__ T swy[kChunk][kPatch];        // y weight of each patch line (0 off the footprint)
-    __shared__ T swz[kChunk][3][kPatch];     // z weight of each patch line times the 3 sources
-    __shared__ T sf[kChunk][3];
-    __shared__ T st[kChunk][3];  // in-cell fractions (Kaiser-Bessel weights are computed from them)
-    __shared__ int soff[kChunk];
-    __shared__ T red[kWaves - 1][3][64];
+    halo += (int64_t)blockIdx.y * halo_stride;
 
-    const int tid = threadIdx.x;
-    const int wid = tid >> 6, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int item = blockIdx.x;
     const int pz = item % npz, py = (item / npz) % npy, sx = item / (npz * npy);
     const int M1 = g.M[0], M2 = g.M[1], M3 = g.M[2];
-    const int x0 = sx * seg, x1 = min(x0 + seg, M1);
+    const int x0 = sx * seg;
     const int y0 = py * kPatch, z0 = pz * kPatch;
     const int ly = lane >> 3, lz = lane & 7;
     const int B = g.B;
-
-    const T e2 = exp((T)-2 * wa.beta);  // ratio of consecutive Gaussian recurrence factors
-    T acc[P][3];
-#pragma unroll
-    for (int k = 0; k < P; ++k) acc[k][0] = acc[k][1] = acc[k][2] = (T)0;
 
     const int zlo = z0 - P / 2, zhi = z0 + kPatch - 1 + P / 2 - 1;
     const int zt0 = floor_div(zlo, B), zt1 = floor_div(zhi, B);
     const int nzs = zt1 - zt0 + 1;
     const int R = W * nzs;
-    const int64_t nc = g.ncells;
+    const int nzs_inv = 65536 / nzs + 1;  // r / nzs = (r nzs_inv) >> 16 for r < kMaxRuns
+    int wn = min(kWindow, seg);
+    while (wn * (R + 1) > kTable) wn >>= 1;
 
-    // Output steps: the partial sums of the waves are added in a fixed order through LDS and
-    // the sum of wave 0 goes to dst[0], dst[cs], dst[2 cs] (the three components).
-    auto output = [&](T a0, T a1, T a2, auto* dst, int64_t cs) {
-        if (wid > 0) {
-            red[wid - 1][0][lane] = a0;
-            red[wid - 1][1][lane] = a1;
-            red[wid - 1][2][lane] = a2;
-        }
-        __syncthreads();
-        if (wid == 0) {
-#pragma unroll
-            for (int k = 0; k < kWaves - 1; ++k) {
-                a0 += red[k][0][lane];
-                a1 += red[k][1][lane];
-                a2 += red[k][2][lane];
-            }
-            using D = typename std::remove_pointer<decltype(dst)>::type;
-            dst[0] = (D)a0;
-            dst[cs] = (D)a1;
-            dst[2 * cs] = (D)a2;
-        }
-    };
-    // With halo == nullptr the segment's sweep starts P - 1 slabs early (a warm-up that makes its
-    // first points complete).  With a halo buffer it sweeps only its own slabs [x0, x1): its first
-    // and last P - 1 points are then partial, and go to the halo's head and tail planes of this
-    // segment (head[s][k] and tail[s][k] hold the point x0 - P/2 + 1 + k and x1 - P/2 + 1 + k);
-    // k_p2g_halo_sum adds tail[s - 1] to head[s] into the grid.
+    // this lane's part of a staged particle (see above)
+    const int role = lane & 3, axis = role < 2 ? 0 : role - 1;
+    const double h = g.h[axis];
+    const double e2 = exp(-2.0 * wa.beta);  // ratio of consecutive Gaussian recurrence factors
+    double* const row0 = smem + wid * kBatch * kRow;
+    double* const mine = row0 + (lane >> 2) * kRow;
+
+    const int64_t nc = g.ncells;
     const int64_t m23 = (int64_t)M2 * M3;
-    const int64_t line = (int64_t)(y0 + ly) * M3 + (z0 + lz);
+    const unsigned line = (unsigned)((y0 + ly) * M3 + (z0 + lz));
     const int hk = P - 1;
-    double* head = halo ? halo + (int64_t)sx * hk * 3 * m23 + line : nullptr;
-    double* tail = halo ? halo + ((int64_t)gridDim.x / (npy * npz) + sx) * hk * 3 * m23 + line : nullptr;
-    const int cbeg = halo ? x0 : x0 - P / 2, cend = halo ? x1 - 1 : x1 + P / 2 - 2;
-    for (int cxu = cbeg; cxu <= cend; ++cxu) {
-        const int cx = wrapi(cxu, M1);
-        // runs of this slab: one per (window row, z-tile segment); wave 0 builds the table
-        int carry = 0;
-        if (wid == 0) {
+    double* const head = halo + (int64_t)sx * hk * 3 * m23;
+    double* const tail = halo + ((int64_t)gridDim.x / (npy * npz) + sx) * hk * 3 * m23;
+
+    double carry[kCarry][3];
+#pragma unroll
+    for (int i = 0; i < kCarry; ++i) carry[i][0] = carry[i][1] = carry[i][2] = 0.0;
+    double folded[2][3] = {};  // Fold: points wid and wid + 4 modulo 8
+
+    for (int sb = 0; sb < seg; sb += wn) {
+        // run table of the window's slabs: one run per (window row, z-tile segment); entry r of slab s
+        // holds the run's first particle and the number of the slab's particles before it, entry R ends
+        // the slab's search
+        for (int s = wid; s < wn; s += kWaves) {
+            const int cx = wrapi(x0 + sb + s, M1);
+            int before = 0;
             for (int r0 = 0; r0 < R; r0 += kWave) {
                 const int r = r0 + lane;
-                int len = 0;
+                int len = 0, st = 0;
                 if (r < R) {
-                    const int iy = r / nzs, zs = r - iy * nzs;
+                    const int iy = (r * nzs_inv) >> 16, zs = r - iy * nzs;
                     const int cy = wrapi(y0 - P / 2 + iy, M2);
                     const int zt = zt0 + zs;
                     const int au = max(zlo, zt * B), bu = min(zhi, zt * B + B - 1);
                     const int k0 = cell_key(cx, cy, wrapi(au, M3), g);
-                    const int st = start[k0];
+                    st = start[k0];
                     len = start[k0 + (bu - au) + 1] - st;
-                    run_start[r] = st;
                 }
                 int inc = len;
 #pragma unroll
@@ -140,158 +176,224 @@ __global__ __launch_bounds__(kWaves * 64) void k_p2g_sweep(const typename RecVie
                     const int y = __shfl_up(inc, o, kWave);
                     if (lane >= o) inc += y;
                 }
-                if (r < R) run_pre[r + 1] = carry + inc;
-                carry += __shfl(inc, kWave - 1, kWave);
+                if (r < R) {
+                    run_start[s * (R + 1) + r] = st;
+                    run_pre[s * (R + 1) + r] = before + inc - len;
+                }
+                before += __shfl(inc, kWave - 1, kWave);
             }
-            if (lane == 0) run_pre[0] = 0;
+            if (lane == 0) {
+                slab_n[s] = before;
+                run_pre[s * (R + 1) + R] = INT_MAX;
+            }
         }
         __syncthreads();
-        const int total = __builtin_amdgcn_readfirstlane(run_pre[R]);
 
-        // the slab's particles are split evenly over the waves; each wave stages and spreads
-        // its share in rounds of kPerWave
-        const int share = (total + kWaves - 1) / kWaves;
-        const int wend = min(total, (wid + 1) * share);
-        const int q0 = wid * kPerWave;
-        for (int base = wid * share; base < wend; base += kPerWave) {
-            const int cnt = min(kPerWave, wend - base);
-            if (lane < cnt) {
-                const int flat = base + lane;
-                int lo = 0, hi = R;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (run_pre[mid] <= flat) lo = mid; else hi = mid;
-                }
-                const int r = lo;
-                const int p = run_start[r] + (flat - run_pre[r]);
-                int c[3];
-                T t[3], f[3];
-                RecView<T>::load(rec[p], g, c, t, f);
-                if (sv) {  // spread three stresslet components instead of the force
+        // one pass with four slabs per wave, or a pass per group of four slabs
+        const int groups = wn / kSlabs;
+        int most = 0, shared = 0;
+        for (int j = 0; j < groups; ++j) {
+            int c = 0;
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) f[d] = (T)sv[6 * (int64_t)p + sv_off + d];
-                }
-                const int iy = r / nzs, zs = r - iy * nzs;
-                const int oy = iy - (P - 1);  // stencil anchor - y0
-                const int czu = (zt0 + zs) * B + (c[2] & (B - 1));
-                const int oz = czu - P / 2 + 1 - z0;
-                const int q = q0 + lane;
-                soff[q] = (oy + P) | ((oz + P) << 8);
+            for (int k = 0; k < kSlabs; ++k) c += slab_n[j * kSlabs + k];
+            most = max(most, c);
+            shared += (c + kWaves - 1) / kWaves + kMergeCost;
+        }
+        const bool split = __builtin_amdgcn_readfirstlane(shared < most + kMergeCost ? 1 : 0) != 0;
+        const int passes = split ? groups : 1, pn = split ? kSlabs : wn;
+        for (int pass = 0; pass < passes; ++pass) {
+            const int sa = (split ? pass : wid) * kSlabs;  // this wave's first slab
+            int G[kSlabs + 1];  // particles of its slabs before slab k
+            G[0] = 0;
 #pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    sf[q][d] = f[d];
-                    st[q][d] = t[d];
-                }
-            }
-            wave_lds_sync();
-            if (!wa.kb) {
-                // Gaussian x weights: two lanes per particle, P/2 consecutive weights each by the
-                // same recurrence (two exponentials per lane)
-                for (int li = lane; li < 2 * cnt; li += kWave) {
-                    const int qq = q0 + (li >> 1), j0 = (li & 1) * (P / 2);
-                    const T t = st[qq][0];
-                    const T u0 = (T)(j0 - (P / 2 - 1)) - t;
-                    T w = exp(-wa.beta * u0 * u0);
-                    T r = exp(-wa.beta * ((T)2 * u0 + (T)1));
+            for (int k = 0; k < kSlabs; ++k)
+                G[k + 1] = G[k] + (sa < wn ? __builtin_amdgcn_readfirstlane(slab_n[sa + k]) : 0);
+            const int all = G[kSlabs];
+            const int share = split ? (all + kWaves - 1) / kWaves : all;
+            const int fa = split ? min(all, wid * share) : 0, fb = split ? min(all, fa + share) : all;
+
+            double acc[kPts][3];
 #pragma unroll
-                    for (int l = 0; l < P / 2; ++l) {
-                        swx[qq][j0 + l] = (j0 + l == P - 1 && t == (T)0) ? (T)0 : w;
-                        w *= r;
-                        r *= e2;
+            for (int k = 0; k < kPts; ++k) acc[k][0] = acc[k][1] = acc[k][2] = 0.0;
+
+            // A particle of the wave's share, from its place in the order of the slabs' run tables
+            // (places past the last repeat it): its index, and the stencil offset of this lane's first
+            // weight (for z without the cell's offset in its tile).  The four lanes of a particle search
+            // its run together, four ways a step.
+            int idx = 0, off = 0;
+            auto locate = [&](int base) {
+                const int flat = min(base + (lane >> 2), fb - 1);
+                int k = 0, at = 0;
+#pragma unroll
+                for (int j = 1; j < kSlabs; ++j)
+                    if (flat >= G[j]) {
+                        k = j;
+                        at = G[j];
                     }
+                const int tb = (sa + k) * (R + 1), t = flat - at;
+                int lo = 0;
+                auto step = [&](int s) {
+                    int below = run_pre[tb + min(lo + s * (role + 1), R)] <= t ? 1 : 0;
+                    below += quad_lane<0xb1>(below);  // lane ^ 1
+                    below += quad_lane<0x4e>(below);  // lane ^ 2
+                    lo += s * below;
+                };
+                if (R > 256) step(256);
+                step(64);
+                step(16);
+                step(4);
+                step(1);
+                idx = run_start[tb + lo] + (t - run_pre[tb + lo]);
+                const int iy = (lo * nzs_inv) >> 16, zs = lo - iy * nzs;
+                off = role < 2 ? role * (P / 2) : role == 2 ? P - 1 - iy : z0 + P / 2 - 1 - (zt0 + zs) * B;
+            };
+            struct Part {  // what this lane reads of a particle
+                double x, f0, f1, f2;
+                int c, off;
+            } p;
+            auto fetch = [&]() {
+                const Rec64& q = rec[idx];
+                p.x = q.x[axis];
+                p.c = q.c[axis];
+                p.off = off;
+                if (role == 3) {
+                    const double* f = sv ? sv + 6 * (int64_t)idx + sv_off : q.f;
+                    p.f0 = f[0];
+                    p.f1 = f[1];
+                    p.f2 = f[2];
                 }
-                // y and z weights of the patch's lines, one lane per (particle, axis): line l is at
-                // stencil offset j = l - o and distance u0 + l from the particle, and the Gaussian
-                // obeys w(u + 1) = w(u) exp(-beta (2u + 1)): two exponentials and 2 x 8 products
-                for (int li = lane; li < 2 * cnt; li += kWave) {
-                    const int qq = q0 + (li >> 1);
-                    const bool isy = (li & 1) == 0;
-                    const int off = soff[qq];
-                    const int o = (isy ? (off & 255) : (off >> 8)) - P;  // stencil anchor - patch origin
-                    const T t = st[qq][isy ? 1 : 2];
-                    const T u0 = (T)(-o - (P / 2 - 1)) - t;
-                    T w = exp(-wa.beta * u0 * u0);
-                    T r = exp(-wa.beta * ((T)2 * u0 + (T)1));
-                    T wl[kPatch];
+            };
+            auto stage = [&]() {
+                const double t = p.x / h - (double)p.c;
+                const int j0 = p.off - (role == 3 ? (p.c & (B - 1)) : 0);
+                const unsigned support = t == 0.0 ? P - 1 : P;  // open: no weight at distance P/2
+                double* const to = mine + (role < 2 ? role * (P / 2) : P + (role - 2) * kPatch);
+                if (!wa.kb) {
+                    // w(u + 1) = w(u) exp(-beta (2u + 1)) from u0, the distance of offset j0
+                    const double u0 = (double)(j0 - (P / 2 - 1)) - t;
+                    double w = exp(-wa.beta * u0 * u0);
+                    double r = exp(-wa.beta * (2.0 * u0 + 1.0));
 #pragma unroll
                     for (int l = 0; l < kPatch; ++l) {
-                        const int j = l - o;
-                        const bool in = (unsigned)j < (unsigned)P && !(j == P - 1 && t == (T)0);
-                        wl[l] = in ? w : (T)0;
+                        if (l < P / 2 || role >= 2) to[l] = (unsigned)(j0 + l) < support ? w : 0.0;
                         w *= r;
                         r *= e2;
                     }
-                    if (isy) {
+                } else {
 #pragma unroll
-                        for (int l = 0; l < kPatch; ++l) swy[qq][l] = wl[l];
-                    } else {
-                        const T f0 = sf[qq][0], f1 = sf[qq][1], f2 = sf[qq][2];
+                    for (int l = 0; l < kPatch; ++l) {
+                        const int j = j0 + l;
+                        if (l < P / 2 || role >= 2)
+                            to[l] = (unsigned)j < support ? window_weight_one<double, P>(j, t, wa) : 0.0;
+                    }
+                }
+                if (role == 3) {
+                    mine[P + 2 * kPatch] = p.f0;
+                    mine[P + 2 * kPatch + 1] = p.f1;
+                    mine[P + 2 * kPatch + 2] = p.f2;
+                }
+            };
+
+            if (fa < fb) {
+                locate(fa);
+                fetch();
+            }
+            for (int base = fa; base < fb; base += kBatch) {
+                const int cnt = min(kBatch, fb - base);
+                locate(base + kBatch);
+                stage();
+                wave_lds_sync();
+                fetch();
+                // single-value LDS loads (a paired load occupies the LDS pipeline twice as long), those of
+                // particle q + 1 ahead of the sums of particle q
+                const double* r = row0;
+                double nx = ld1(r[lane & 15]), ny = ld1(r[P + ly]), nz = ld1(r[P + kPatch + lz]);
+                double n0 = ld1(r[P + 2 * kPatch]), n1 = ld1(r[P + 2 * kPatch + 1]), n2 = ld1(r[P + 2 * kPatch + 2]);
+                int q = 0;
 #pragma unroll
-                        for (int l = 0; l < kPatch; ++l) {
-                            swz[qq][0][l] = wl[l] * f0;
-                            swz[qq][1][l] = wl[l] * f1;
-                            swz[qq][2][l] = wl[l] * f2;
+                for (int k = 0; k < kSlabs; ++k)
+                    for (const int qe = min(cnt, G[k + 1] - base); q < qe; ++q) {
+                        const double w = nx, wyz = ny * nz;
+                        const double g0 = wyz * n0, g1 = wyz * n1, g2 = wyz * n2;
+                        r = row0 + min(q + 1, kBatch - 1) * kRow;
+                        nx = ld1(r[lane & 15]);
+                        ny = ld1(r[P + ly]);
+                        nz = ld1(r[P + kPatch + lz]);
+                        n0 = ld1(r[P + 2 * kPatch]);
+                        n1 = ld1(r[P + 2 * kPatch + 1]);
+                        n2 = ld1(r[P + 2 * kPatch + 2]);
+                        spread<0, P>(acc + k, w, g0, g1, g2);
+                    }
+                wave_lds_sync();
+            }
+
+            // merge, one component at a time: wave w sums the points p = w, w + 4, ... of the pass over
+            // the carried sums and the waves in order
+            const int last = pn + P - 1;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < kPts; ++k) smem[(wid * kPts + k) * kWave + lane] = acc[k][c];
+                __syncthreads();
+                double v[kOut];
+#pragma unroll
+                for (int i = 0; i < kOut; ++i) {
+                    v[i] = i < kCarry ? carry[i < kCarry ? i : 0][c] : 0.0;
+                    const int p = wid + kWaves * i;
+                    if (p < last) {
+#pragma unroll
+                        for (int q = 0; q < kWaves; ++q) {
+                            const int k = split ? p : p - q * kSlabs;
+                            if ((unsigned)k < (unsigned)kPts) v[i] += smem[(q * kPts + k) * kWave + lane];
                         }
                     }
                 }
-            } else {
-                // Kaiser-Bessel: one polynomial per weight, spread over all lanes of the wave
-                for (int k = lane; k < cnt * P; k += kWave) {
-                    const int qq = q0 + k / P, j = k % P;
-                    swx[qq][j] = window_weight_one<T, P>(j, st[qq][0], wa);
-                }
-                for (int k = lane; k < cnt * 2 * kPatch; k += kWave) {
-                    const int qq = q0 + k / (2 * kPatch), l = k % kPatch;
-                    const bool isy = (k / kPatch) % 2 == 0;
-                    const int off = soff[qq];
-                    const int j = l + P - (isy ? (off & 255) : (off >> 8));  // stencil offset of line l
-                    T wv = (T)0;
-                    if ((unsigned)j < (unsigned)P) wv = window_weight_one<T, P>(j, st[qq][isy ? 1 : 2], wa);
-                    if (isy) {
-                        swy[qq][l] = wv;
-                    } else {
-                        swz[qq][0][l] = wv * sf[qq][0];
-                        swz[qq][1][l] = wv * sf[qq][1];
-                        swz[qq][2][l] = wv * sf[qq][2];
+#pragma unroll
+                for (int i = 0; i < kWindow / kWaves; ++i) {
+                    const int p = wid + kWaves * i;
+                    if (p < pn) {
+                        const int at = sb + pass * kSlabs + p;  // point of the segment
+                        if constexpr (Fold) {
+                            if (at & kWaves) folded[1][c] += v[i];
+                            else folded[0][c] += v[i];
+                        } else if (at < hk) (head + ((int64_t)at * 3 + c) * m23)[line] = v[i];
+                        else (grid + (c * nc + (int64_t)(x0 - P / 2 + 1 + at) * m23))[line] = (TG)v[i];
                     }
                 }
-            }
-            wave_lds_sync();
-#pragma unroll 2
-            for (int q = q0; q < q0 + cnt; ++q) {
-                // single-value LDS loads (a paired load occupies the LDS pipeline twice as long)
-                const T wy = ld1(swy[q][ly]);
-                const T g0 = wy * ld1(swz[q][0][lz]), g1 = wy * ld1(swz[q][1][lz]), g2 = wy * ld1(swz[q][2][lz]);
+                // the points past the pass's slabs are carried
 #pragma unroll
-                for (int k = 0; k < P; ++k) {
-                    const T wx = swx[q][k];
-                    acc[k][0] += wx * g0;
-                    acc[k][1] += wx * g1;
-                    acc[k][2] += wx * g2;
+                for (int i = 0; i < kCarry; ++i) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int j = 1; j <= kWindow / kWaves; ++j)
+                        if (i + j < kOut && pn == j * kWaves) s = v[i + j < kOut ? i + j : 0];
+                    carry[i][c] = s;
                 }
             }
-            wave_lds_sync();
-        }
-
-        const int xo = cxu - P / 2 + 1;
-        if (halo && xo < x0 + P / 2)
-            output(acc[0][0], acc[0][1], acc[0][2], head + (int64_t)(xo - (x0 - P / 2 + 1)) * 3 * m23, m23);
-        else if (xo >= x0)
-            output(acc[0][0], acc[0][1], acc[0][2], grid + (int64_t)xo * m23 + line, nc);
-#pragma unroll
-        for (int k = 0; k + 1 < P; ++k) {
-            acc[k][0] = acc[k + 1][0];
-            acc[k][1] = acc[k + 1][1];
-            acc[k][2] = acc[k + 1][2];
-        }
-        acc[P - 1][0] = acc[P - 1][1] = acc[P - 1][2] = (T)0;
-        __syncthreads();
-    }
-    if (halo) {
-#pragma unroll
-        for (int k = 0; k < P - 1; ++k) {
-            output(acc[k][0], acc[k][1], acc[k][2], tail + (int64_t)k * 3 * m23, m23);
             __syncthreads();
+        }
+    }
+    if constexpr (Fold) {
+#pragma unroll
+        for (int i = 0; i < kCarry; ++i)  // points 8 + wid + 4 i
+#pragma unroll
+            for (int c = 0; c < 3; ++c) folded[i & 1][c] += carry[i][c];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int x = wrapi(wid + kWaves * i - P / 2 + 1, M1);
+                (grid + (c * nc + (int64_t)x * m23))[line] = (TG)folded[i][c];
+            }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kCarry; ++i) {
+            const int p = wid + kWaves * i;
+            if (p < hk) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) (tail + ((int64_t)p * 3 + c) * m23)[line] = carry[i][c];
+            }
         }
     }
 }
@@ -329,7 +431,8 @@ hipError_t launch_p2g_t(const Plan& pl, const Work& w, hipStream_t s, bool st, i
     const int seg = p2g_segment_length(g.M, P);
     const int nseg = g.M[0] / seg;
     const int blocks = nseg * npy * npz;
-    // the halo scheme needs every boundary point to lie in exactly two segments
+    // with halo planes every boundary point lies in exactly two segments; without (M1 = 8 < P, one
+    // segment) the sweep folds its points
     double* halo = seg >= P ? w.p2g_halo : nullptr;
     const int64_t halo_n = (int64_t)nseg * (P - 1) * 3 * g.M[1] * g.M[2];
     const int fix_blocks = (int)std::min<int64_t>((halo_n + 255) / 256, 4096);
@@ -338,12 +441,21 @@ hipError_t launch_p2g_t(const Plan& pl, const Work& w, hipStream_t s, bool st, i
     const int64_t gstride = (int64_t)(st ? 9 : 3) * g.ncells, hstride = p2g_halo_elems(pl);
     for (int ps = 0; ps < passes; ++ps) {
         TG* grid = (TG*)w.grid + (int64_t)3 * ps * g.ncells;
-        hipLaunchKernelGGL((k_p2g_sweep<double, TG, P>), dim3(blocks, nsys), dim3(kWaves * kWave), 0, s,
-                           (const Rec64*)w.rec, w.start, g, make_win_args<double>(pl), seg, npy, npz,
-                           ps == 0 ? nullptr : w.srec, 3 * (ps - 1), grid, halo, gstride, hstride);
-        if (halo)
+        const double* sv = ps == 0 ? nullptr : w.srec;
+        auto sweep = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(blocks, nsys), dim3(kWaves * kWave), 0, s, (const Rec64*)w.rec, w.start,
+                               g, make_win_args<double>(pl), seg, npy, npz, sv, 3 * (ps - 1), grid, halo, gstride,
+                               hstride);
+        };
+        if (halo) {
+            sweep(k_p2g_sweep<TG, P, false>);
             hipLaunchKernelGGL((k_p2g_halo_sum<TG>), dim3(fix_blocks, nsys), dim3(256), 0, s, (const double*)halo,
                                nseg, seg, P, g, grid, gstride, hstride);
+        } else if constexpr (P > 8) {
+            sweep(k_p2g_sweep<TG, P, true>);
+        } else {
+            return hipErrorInvalidValue;  // grids have at least 8 points: seg >= P
+        }
     }
     return hipGetLastError();
 }
