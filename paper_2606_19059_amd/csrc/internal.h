@@ -140,14 +140,14 @@ struct Plan {
 // Device pointers carved out of the caller's workspace.
 struct Work {
     int* key;        // [n]   sort key of each input particle; after the sort, its sorted position
-    int* perm;       // [n]   sorted slot -> original index (also carried in records)
-    int* count;      // [ncells]   histogram, then scatter cursor
+    int* perm;       // [n]   original indices, cell by cell
+    int* count;      // [ncells]   histogram
     int* start;      // [ncells+1] exclusive scan of count
     int* chunk_off;  // [ntiles+1] P2P wave work-list offsets
     int* part;       // scan partials
     int* cell_lists; // [cell_list_elems(n)] cells too large for a one-thread sort of their order
     void* rec;       // [n] Rec64, sorted order
-    double* u_near;  // [3][n] near field, sorted order
+    double* u_near;  // [3][n] near field, sorted order (cleared by the sort)
     double* srec;    // [n][6] symmetric stresslet tensors (xx, yy, zz, xy, xz, yz), sorted order
                      // (stresslet plans only)
     void* grid;      // 3 (9 for stresslet plans) x ncells reals (double or float), then the
@@ -182,9 +182,7 @@ hipError_t launch_fill_i32(int* p, int64_t count, int value, hipStream_t s);
 // *out (= 0 first when `reset`) += number of non-finite values among a[0..count)
 hipError_t launch_count_nonfinite(const double* a, int64_t count, int* out, hipStream_t s, bool reset = true);
 
-// Exclusive scan of in[0..count) into out[0..count] (out[count] = total); `part`
-// needs scan_part_elems(count) ints.
-hipError_t launch_exclusive_scan(const int* in, int* out, int count, int* part, hipStream_t s);
+// ints of the cell scan's block sums
 int scan_part_elems(int count);
 // ints of the sort's lists of large cells for n particles
 int64_t cell_list_elems(int64_t n);

@@ -532,7 +532,7 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
 // restricted to sources with a larger sorted index than the target; the mirrored offset
 // -D carries the same pairs.  The source side accumulates per ring entry in LDS and is
 // added to u^N with one FP64 atomic per component and source when the entry retires.
-// u^N is zeroed first.  The order of those atomic additions varies between runs, so
+// The sort zeroes u^N.  The order of those atomic additions varies between runs, so
 // results agree to rounding, not bitwise (the one-sided kernel above is the reproducible
 // variant).
 //
@@ -573,12 +573,6 @@ static_assert(kBalBatch == 32 && kSymRing == 64, "the mask, ring and queue sizes
 
 // wave ballot of a condition, without materialising it as an integer first
 __device__ inline unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-
-__global__ void k_zero_f64(double* __restrict__ p, int64_t count)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0.0;
-}
 
 // ST: stresslet sources too (srec: sorted symmetric tensors, 6 per particle); T^N is odd,
 // so the source side of a pair takes -T^N(r) S_target.
@@ -1134,8 +1128,6 @@ hipError_t launch_p2p(const Plan& pl, const Work& w, int n, hipStream_t s, bool 
     const int64_t fill = (23040 / waves - 1) | 1;
     const int kSplit = (int)std::min<int64_t>(33, std::max<int64_t>(kTileSplit, fill));
     const dim3 sgrid((unsigned)(waves * kSplit));
-    const int64_t cnt = 3 * (int64_t)n;
-    hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, w.u_near, cnt);
     if (st) {
         switch (lv) {
         case 0: launch_p2p_sym<double, 0, true>(w, n, s, g, a, sgrid, kSplit); break;

@@ -12,15 +12,25 @@ namespace ewald {
 
 namespace {
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
+constexpr int kScanThreads = 1024;
+constexpr int kScanItems = 4;                          // consecutive elements per thread: 16-byte accesses
 constexpr int kScanChunk = kScanThreads * kScanItems;  // elements per block
+constexpr int kScanDirect = 4096;   // up to so many block sums every block adds those before it itself
+constexpr int kTilesDirect = 32768; // up to so many tiles one block scans the P2P work list
 
 __global__ void k_fill_i32(int* __restrict__ p, int64_t count, int value)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t k = i; k < count; k += stride) p[k] = value;
+}
+
+// count[0..ncells) = 0, and the lengths of the sort's two lists
+__global__ void k_clear(int* __restrict__ count, int ncells, int* __restrict__ lists)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    for (int k = i; k < ncells / 4; k += stride) reinterpret_cast<int4*>(count)[k] = int4{0, 0, 0, 0};
+    if (i < 2) lists[i] = 0;
 }
 
 // Periodic wrap into [0, L) and grid cell / fraction along one axis: c = floor(y/h),
@@ -38,9 +48,10 @@ __device__ inline void cell_of(double x, double L, double h, int M, int& c, doub
     t = s - (double)ci;
 }
 
-// key = system * ncells + cell key: the systems of a batch occupy consecutive key ranges
+// key = system * ncells + cell key: the systems of a batch occupy consecutive key ranges.  rank: the
+// particle's (arbitrary) place among those of its cell, so that the scatter needs no second counter.
 __global__ void k_bin(int n, const double* __restrict__ x, Geometry g, int* __restrict__ key,
-                      int* __restrict__ count, Batch b)
+                      int* __restrict__ rank, int* __restrict__ count, Batch b)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -50,30 +61,27 @@ __global__ void k_bin(int n, const double* __restrict__ x, Geometry g, int* __re
     for (int d = 0; d < 3; ++d) cell_of(x[(int64_t)d * n + i], g.L[d], g.h[d], g.M[d], c[d], t, wx);
     const int k = batch_system(b, i) * g.ncells + cell_key(c[0], c[1], c[2], g);
     key[i] = k;
-    atomicAdd(&count[k], 1);
+    rank[i] = atomicAdd(&count[k], 1);
 }
 
-__global__ void k_copy_i32(const int* __restrict__ a, int* __restrict__ b, int count)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) b[i] = a[i];
-}
-
-__global__ void k_scatter(int n, const int* __restrict__ key, int* __restrict__ cursor,
-                          int* __restrict__ perm)
+__global__ void k_scatter(int n, const int* __restrict__ key, const int* __restrict__ rank,
+                          const int* __restrict__ start, int* __restrict__ perm, double* __restrict__ u_near)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int slot = atomicAdd(&cursor[key[i]], 1);
-    perm[slot] = i;
+    perm[start[key[i]] + rank[i]] = i;
+    // the near field that the symmetric P2P adds to
+    u_near[i] = 0.0;
+    u_near[(int64_t)n + i] = 0.0;
+    u_near[2 * (int64_t)n + i] = 0.0;
 }
 
-// Order each cell's particles by original index, so that the sorted order (and every sum
-// taken in it) does not depend on the order of the scatter's atomics.  Cells of up to
-// kCellSerial particles are sorted here by one thread (insertion sort); larger ones are
-// appended to one of two lists (`lists[0]`, `lists[1]` hold their lengths) and sorted by
-// k_sort_mid_cells (one wavefront per cell, up to kCellMid particles) or k_sort_big_cells
-// (one block per cell, any size).  The lists' order varies, but each cell's result does not.
+// The order inside a cell is by original index, so that the sorted order (and every sum taken in it)
+// does not depend on the order of the scatter's atomics.  In cells of up to kCellSerial particles the
+// gather counts the smaller indices of each particle's cell; larger cells are appended to one of two
+// lists by the scan (`lists[0]`, `lists[1]` hold their lengths) and their indices sorted, by one
+// wavefront per cell up to kCellMid particles, by one block per cell above.  The lists' order varies,
+// but each cell's result does not.
 constexpr int kCellSerial = 16;
 constexpr int kCellMid = 256;
 constexpr int kBigThreads = 256;
@@ -82,47 +90,18 @@ constexpr int kBigRun = 8192;  // ints sorted in LDS at once (32 KB)
 __host__ __device__ inline int64_t mid_list_cap(int64_t n) { return n / (kCellSerial + 1) + 1; }
 __host__ __device__ inline int64_t big_list_cap(int64_t n) { return n / (kCellMid + 1) + 1; }
 
-__global__ void k_cell_order(int ncells, const int* __restrict__ start, int* __restrict__ perm,
-                             int* __restrict__ lists, int64_t mid_cap)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncells) return;
-    const int a = start[c], b = start[c + 1];
-    if (b - a < 2) return;
-    if (b - a > kCellMid) {
-        const int k = atomicAdd(&lists[1], 1);
-        lists[2 + mid_cap + k] = c;
-        return;
-    }
-    if (b - a > kCellSerial) {
-        const int k = atomicAdd(&lists[0], 1);
-        lists[2 + k] = c;
-        return;
-    }
-    for (int i = a + 1; i < b; ++i) {
-        const int v = perm[i];
-        int j = i - 1;
-        while (j >= a && perm[j] > v) {
-            perm[j + 1] = perm[j];
-            --j;
-        }
-        perm[j + 1] = v;
-    }
-}
-
 // One wavefront per listed cell (kCellSerial < size <= kCellMid): every lane holds up to
 // four of the cell's (distinct) indices, counts how many of the cell's indices are smaller
 // (a broadcast read of each from LDS) and writes its index at that rank.
-__global__ void __launch_bounds__(256) k_sort_mid_cells(const int* __restrict__ start, int* __restrict__ perm,
-                                                        const int* __restrict__ lists)
+__device__ void sort_mid_cells(const int* __restrict__ start, int* __restrict__ perm,
+                               const int* __restrict__ lists, int* sh, int block, int blocks)
 {
     constexpr int kPer = kCellMid / kWave;
-    __shared__ int sh[256 / kWave][kCellMid];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    int* s = sh[wv];
+    int* s = sh + wv * kCellMid;
     const int nmid = lists[0];
-    const int waves = gridDim.x * (blockDim.x / kWave);
-    for (int q = blockIdx.x * (blockDim.x / kWave) + wv; q < nmid; q += waves) {
+    const int waves = blocks * (blockDim.x / kWave);
+    for (int q = block * (blockDim.x / kWave) + wv; q < nmid; q += waves) {
         const int c = lists[2 + q];
         const int a = start[c], m = start[c + 1] - a;
         int v[kPer];
@@ -170,14 +149,12 @@ __device__ inline int count_below(const int* __restrict__ a, int len, int v)
 // its rank in the merged run (its offset in its own run plus the count of smaller indices
 // in the other, by binary search), ping-ponging between the cell's range of `perm` and
 // the same range of `scratch`.
-__global__ void __launch_bounds__(kBigThreads) k_sort_big_cells(const int* __restrict__ start, int* __restrict__ perm,
-                                                                int* __restrict__ scratch, const int* __restrict__ lists,
-                                                                int64_t mid_cap)
+__device__ void sort_big_cells(const int* __restrict__ start, int* __restrict__ perm, int* __restrict__ scratch,
+                               const int* __restrict__ lists, int64_t mid_cap, int* s, int block, int blocks)
 {
-    __shared__ int s[kBigRun];
     const int nbig = lists[1];
     const int tid = threadIdx.x;
-    for (int q = blockIdx.x; q < nbig; q += gridDim.x) {
+    for (int q = block; q < nbig; q += blocks) {
         const int c = lists[2 + mid_cap + q];
         const int a = start[c], m = start[c + 1] - a;
         int* v = perm + a;
@@ -227,18 +204,15 @@ __global__ void __launch_bounds__(kBigThreads) k_sort_big_cells(const int* __res
     }
 }
 
-// inv[perm[s]] = s: the sorted position of each input particle.  The gathers below then read the
-// caller's (3, N) arrays in their own order (coalesced) and write each whole record to its sorted
-// position; gathering through perm instead reads six arrays at random positions, which costs a full
-// memory segment per 8-byte value (15 times the bytes used at 1e6 uniform particles).
-__global__ void k_invert(int n, const int* __restrict__ perm, int* __restrict__ inv)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < n) inv[perm[s]] = s;
-}
-
+// Records in sorted order.  The sorted position of particle i is its cell's start plus the number of
+// smaller indices in the cell (counted where cells are small, by binary search where they have been
+// sorted); key[i] takes it, for k_gather_st.  The caller's (3, N) arrays are read in their own order
+// (coalesced) and each whole record is written to its sorted position; gathering through perm instead
+// reads six arrays at random positions, which costs a full memory segment per 8-byte value (15 times
+// the bytes used at 1e6 uniform particles).
 __global__ void k_gather64(int n, const double* __restrict__ x, const double* __restrict__ f,
-                           const int* __restrict__ inv, Geometry g, Rec64* __restrict__ rec)
+                           const int* __restrict__ start, const int* __restrict__ perm, int* __restrict__ key,
+                           Geometry g, Rec64* __restrict__ rec)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -250,7 +224,15 @@ __global__ void k_gather64(int n, const double* __restrict__ x, const double* __
         r.f[d] = f[(int64_t)d * n + i];
     }
     r.orig = i;
-    rec[inv[i]] = r;
+    const int k = key[i], a = start[k], m = start[k + 1] - a;
+    int pos = a;
+    if (m > kCellSerial) {
+        pos += count_below(perm + a, m, i);
+    } else if (m > 1) {
+        for (int j = 0; j < m; ++j) pos += perm[a + j] < i ? 1 : 0;
+    }
+    key[i] = pos;
+    rec[pos] = r;
 }
 
 // Symmetric part of each stresslet source tensor q n^T, in sorted order: the stresslet
@@ -271,17 +253,7 @@ __global__ void k_gather_st(int n, const double* __restrict__ q, const double* _
     o[5] = 0.5 * (q1 * n2 + q2 * n1);
 }
 
-// Number of 64-target waves per P2P tile (the tiles of all systems).
-__global__ void k_tile_chunks(Geometry g, const int* __restrict__ start, int* __restrict__ chunks)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= g.ntiles * g.nsys) return;
-    const int per = 1 << (3 * g.log2B);
-    const int cnt = start[(t + 1) * per] - start[t * per];
-    chunks[t] = (cnt + kWave - 1) / kWave;
-}
-
-// ---- exclusive scan (three phases: block sums, scan of sums, block scans) ----
+// ---- exclusive scan (block sums, scan of sums where there are many, block scans) ----
 
 __device__ inline int block_exclusive_scan(int v, int* sh, int& total)
 {
@@ -308,17 +280,24 @@ __device__ inline int block_exclusive_scan(int v, int* sh, int& total)
     return off + inc - v;
 }
 
-__global__ void k_scan_reduce(const int* __restrict__ in, int count, int* __restrict__ part)
+// a thread's kScanItems consecutive elements (0 past the end); the arrays are 256-byte aligned
+__device__ inline int4 scan_load(const int* __restrict__ in, int i, int count)
+{
+    if (i + 3 < count) return *reinterpret_cast<const int4*>(in + i);
+    int4 v = {0, 0, 0, 0};
+    if (i < count) v.x = in[i];
+    if (i + 1 < count) v.y = in[i + 1];
+    if (i + 2 < count) v.z = in[i + 2];
+    return v;
+}
+
+__global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const int* __restrict__ in, int count,
+                                                              int* __restrict__ part)
 {
     __shared__ int sh[kScanThreads / kWave];
-    const int base = blockIdx.x * kScanChunk;
-    int s = 0;
-    for (int k = 0; k < kScanItems; ++k) {
-        const int i = base + k * kScanThreads + threadIdx.x;
-        if (i < count) s += in[i];
-    }
+    const int4 v = scan_load(in, blockIdx.x * kScanChunk + threadIdx.x * kScanItems, count);
     int total;
-    block_exclusive_scan(s, sh, total);
+    block_exclusive_scan(v.x + v.y + v.z + v.w, sh, total);
     if (threadIdx.x == 0) part[blockIdx.x] = total;
 }
 
@@ -342,28 +321,96 @@ __global__ void k_scan_parts(int* __restrict__ part, int nb)
     if (threadIdx.x == 0) part[nb] = total;
 }
 
-__global__ void k_scan_final(const int* __restrict__ in, int count, const int* __restrict__ part,
-                             int* __restrict__ out, int nb)
+// Direct: part holds the block sums themselves, and every block adds those before it (a launch less);
+// otherwise their exclusive scan.  lists (or null): the cells of more than kCellSerial elements are
+// appended to the sort's lists.
+template <bool Direct>
+__global__ void __launch_bounds__(kScanThreads) k_scan_final(const int* __restrict__ in, int count,
+                                                             const int* __restrict__ part, int* __restrict__ out,
+                                                             int* __restrict__ lists, int64_t mid_cap)
 {
     __shared__ int sh[kScanThreads / kWave];
     const int base = blockIdx.x * kScanChunk + threadIdx.x * kScanItems;
-    int v[kScanItems];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        const int i = base + k;
-        v[k] = (i < count) ? in[i] : 0;
-        s += v[k];
+    const int4 v = scan_load(in, base, count);
+    int before = 0;
+    if (Direct) {
+        int s = 0;
+        for (int k = threadIdx.x; k < (int)blockIdx.x; k += kScanThreads) s += part[k];
+        block_exclusive_scan(s, sh, before);
+    } else {
+        before = part[blockIdx.x];
     }
     int total;
-    int off = block_exclusive_scan(s, sh, total) + part[blockIdx.x];
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        const int i = base + k;
-        if (i < count) out[i] = off;
-        off += v[k];
+    const int off = block_exclusive_scan(v.x + v.y + v.z + v.w, sh, total) + before;
+    const int4 o = {off, off + v.x, off + v.x + v.y, off + v.x + v.y + v.z};
+    if (base + 3 < count) {
+        *reinterpret_cast<int4*>(out + base) = o;
+    } else {
+        if (base < count) out[base] = o.x;
+        if (base + 1 < count) out[base + 1] = o.y;
+        if (base + 2 < count) out[base + 2] = o.z;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[count] = part[nb];
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[count] = before + total;
+    if (lists && max(max(v.x, v.y), max(v.z, v.w)) > kCellSerial) {
+        const int m[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (m[k] > kCellMid) lists[2 + mid_cap + atomicAdd(&lists[1], 1)] = base + k;
+            else if (m[k] > kCellSerial) lists[2 + atomicAdd(&lists[0], 1)] = base + k;
+        }
+    }
+}
+
+// Number of 64-target chunks of a P2P tile (the tiles of all systems).
+__device__ inline int tile_chunks(const Geometry& g, const int* __restrict__ start, int t)
+{
+    const int per = 1 << (3 * g.log2B);
+    return (start[(t + 1) * per] - start[t * per] + kWave - 1) / kWave;
+}
+
+__global__ void k_tile_chunks(Geometry g, const int* __restrict__ start, int* __restrict__ chunks)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < g.ntiles * g.nsys) chunks[t] = tile_chunks(g, start, t);
+}
+
+// Index order of the listed cells, and in block 0 the P2P work list (chunk_off: the exclusive scan of
+// the tiles' chunks; null where other kernels make it): one launch for what only waits for the
+// scatter.  `scratch` is the merge buffer of the largest cells.
+__global__ void __launch_bounds__(kBigThreads) k_order_cells(const int* __restrict__ start, int* __restrict__ perm,
+                                                             int* __restrict__ scratch, const int* __restrict__ lists,
+                                                             int64_t mid_cap, Geometry g, int* __restrict__ chunk_off)
+{
+    __shared__ int s[kBigRun];
+    static_assert(kBigRun >= kBigThreads / kWave * kCellMid, "one LDS row per wave");
+    if (blockIdx.x == 0) {
+        if (!chunk_off) return;
+        const int nt = g.ntiles * g.nsys;
+        int before = 0;
+        for (int t0 = 0; t0 < nt; t0 += 4 * kBigThreads) {
+            const int t = t0 + 4 * threadIdx.x;
+            int v[4], sum = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = t + k < nt ? tile_chunks(g, start, t + k) : 0;
+                sum += v[k];
+            }
+            int total;
+            int off = before + block_exclusive_scan(sum, s, total);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (t + k < nt) chunk_off[t + k] = off;
+                off += v[k];
+            }
+            before += total;
+        }
+        if (threadIdx.x == 0) chunk_off[nt] = before;
+        return;
+    }
+    const int block = blockIdx.x - 1, blocks = gridDim.x - 1;
+    sort_mid_cells(start, perm, lists, s, block, blocks);
+    __syncthreads();
+    sort_big_cells(start, perm, scratch, lists, mid_cap, s, block, blocks);
 }
 
 inline int blocks_for(int64_t n, int t) { return (int)((n + t - 1) / t); }
@@ -409,47 +456,49 @@ hipError_t launch_count_nonfinite(const double* a, int64_t count, int* out, hipS
     return hipGetLastError();
 }
 
-hipError_t launch_exclusive_scan(const int* in, int* out, int count, int* part, hipStream_t s)
+// Exclusive scan of in[0..count) into out[0..count] (out[count] = total); see k_scan_final
+static void launch_scan(const int* in, int* out, int count, int* part, int* lists, int64_t mid_cap, hipStream_t s)
 {
     const int nb = (count + kScanChunk - 1) / kScanChunk;
     hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kScanThreads), 0, s, in, count, part);
-    hipLaunchKernelGGL(k_scan_parts, dim3(1), dim3(1024), 0, s, part, nb);
-    hipLaunchKernelGGL(k_scan_final, dim3(nb), dim3(kScanThreads), 0, s, in, count, part, out, nb);
-    return hipGetLastError();
+    if (nb <= kScanDirect) {
+        hipLaunchKernelGGL((k_scan_final<true>), dim3(nb), dim3(kScanThreads), 0, s, in, count, part, out, lists,
+                           mid_cap);
+    } else {
+        hipLaunchKernelGGL(k_scan_parts, dim3(1), dim3(1024), 0, s, part, nb);
+        hipLaunchKernelGGL((k_scan_final<false>), dim3(nb), dim3(kScanThreads), 0, s, in, count, part, out, lists,
+                           mid_cap);
+    }
 }
 
+// Seven launches: clear, bin, two for the scan, scatter, order (with the P2P work list), gather.  Small
+// evaluations are bound by launches (about 4.5 us each behind one another).
 hipError_t launch_sort(const Plan& pl, const Work& w, int n, const double* x, const double* f,
                        const Batch& b, hipStream_t s)
 {
     Geometry g = pl.g;
     g.nsys = b.count;
     const int ncells = g.ncells * g.nsys, ntiles = g.ntiles * g.nsys;  // over all systems
-    hipError_t e = launch_fill_i32(w.count, ncells, 0, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bin, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, x, g, w.key, w.count, b);
-    e = launch_exclusive_scan(w.count, w.start, ncells, w.part, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_copy_i32, dim3(blocks_for(ncells, 256)), dim3(256), 0, s, w.start, w.count, ncells);
-    hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, w.key, w.count, w.perm);
-    // per-cell order by original index; the key array is free after the scatter and serves as
-    // the merge buffer of the largest cells
-    if ((e = launch_fill_i32(w.cell_lists, 2, 0, s)) != hipSuccess) return e;
+    int* rank = (int*)w.rec;  // the records come last
     const int64_t mid_cap = mid_list_cap(n);
-    hipLaunchKernelGGL(k_cell_order, dim3(blocks_for(ncells, 256)), dim3(256), 0, s, ncells, w.start,
-                       w.perm, w.cell_lists, mid_cap);
-    const int mid_blocks = (int)std::min<int64_t>(2048, std::max<int64_t>(1, mid_list_cap(n) / 4));
-    hipLaunchKernelGGL(k_sort_mid_cells, dim3(mid_blocks), dim3(256), 0, s, w.start, w.perm, w.cell_lists);
-    const int big_blocks = (int)std::min<int64_t>(512, big_list_cap(n));
-    hipLaunchKernelGGL(k_sort_big_cells, dim3(big_blocks), dim3(kBigThreads), 0, s, w.start, w.perm, w.key,
-                       w.cell_lists, mid_cap);
-    // the key array is free again: it takes the inverse permutation (read by both gathers)
-    hipLaunchKernelGGL(k_invert, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, w.perm, w.key);
-    hipLaunchKernelGGL(k_gather64, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, x, f, w.key, g,
+    const int clear_blocks = (int)std::min<int64_t>(65536, blocks_for(ncells, 1024));
+    hipLaunchKernelGGL(k_clear, dim3(clear_blocks), dim3(256), 0, s, w.count, ncells, w.cell_lists);
+    hipLaunchKernelGGL(k_bin, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, x, g, w.key, rank, w.count, b);
+    launch_scan(w.count, w.start, ncells, w.part, w.cell_lists, mid_cap, s);
+    hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, w.key, rank, w.start, w.perm,
+                       w.u_near);
+    // the rank array is free after the scatter and serves as the merge buffer of the largest cells
+    const bool direct = ntiles <= kTilesDirect;
+    const int order_blocks = 1 + (int)std::min<int64_t>(2048, std::max<int64_t>(1, mid_list_cap(n) / 4));
+    hipLaunchKernelGGL(k_order_cells, dim3(order_blocks), dim3(kBigThreads), 0, s, w.start, w.perm, rank,
+                       w.cell_lists, mid_cap, g, direct ? w.chunk_off : nullptr);
+    hipLaunchKernelGGL(k_gather64, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, x, f, w.start, w.perm, w.key, g,
                        (Rec64*)w.rec);
-    // P2P work list: waves per tile, then their offsets
-    hipLaunchKernelGGL(k_tile_chunks, dim3(blocks_for(ntiles, 256)), dim3(256), 0, s, g, w.start,
-                       w.count);
-    return launch_exclusive_scan(w.count, w.chunk_off, ntiles, w.part, s);
+    if (!direct) {
+        hipLaunchKernelGGL(k_tile_chunks, dim3(blocks_for(ntiles, 256)), dim3(256), 0, s, g, w.start, w.count);
+        launch_scan(w.count, w.chunk_off, ntiles, w.part, nullptr, 0, s);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_gather_st(const Plan& pl, const Work& w, int n, const double* q, const double* nrm,
