@@ -1125,8 +1125,11 @@ hipError_t launch_p2p(const Plan& pl, const Work& w, int n, hipStream_t s, bool 
     // 0.61 / 0.55 / 0.51 / 0.54 / 0.66; 3368 (1.5e5, FP64) 0.49 / 0.44 / 0.45 / 0.51 / 0.76; 19721 (1e6, 1e-8,
     // 256^3) 3.67 / 3.79 / 3.89 / 4.36 / 6.18.  Odd, so that the waves of a chunk, consecutive blocks, spread
     // over the XCDs (with 8 or 16, all the chunks' first waves, the heaviest, meet on one).
-    const int64_t fill = (23040 / waves - 1) | 1;
-    const int kSplit = (int)std::min<int64_t>(33, std::max<int64_t>(kTileSplit, fill));
+    // With stresslet sources fewer waves fit a CU (16 KB of LDS each) and the pairs cost more: 1294 chunks
+    // (5e4 at 1e-8) 0.26 / 0.23 / 0.24 / 0.27 / 0.45, 5200 (3e5, FP32) 1.89 / 1.73 / 1.70 / 1.82 / 2.31.
+    const int64_t fill = ((st ? 11520 : 23040) / waves - 1) | 1;
+    const int64_t least = st && waves < 8192 ? 5 : kTileSplit;
+    const int kSplit = (int)std::min<int64_t>(33, std::max(least, fill));
     const dim3 sgrid((unsigned)(waves * kSplit));
     if (st) {
         switch (lv) {
