@@ -22,19 +22,21 @@ namespace ewald {
 namespace {
 
 // Window weights and stencil anchors of NG consecutive sorted targets sg, sg + 1, ... (those
-// at or past s1 repeat target s1 - 1), by the 64 lanes of one wave: sw[q][d][j] is the weight
-// of stencil offset j along axis d of target q, anc[q][d] the (unwrapped) first stencil cell.
+// at or past s1 repeat target s1 - 1), by `lanes` threads of which this is number `lane`: sw[q][d][1 + j]
+// is the weight of stencil offset j along axis d of target q, between two zeros (sw[q][d][0] and
+// sw[q][d][P + 1], which serve all offsets off the stencil), anc[q][d] the (unwrapped) first
+// stencil cell.
 template <typename T, int P, int NG>
 __device__ inline void stage_weights(const typename RecView<T>::Rec* __restrict__ rec, const Geometry& g,
-                                     const WinArgs<T>& wa, int sg, int s1, T (*sw)[3][P], int (*anc)[3],
-                                     int lane)
+                                     const WinArgs<T>& wa, int sg, int s1, T (*sw)[3][P + 2], int (*anc)[3],
+                                     int lane, int lanes)
 {
     if (sizeof(T) == 8 && !wa.kb) {
         // FP64 Gaussian: two lanes per (target, axis), each walking P/2 weights away from the
         // peak by the recurrence w(u + s) = w(u) exp(-beta (2 s u + 1)), s = -1 for offsets
         // P/2-1 down to 0 and s = +1 for P/2 up to P-1 (two exponentials per lane)
         const T e2 = exp((T)-2 * wa.beta);  // ratio of consecutive recurrence factors
-        for (int k = lane; k < NG * 6; k += kWave) {
+        for (int k = lane; k < NG * 6; k += lanes) {
             const int qq = k / 6, d = (k >> 1) % 3, up = k & 1;
             int c[3];
             T t[3], f[3];
@@ -47,21 +49,25 @@ __device__ inline void stage_weights(const typename RecView<T>::Rec* __restrict_
 #pragma unroll
             for (int l = 0; l < P / 2; ++l) {
                 const int jj = up ? P / 2 + l : P / 2 - 1 - l;
-                sw[qq][d][jj] = (jj == P - 1 && td == (T)0) ? (T)0 : w;
+                sw[qq][d][1 + jj] = (jj == P - 1 && td == (T)0) ? (T)0 : w;
                 w *= r;
                 r *= e2;
             }
+            sw[qq][d][up ? P + 1 : 0] = (T)0;
             if (!up) anc[qq][d] = (d == 0 ? c[0] : (d == 1 ? c[1] : c[2])) - P / 2 + 1;
         }
     } else {
-        for (int k = lane; k < NG * 3 * P; k += kWave) {
+        for (int k = lane; k < NG * 3 * P; k += lanes) {
             const int qq = k / (3 * P), d = (k / P) % 3, jj = k % P;
             int c[3];
             T t[3], f[3];
             RecView<T>::load(rec[min(sg + qq, s1 - 1)], g, c, t, f);
             const T td = (d == 0) ? t[0] : (d == 1 ? t[1] : t[2]);
-            sw[qq][d][jj] = window_weight_one<T, P>(jj, td, wa);
-            if (jj == 0) anc[qq][d] = c[d] - P / 2 + 1;
+            sw[qq][d][1 + jj] = window_weight_one<T, P>(jj, td, wa);
+            if (jj == 0) {
+                anc[qq][d] = c[d] - P / 2 + 1;
+                sw[qq][d][0] = sw[qq][d][P + 1] = (T)0;
+            }
         }
     }
 }
@@ -115,43 +121,57 @@ struct G2PMat {
     typedef typename std::conditional<f32, float, double>::type S;
     typedef typename std::conditional<f32, g2p_v4f, g2p_v4d>::type V4;
 };
-constexpr int kMG = 16;     // targets per wave (matrix rows)
-constexpr int kMWaves = 4;  // waves per block: one 64-target chunk of a tile
+constexpr int kMG = 16;     // targets per group (matrix rows)
+constexpr int kMWaves = 4;  // waves per block
 
 // column blocks of a plan: 3 (B + P - 1) columns
 constexpr int g2p_mfma_blocks(int B, int P) { return (3 * (B + P - 1) + 15) / 16; }
 
-// Up to five column blocks the FP64 kernel is bounded to 96 VGPRs (five waves per SIMD instead of
-// four): the loads of a step wait on L2 most of the time, and the fifth wave hides more of it
-// (c3 5.73 -> 5.47 ms, H 0.79 -> 0.77 ms, c2 unchanged); six blocks would spill under that bound.
-// The FP32 kernel fits eight waves (64 VGPRs) up to four blocks, and five below P = 16; six
-// otherwise.
+// Two forms of the kernel:
+//   a wave per 16 targets, four per block (a 64-target chunk);
+//   Split: four waves of a block share the contraction of 16 targets, a quarter of the box's points
+//   each, their sums added in wave order: few or sparse targets on FP64 grids, where a wave's chain of
+//   dependent loads is the time, or (large sparse boxes) the waves of a chunk evict each other's grid
+//   lines.  FP32 grids keep one order of their FP32 sums.
+// What bounds a step: NB matrix instructions (64 cycles each in FP64, during which the SIMD issues no
+// vector instruction) plus the vector instructions of the operands and addresses, about 25 with the
+// zero-padded weight rows and shifted byte offsets (45 and two quarter-rate multiplications before:
+// c2 1.22 -> 1.11 ms, H 0.56 -> 0.52, c4 3.66 -> 3.48, c3 4.15 -> 3.96).  Two row blocks per wave, which
+// halve the grid loads, were no faster (c2 1.20 ms, c4 3.38, 1.5e5 on 128 x 128 x 256 0.45 against 0.41).
+//
+// Waves per SIMD (register bound) of the first form: up to five column blocks the FP64 kernel is
+// bounded to 96 VGPRs (five waves per SIMD instead of four): the loads of a step wait on L2 most of
+// the time, and the fifth wave hides more of it (c3 5.73 -> 5.47 ms, H 0.79 -> 0.77 ms, c2 unchanged);
+// six blocks would spill under that bound.  The FP32 kernel fits eight waves (64 VGPRs) up to four
+// blocks, and five below P = 16; six otherwise.
 template <typename T, typename TG, int P, int NB>
 constexpr int g2p_waves()
 {
     return G2PMat<T, TG>::f32 ? ((NB <= 4 || (NB == 5 && P < 16)) ? 8 : 6) : (NB <= 5 ? 5 : 4);
 }
-template <typename T, typename TG, int P, int NB>
-__global__ __launch_bounds__(kMWaves * 64) __attribute__((amdgpu_waves_per_eu(g2p_waves<T, TG, P, NB>()))) void k_g2p_mfma(const typename RecView<T>::Rec* __restrict__ rec,
-                                                           const int* __restrict__ start,
-                                                           const int* __restrict__ chunk_off,
-                                                           const TG* __restrict__ grid, Geometry g, WinArgs<T> wa,
-                                                           double self_coef, const double* __restrict__ u_near,
-                                                           const double* __restrict__ f_in, double* __restrict__ u,
-                                                           double* __restrict__ u_near_out,
-                                                           double* __restrict__ u_far_out, int n)
+
+template <typename T, typename TG, int P, int NB, bool Split>
+__global__ __launch_bounds__(kMWaves * 64) __attribute__((amdgpu_waves_per_eu(g2p_waves<T, TG, P, NB>())))
+void k_g2p_mfma(const typename RecView<T>::Rec* __restrict__ rec, const int* __restrict__ start,
+                const int* __restrict__ chunk_off, const TG* __restrict__ grid, Geometry g, WinArgs<T> wa,
+                double self_coef, const double* __restrict__ u_near, const double* __restrict__ f_in,
+                double* __restrict__ u, double* __restrict__ u_near_out, double* __restrict__ u_far_out, int n)
 {
-    __shared__ T sw[kMWaves][kMG][3][P];
-    __shared__ int anc[kMWaves][kMG][3];
+    constexpr int kSets = Split ? 1 : kMWaves;  // target groups per block
+    __shared__ T sw[kSets][kMG][3][P + 2];
+    __shared__ int anc[kSets][kMG][3];
     typedef typename G2PMat<T, TG>::S TM;
     // rows of D held by a lane: 4 r + quarter (FP64 instruction) or 4 quarter + r (FP32)
     constexpr bool kRowsGrouped = G2PMat<T, TG>::f32;
-    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int nt = g.ntiles * g.nsys;
     const int total = chunk_off[nt];  // 64-target chunks of all tiles of all systems
-    if ((int)blockIdx.x >= total) return;
+    const int items = Split ? total * (kWave / kMG) : total;
+    if ((int)blockIdx.x >= items) return;
     // blocks are dealt to the 8 XCDs round robin: each XCD takes one contiguous range of chunks
-    const int chunk = xcd_remap((int)blockIdx.x, total);
+    const int item = xcd_remap((int)blockIdx.x, items);
+    const int chunk = Split ? item / (kWave / kMG) : item;
+    const int set = Split ? 0 : wid;
     int lo = 0, hi = nt;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -160,13 +180,21 @@ __global__ __launch_bounds__(kMWaves * 64) __attribute__((amdgpu_waves_per_eu(g2
     const int t = lo;
     const int per = 1 << (3 * g.log2B);
     const int t_end = start[(t + 1) * per];
-    const int sg = start[t * per] + (chunk - chunk_off[t]) * kWave + wid * kMG;
-    if (sg >= t_end) return;  // this wave's part of a short chunk is empty (no block barriers below)
+    const int sg = start[t * per] + (chunk - chunk_off[t]) * kWave +
+                   (Split ? item % (kWave / kMG) : wid) * kMG;
+    // this group's part of a short chunk is empty (Split: for the whole block; the other form has no
+    // block barriers below)
+    if (sg >= t_end) return;
     const int s1 = min(sg + kMG, t_end);
-    T (*swq)[3][P] = sw[wid];
-    int (*ancq)[3] = anc[wid];
-    stage_weights<T, P, kMG>(rec, g, wa, sg, s1, swq, ancq, lane);
-    wave_lds_sync();
+    T (*swq)[3][P + 2] = sw[set];
+    int (*ancq)[3] = anc[set];
+    if constexpr (Split) {
+        stage_weights<T, P, kMG>(rec, g, wa, sg, s1, swq, ancq, (int)threadIdx.x, kMWaves * kWave);
+        __syncthreads();
+    } else {
+        stage_weights<T, P, kMG>(rec, g, wa, sg, s1, swq, ancq, lane, kWave);
+        wave_lds_sync();
+    }
 
     // the group's box: x and y from the anchors of its 16 targets (short groups repeat the
     // last), reduced over the 16 lanes of each quarter wave; z from the tile
@@ -186,12 +214,13 @@ __global__ __launch_bounds__(kMWaves * 64) __attribute__((amdgpu_waves_per_eu(g2
     const int Uy = __builtin_amdgcn_readfirstlane(mx1) - uy + P;
     const int Uzt = g.B + P - 1;
     const int ncol = 3 * Uzt;
-    const int steps = (Ux * Uy + 3) >> 2;
+    const int all_steps = (Ux * Uy + 3) >> 2;
 
-    const int M1 = g.M[0], M2 = g.M[1], M3 = g.M[2];
-    const unsigned plane = (unsigned)M2 * (unsigned)M3;
-    const unsigned nc = (unsigned)g.ncells;
-    const TG* __restrict__ gs = grid + (int64_t)3 * (t / g.ntiles) * g.ncells;
+    // byte offsets from the system's grid (below 4 GB: 3 x 512^3 FP64); grid sizes are powers of two
+    const unsigned mx = (unsigned)g.M[0] - 1, my = (unsigned)g.M[1] - 1, mz = (unsigned)g.M[2] - 1;
+    const int sy = __builtin_ctz((unsigned)g.M[2]) + (sizeof(TG) == 8 ? 3 : 2);
+    const int sx = sy + __builtin_ctz((unsigned)g.M[1]);
+    const char* __restrict__ gs = (const char*)(grid + (int64_t)3 * (t / g.ntiles) * g.ncells);
     // this lane's column of each block: component c and box z (columns past 3 U_z read a valid
     // point and are ignored)
     unsigned zc[NB];
@@ -199,28 +228,30 @@ __global__ __launch_bounds__(kMWaves * 64) __attribute__((amdgpu_waves_per_eu(g2
     for (int cb = 0; cb < NB; ++cb) {
         const int col = min(16 * cb + i, ncol - 1);
         const int c = col / Uzt, z = col - c * Uzt;
-        zc[cb] = (unsigned)c * nc + (unsigned)((uz + z) & (M3 - 1));
+        zc[cb] = ((unsigned)c * (unsigned)g.ncells + ((unsigned)(uz + z) & mz)) * (unsigned)sizeof(TG);
     }
     // this lane's row of A: target i's offsets in the box
     const int dxi = ancq[i][0] - ux, dyi = ancq[i][1] - uy;
-    const T* __restrict__ wxi = swq[i][0];
-    const T* __restrict__ wyi = swq[i][1];
 
     // box point (xk, yk) of this lane's k = 4 step + kq (U_y >= P >= 4: one wrap at most).  Steps
     // go in pairs with two operand sets, each loaded one step ahead of its use; steps past the
     // last have x >= U_x, so jx >= P and A = 0, and read valid (wrapped) grid points.
-    int xk = 0, yk = kq;
-    auto a_of = [&]() {
-        const int jx = xk - dxi, jy = yk - dyi;
-        const bool in = (unsigned)jx < (unsigned)P && (unsigned)jy < (unsigned)P;
-        const T w = wxi[in ? jx : 0] * wyi[in ? jy : 0];
-        return in ? (TM)w : (TM)0;
-    };
-    auto load_b = [&](TM* b) {
-        const unsigned xy =
-            (unsigned)((ux + xk) & (M1 - 1)) * plane + (unsigned)((uy + yk) & (M2 - 1)) * (unsigned)M3;
+    int xk = 0, yk = kq, steps = all_steps;
+    if constexpr (Split) {
+        // an even number of steps per wave: a pair stays with its wave
+        const int q = ((all_steps + 7) >> 3) << 1;
+        const int k0 = 4 * q * wid + kq;
+        xk = k0 / Uy;
+        yk = k0 - xk * Uy;
+        steps = min(q, all_steps - q * wid);
+    }
+    // weight of an offset, zero off the stencil
+    auto weight = [&](const T* w, int j) { return w[1 + min(max(j, -1), P)]; };
+    auto load = [&](TM& a, TM* b) {
+        a = (TM)(weight(swq[i][0], xk - dxi) * weight(swq[i][1], yk - dyi));
+        const unsigned xy = (((unsigned)(ux + xk) & mx) << sx) | (((unsigned)(uy + yk) & my) << sy);
 #pragma unroll
-        for (int cb = 0; cb < NB; ++cb) b[cb] = (TM)gs[xy + zc[cb]];
+        for (int cb = 0; cb < NB; ++cb) b[cb] = (TM) * (const TG*)(gs + (xy + zc[cb]));
     };
     auto advance = [&]() {
         yk += 4;
@@ -234,22 +265,38 @@ __global__ __launch_bounds__(kMWaves * 64) __attribute__((amdgpu_waves_per_eu(g2
     for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[cb][r] = (TM)0;
-    TM a0 = a_of(), b0[NB], a1, b1[NB];
-    load_b(b0);
+    TM a0, b0[NB], a1, b1[NB];
+    load(a0, b0);
 #pragma unroll 1
     for (int st = 0; st < steps; st += 2) {
         advance();
-        a1 = a_of();
-        load_b(b1);
+        load(a1, b1);
         __builtin_amdgcn_sched_barrier(0);  // the loads go out before this step's instructions
 #pragma unroll
         for (int cb = 0; cb < NB; ++cb) acc[cb] = g2p_mfma(a0, b0[cb], acc[cb]);
         advance();
-        a0 = a_of();
-        load_b(b0);
+        load(a0, b0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int cb = 0; cb < NB; ++cb) acc[cb] = g2p_mfma(a1, b1[cb], acc[cb]);
+    }
+
+    if constexpr (Split) {
+        __shared__ TM red[3][NB][4][kWave];
+        if (wid > 0) {
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[wid - 1][cb][r][lane] = acc[cb][r];
+        }
+        __syncthreads();
+        if (wid > 0) return;
+#pragma unroll 1
+        for (int w = 0; w < 3; ++w)
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[cb][r] += red[w][cb][r][lane];
     }
 
     // u^F of this lane's four rows: weight each column by w_z of its row's target, sum the 16 columns
@@ -263,9 +310,7 @@ __global__ __launch_bounds__(kMWaves * 64) __attribute__((amdgpu_waves_per_eu(g2
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int q = kRowsGrouped ? 4 * kq + r : 4 * r + kq;
-            const int jz = z + uz - ancq[q][2];
-            const bool in = col < ncol && (unsigned)jz < (unsigned)P;
-            const double v = in ? (double)swq[q][2][in ? jz : 0] * (double)acc[cb][r] : 0.0;
+            const double v = (double)weight(swq[q][2], z + uz - ancq[q][2]) * (double)acc[cb][r];
             p[r][0] += c == 0 ? v : 0.0;
             p[r][1] += c == 1 ? v : 0.0;
             p[r][2] += c == 2 ? v : 0.0;
@@ -305,9 +350,23 @@ hipError_t launch_g2p_mfma(const Plan& pl, const Work& w, int n, const double* f
     // an upper bound on the chunks (each tile has at most one short chunk); blocks past the
     // actual count exit at once
     const int64_t blocks = (int64_t)g.ntiles * g.nsys + (n + kWave - 1) / kWave;
-    hipLaunchKernelGGL((k_g2p_mfma<T, TG, P, NB>), dim3((unsigned)blocks), dim3(kMWaves * kWave), 0, s,
-                       (const typename RecView<T>::Rec*)w.rec, w.start, w.chunk_off, (const TG*)w.grid, g,
-                       make_win_args<T>(pl), pl.info.self_coef, w.u_near, f, u, un, uf, n);
+    auto launch = [&](auto kernel, int64_t nb) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kMWaves * kWave), 0, s,
+                           (const typename RecView<T>::Rec*)w.rec, w.start, w.chunk_off, (const TG*)w.grid, g,
+                           make_win_args<T>(pl), pl.info.self_coef, w.u_near, f, u, un, uf, n);
+    };
+    if constexpr (std::is_same<TG, double>::value) {
+        // by the plan alone, so that a system's result does not depend on what is evaluated with it:
+        // plans of up to 131072 particles (ms of the two forms: 1e3 0.044 / 0.017, 1.6e4 at 1e-8 0.076 / 0.050,
+        // 6.6e4 0.198 / 0.173; 2.6e5 on 128^3 0.404 / 0.450, c2 1.11 / 1.29, c4 3.48 / 4.01), and sparse
+        // ones, below a particle per ten cells (1.5e5 of 2.6e5 on 128 x 128 x 256 0.413 / 0.381, 1e6 on
+        // 256^3 2.35 / 2.00)
+        if (pl.p.n_max <= 131072 || 10 * pl.p.n_max < g.ncells) {
+            launch(k_g2p_mfma<T, TG, P, NB, true>, blocks * (kWave / kMG));
+            return hipGetLastError();
+        }
+    }
+    launch(k_g2p_mfma<T, TG, P, NB, false>, blocks);
     return hipGetLastError();
 }
 
