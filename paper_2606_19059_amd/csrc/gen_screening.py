@@ -15,7 +15,12 @@ of u (kScreenC32, kScreenA, kScreenB).
 It also prints the polynomials of 2^s on |s| <= 1/2 for the reduced-cost exponentials
 (e^{-y} = 2^z with z = -y log2(e) = n + s, n = rint(z)): Chebyshev interpolants of the printed
 degrees at 50 digits, in the monomial basis of s, divided by their leading coefficients
-(kExpLead*).  Run: python gen_screening.py > screening.h
+(kExpLead*).
+
+The reduced-cost FP64 pairs take erfcx(x) + (2/sqrt(pi)) x itself as a polynomial (kScreenW*), in
+X = x sqrt(log2 e) (so that e^{-x^2} = 2^{-X^2}), divided by its leading coefficient: the minimax
+polynomial under the weight e^{-x^2} that multiplies it (Remez exchange at 50 digits), which needs no
+reciprocal.  Run: python gen_screening.py > screening.h
 """
 import mpmath as mp
 
@@ -27,6 +32,44 @@ XMAX = mp.mpf(13) / 2
 DEGREES = {"64": 16, "64s": 12, "64f": 10, "32": 11}
 # degree of the polynomial of 2^s, |s| <= 1/2: "1" for 1e-10 <= tol < 1e-8, "2" for tol >= 1e-8
 EXP_DEGREES = {"1": 8, "2": 7}
+# degree of the weighted polynomials, by the same levels
+WEIGHTED_DEGREES = {"1": 18, "2": 15}
+
+
+def weighted_remez(fun, weight, deg, xmax):
+    """Monomial coefficients of the degree-deg polynomial p that minimises the maximum of
+    weight (p - fun) on [0, xmax], by Remez exchange on a grid of 3001 points."""
+    n = deg + 2
+    # first reference: Chebyshev points of the range where the weight leaves something to fit
+    xe = min(xmax, mp.sqrt(mp.mpf(deg)) * mp.mpf("1.05") + mp.mpf("0.6"))
+    pts = [xe * (1 - mp.cos(mp.pi * k / (n - 1))) / 2 for k in range(n)]
+    grid = [xmax * mp.mpf(k) / 3000 for k in range(3001)]
+    ref = [fun(x) for x in grid]
+    for _ in range(30):
+        a, b = mp.matrix(n, n), mp.matrix(n, 1)
+        for i, x in enumerate(pts):
+            wx = weight(x)
+            for j in range(deg + 1):
+                a[i, j] = wx * x ** j
+            a[i, deg + 1] = (-1) ** i
+            b[i] = wx * fun(x)
+        s = mp.lu_solve(a, b)
+        c = [s[j] for j in range(deg + 1)]
+        err = [weight(x) * (mp.polyval(c[::-1], x) - r) for x, r in zip(grid, ref)]
+        ext, cur = [], 0  # the largest error of each run of one sign
+        for k in range(1, len(grid)):
+            if (err[k] > 0) != (err[cur] > 0):
+                ext.append(cur)
+                cur = k
+            elif abs(err[k]) > abs(err[cur]):
+                cur = k
+        ext.append(cur)
+        if max(abs(e) for e in err) < abs(s[deg + 1]) * mp.mpf("1.02"):
+            return c
+        while len(ext) > n:
+            ext.pop(0 if abs(err[ext[0]]) < abs(err[ext[-1]]) else -1)
+        pts = [grid[k] for k in ext]
+    raise RuntimeError("no convergence at degree %d" % deg)
 
 
 def cheb_coeffs(fun, n):
@@ -81,6 +124,8 @@ def main():
     print("// erfcx(x) for 0 <= x <= %s: FP64 in t = (x - K)/(x + K), monomials divided by the" % mp.nstr(XMAX, 3))
     print("// leading coefficient (kScreenLead*; kScreenM*[k], k < deg, the leading 1 implicit);")
     print("// FP32 in u = A t + B (kScreenC32).  2^s for |s| <= 1/2: kExpLead* x monic kExpM*.")
+    print("// erfcx(x) + 2x/sqrt(pi), minimax under the weight e^{-x^2}, in X = x sqrt(log2 e):")
+    print("// kScreenLeadW* x monic kScreenW*.")
     print("#pragma once")
     print("namespace ewald {")
     print("constexpr double kScreenK = %d;" % K)
@@ -106,6 +151,15 @@ def main():
         print("constexpr int kExpDeg%s = %d;" % (tag, deg))
         print("constexpr double kExpLead%s = %.17g;" % (tag, float(lead)))
         print(arr("kExpM%s" % tag, [v / lead for v in mono_s[:deg]]))
+    scale = mp.sqrt(1 / mp.log(2))  # X = x sqrt(log2 e)
+    for tag, deg in WEIGHTED_DEGREES.items():
+        c = weighted_remez(lambda x: mp.erfc(x) * mp.exp(x * x) + 2 * x / mp.sqrt(mp.pi),
+                           lambda x: mp.exp(-x * x), deg, XMAX)
+        c = [v / scale ** k for k, v in enumerate(c)]
+        lead = c[deg]
+        print("constexpr int kScreenDegW%s = %d;" % (tag, deg))
+        print("constexpr double kScreenLeadW%s = %.17g;" % (tag, float(lead)))
+        print(arr("kScreenW%s" % tag, [v / lead for v in c[:deg]]))
     print("}  // namespace ewald")
 
 

@@ -36,16 +36,20 @@ namespace {
 // that the formula's own error stays 30-40 times below it:
 //   0 (tol < 1e-10): degree-16 screening polynomial (|dC| < 5e-15), library exponential, two
 //     Newton steps on the hardware reciprocal, third-order rsqrt correction;
-//   1 (1e-10 <= tol < 1e-8): degree 12 (|dC| < 4e-12), e^{-y} = 2^z (z = -y log2 e) as 2^n times a
-//     degree-8 Chebyshev polynomial of 2^s, z = n + s, n = rint(z) (relative error 1.1e-12; no
-//     range checks: -61 < z <= 0 on the P2P range), one Newton step on rcp and on rsqrt;
-//   2 (tol >= 1e-8): degree 10 (|dC| < 3e-10) and a degree-7 polynomial of 2^s (5.6e-11), else
-//     as level 1: near-field error about 2.5e-10 of the field's max (a CPU model of c2's and of a
-//     coarse plan's geometry).
-// Both polynomials are stored divided by their leading coefficients (screening.h), so that Horner
-// starts with an addition (an FMA cannot take two scalar-register coefficients).  The FP64 pair
-// formula therefore returns its coefficients divided by post = lead_screen x lead_exp (lead_exp = 1
-// at level 0); the kernels multiply each target's and source's sum by post once, at the end.
+//   1 (1e-10 <= tol < 1e-8): erfcx(x) + 2x/sqrt(pi) as a polynomial in x fitted under the weight
+//     e^{-x^2} (degree 18, |dC| < 2.8e-12), e^{-y} = 2^z (z = -y log2 e) as 2^n times a degree-8
+//     Chebyshev polynomial of 2^s, z = n + s, n = rint(z) (relative error 1.1e-12; no range checks:
+//     -61 < z <= 0 on the P2P range), one Newton step on rsqrt;
+//   2 (tol >= 1e-8): degree 15 (|dC| < 1.6e-10) and a degree-7 polynomial of 2^s (5.6e-11), else as
+//     level 1.
+// The weighted polynomial needs no reciprocal: 15 instructions against 16 (one of them quarter rate)
+// with the degree-10 polynomial in (x - 3)/(x + 3) that level 2 took before (|dC| < 3e-10; stresslet
+// pairs still take that form and its degree-12 sibling).  All polynomials are stored divided by their
+// leading coefficients (screening.h), so that Horner starts with an addition (an FMA cannot take two
+// scalar-register coefficients).  The FP64 pair formula therefore returns its coefficients divided by
+// post; the kernels multiply each target's and source's sum by post once, at the end.
+// Levels 1 and 2 of the symmetric kernel work on positions scaled by kappa = xi sqrt(log2 e), which
+// makes the exponent -r^2 itself and r the polynomials' variable (two multiplications per pair less).
 constexpr double kLog2e = 1.4426950408889634074;
 
 struct PairArgs {
@@ -56,9 +60,14 @@ struct PairArgs {
     // x coefficient g = (2/sqrt(pi))/lead_s) and exponential (me) polynomials; a1 / post =
     // C'/r - h e' with h = (4 xi/sqrt(pi))/lead_s
     double zc, g, h, post, lead_s, lead_e;
+    double lead_st;  // leading coefficient of ms (stresslet pairs)
+    // scaled form: kappa, the cutoff (kappa r_c)^2, h / kappa; the sums' factor is post kappa
+    double kappa, rc2s, hs;
     // polynomials passed by value, so that the coefficients sit in scalar registers (an FMA then
-    // takes them as an operand, no per-pair register copies); c32: the FP32 formula's
+    // takes them as an operand, no per-pair register copies); mw: the weighted screening polynomial of
+    // levels 1 and 2, c32: the FP32 formula's
     double ms[kScreenDeg64];
+    double mw[kScreenDegW1];
     double me[kExpDeg1];
     float c32[kScreenDeg32 + 1];
     float zc32;  // FP32 formula: -xi^2 log2 e
@@ -105,6 +114,19 @@ __device__ inline int wave_min_small(int v)
     return lo;
 }
 
+// sum of v over the wave, for every lane: six additions with DPP operands (rows of 16, then the row
+// broadcasts), no LDS
+__device__ inline int wave_sum_i(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2 and 3
+    return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+
 // position of the k-th (from 0) set bit of m, for k < popcount(m): five halving steps
 __device__ inline int select_bit(unsigned m, int k)
 {
@@ -137,7 +159,7 @@ __device__ inline int lanes_below(unsigned long long m)
                                           __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
-// (erfcx(x) + 2x/sqrt(pi)) / lead_s for 0 <= x <= kScreenXmax: the monic polynomial of screening.h
+// (erfcx(x) + 2x/sqrt(pi)) / lead_st for 0 <= x <= kScreenXmax: the monic polynomial of screening.h
 // in t = (x - K)/(x + K) = 1 - 2K/(x + K), plus g x
 template <int Lv>
 __device__ inline double screen_q64(double x, const PairArgs& a)
@@ -183,17 +205,37 @@ __device__ inline double rsqrt_pos(double r2)
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
+// (erfcx(x) + 2x/sqrt(pi)) / lead_s at X = x sqrt(log2 e): the weighted polynomial of screening.h
+template <int Lv>
+__device__ inline double screen_w64(double X, const PairArgs& a)
+{
+    constexpr int deg = Lv == 1 ? kScreenDegW1 : kScreenDegW2;
+    double q = X + a.mw[deg - 1];
+#pragma unroll
+    for (int k = deg - 2; k >= 0; --k) q = fma(q, X, a.mw[k]);
+    return q;
+}
+
 // Coefficients of G^N(r) f = a1 f + b (r.f) r for 0 < r^2 < r_c^2 (FP64), divided by post:
 // a1 = C/r - (4 xi/sqrt(pi)) e, b = C/r^3, with e = e^{-xi^2 r^2} = lead_e e' and C = e Q,
-// Q = lead_s Q'
-template <int Lv>
+// Q = lead_s Q'.  Scaled (levels 1 and 2): r2 is (kappa r)^2, and a1, b are for the scaled r.
+template <int Lv, bool Scaled>
 __device__ inline void coef64(double r2, const PairArgs& a, double& a1, double& b)
 {
     const double rinv = rsqrt_pos<Lv>(r2);
-    const double x = a.xi * r2 * rinv;
-    const double e = Lv > 0 ? exp2_lead<Lv>(a.zc * r2, a) : exp(-a.xi2 * r2);
-    const double Cr = e * screen_q64<Lv>(x, a) * rinv;
-    a1 = fma(-a.h, e, Cr);
+    double e, q;
+    if constexpr (Lv == 0) {
+        e = exp(-a.xi2 * r2);
+        q = screen_q64<Lv>(a.xi * r2 * rinv, a);
+    } else if constexpr (Scaled) {
+        e = exp2_lead<Lv>(-r2, a);
+        q = screen_w64<Lv>(r2 * rinv, a);
+    } else {
+        e = exp2_lead<Lv>(a.zc * r2, a);
+        q = screen_w64<Lv>(a.kappa * r2 * rinv, a);
+    }
+    const double Cr = e * q * rinv;
+    a1 = fma(Scaled ? -a.hs : -a.h, e, Cr);
     b = Cr * (rinv * rinv);
 }
 
@@ -225,21 +267,21 @@ __device__ inline void coef32(double r2d, const PairArgs& a, float& a1, float& b
     b = Cr * (rinv * rinv);
 }
 
-// Pair coefficients in the formula precision TF (double: FP64 path at accuracy level Lv;
-// float: FP32 bulk, Lv unused).
-template <typename TF, int Lv>
+// Pair coefficients in the formula precision TF (double: FP64 path at accuracy level Lv, on scaled
+// positions or not; float: FP32 bulk, Lv unused).
+template <typename TF, int Lv, bool Scaled>
 struct Coef;
 // post: the factor that the sums of eval's contributions take at the end
-template <int Lv>
-struct Coef<double, Lv> {
+template <int Lv, bool Scaled>
+struct Coef<double, Lv, Scaled> {
     __device__ static inline void eval(double r2, const PairArgs& a, double& a1, double& b)
     {
-        coef64<Lv>(r2, a, a1, b);
+        coef64<Lv, Scaled>(r2, a, a1, b);
     }
-    __device__ static inline double post(const PairArgs& a) { return a.post; }
+    __device__ static inline double post(const PairArgs& a) { return Scaled ? a.post * a.kappa : a.post; }
 };
 template <int Lv>
-struct Coef<float, Lv> {
+struct Coef<float, Lv, false> {
     __device__ static inline void eval(double r2, const PairArgs& a, float& a1, float& b) { coef32(r2, a, a1, b); }
     __device__ static inline double post(const PairArgs&) { return 1.0; }
 };
@@ -258,7 +300,7 @@ __device__ inline void coef64_st(double r2, const PairArgs& a, double& a1, doubl
     const double r = r2 * rinv;
     const double x = a.xi * r;
     const double e = Lv > 0 ? a.lead_e * exp2_lead<Lv>(a.zc * r2, a) : exp(-a.xi2 * r2);
-    const double C = e * (a.lead_s * screen_q64<Lv>(x, a));
+    const double C = e * (a.lead_st * screen_q64<Lv>(x, a));
     const double rinv2 = rinv * rinv, rinv3 = rinv2 * rinv;
     a1 = fma(C, rinv, -a.four_xi_over_sqrtpi * e);
     b = C * rinv3;
@@ -424,7 +466,7 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
                 const double rz = ld1(tgt[2][tt]) - ld1(ring[2][slot]);
                 const double r2 = rx * rx + ry * ry + rz * rz;
                 TF a1, b, c0, c1, c2;
-                Coef<TF, Lv>::eval(r2, a, a1, b);
+                Coef<TF, Lv, false>::eval(r2, a, a1, b);
                 apply<TF>(a1, b, (TF)rx, (TF)ry, (TF)rz, ld1(ringf[0][slot]), ld1(ringf[1][slot]), ld1(ringf[2][slot]), c0,
                           c1, c2);
                 atomicAdd(&acc[0][tt], (TA)c0);
@@ -514,7 +556,7 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
     }
     if (NW > 1) __syncthreads();
     if (active && wid == 0) {
-        const double post = Coef<TF, Lv>::post(a);
+        const double post = Coef<TF, Lv, false>::post(a);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             double v = (double)acc_[0][d][lane];
@@ -554,9 +596,12 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
 // relative to the centre of the targets' bounding box, so that |s' - t'|^2 < r_c^2 can be tested
 // in the expanded form |s'|^2 - 2 s'.t' < r_c^2 - |t'|^2 without cancellation beyond a few ulps of
 // (box diagonal + r_c)^2.  A full batch past the own tile (32 sources x 64 targets) is eight
-// v_mfma_f64_16x16x4f64 (sources as rows with K = (x, y, z, |s'|^2), targets as columns with
-// K = (-2x, -2y, -2z, 1)) and 32 comparisons per lane, instead of 32 broadcast LDS reads and six
-// FP64 operations per source: c2 P2P 22.9 -> 21.3 ms, H 12.2 -> 11.3 ms.  The own tile, whose
+// v_mfma_f64_16x16x4f64 (sources as rows, targets as columns, the sums starting from |s'|^2) whose
+// results' sign bits are the tests, instead of 32 broadcast LDS reads and six FP64 operations per
+// source: c2 P2P 22.9 -> 21.3 ms, H 12.2 -> 11.3 ms.  The matrix instructions hold the SIMD for 64 cycles
+// each (no vector instruction issues meanwhile), so the test costs 128 + 75 issue slots per batch (128 +
+// 128 with comparisons and ballots); with the weighted polynomials on scaled positions c2 18.3 -> 17.85 ms,
+// c3 165 -> 161 ms.  The own tile, whose
 // pairs also need r > 0 and the index order, and the last, shorter batch keep the direct test;
 // the direct difference of repeated positions is exactly 0 also in the centred frame.
 constexpr int kSymRing = 64;
@@ -584,12 +629,14 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                                                 PairArgs a, double* __restrict__ u_near, int nsplit)
 {
     constexpr int NS = ST ? 6 : 1;
-    __shared__ double tgt[4][kWave];  // t' (x, y, z) and r_c^2 - |t'|^2
+    constexpr bool kScaled = !ST && std::is_same<TF, double>::value && Lv > 0;
+    using PairCoef = Coef<TF, Lv, kScaled>;
+    __shared__ double tgt[3][kWave];  // t' (x, y, z)
     __shared__ TF tgtf[3][kWave];
     __shared__ TF tgts[NS][kWave];
     __shared__ TF rings[NS][kSymRing];
     __shared__ double acc[3][kWave];
-    __shared__ double ring[3][kSymRing];
+    __shared__ __align__(32) double ring[4][kSymRing];  // s' (x, y, z) and |s'|^2
     __shared__ TF ringf[3][kSymRing];
     __shared__ int ringk[kSymRing];
     // batch size and copies of the per-batch source accumulators (per component, copy, entry)
@@ -628,7 +675,8 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
     const int tc[3] = {tl / (g.NT[1] * g.NT[2]), (tl / g.NT[2]) % g.NT[1], tl % g.NT[2]};
     // positions relative to the centre of the targets' bounding box (see the cutoff test above)
     double w[3], blo[3], bhi[3], cen[3], tx[3], oacc[3];
-    double tlim = a.rc2;
+    const double rc2 = kScaled ? a.rc2s : a.rc2;  // of the (scaled) positions relative to the centre
+    double tlim = -rc2;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         w[d] = g.B * g.h[d];
@@ -636,14 +684,14 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
         bhi[d] = uniform_d(wave_max(me.x[d]));
         cen[d] = uniform_d(0.5 * (blo[d] + bhi[d]));
         tx[d] = active ? me.x[d] - cen[d] : 1e30;  // an inactive lane accepts no pair
-        tlim -= tx[d] * tx[d];
+        if (kScaled) tx[d] *= a.kappa;
+        tlim += tx[d] * tx[d];
         tgt[d][lane] = tx[d];
         tgtf[d][lane] = (TF)me.f[d];
         acc[d][lane] = 0.0;
         if (lane < kCp * kB) racc[d][lane / kB][lane % kB] = 0.0;
         oacc[d] = 0.0;
     }
-    tgt[3][lane] = tlim;
     if (ST) {
         const int ii = active ? i : first;
 #pragma unroll
@@ -651,8 +699,16 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
     }
     __syncthreads();
     const int mi = lane & 15, mk = lane >> 4;  // lane = 16 mk + mi
+    // target operands of the cutoff test's matrix instructions (see process): B = (x, y, z,
+    // |t'|^2 - r_c^2) of targets 16 nb + mi
+    double bt[4];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+        const double l = __shfl(tlim, 16 * nb + mi, kWave);
+        bt[nb] = mk < 3 ? tgt[mk < 3 ? mk : 0][16 * nb + mi] : l;
+    }
     // the stresslet formula (CoefSt) returns its coefficients unscaled
-    const double post = ST ? 1.0 : Coef<TF, Lv>::post(a);
+    const double post = ST ? 1.0 : PairCoef::post(a);
 
     int rhead = 0, rcount = 0;
     const bool by_tile = nsplit <= kTileSplit;
@@ -670,77 +726,68 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
         //    tile in the ring, so a batch whose first entry is not of the own tile needs
         //    only the cutoff test.
         unsigned m = 0;
-        int qn = 0;
         const bool own_tile = uniform_i(ringk[rhead]) < kFar;
         if (own_tile) {
             for (int j = 0; j < cnt; ++j) {
                 const int slot = (rhead + j) & (kSymRing - 1);
                 const double rx = tx[0] - ld1(ring[0][slot]), ry = tx[1] - ld1(ring[1][slot]), rz = tx[2] - ld1(ring[2][slot]);
                 const double r2 = rx * rx + ry * ry + rz * rz;
-                const bool pass = (r2 < a.rc2) & (r2 > 0.0) & (ringk[slot] > i);
+                const bool pass = (r2 < rc2) & (r2 > 0.0) & (ringk[slot] > i);
                 m = pass ? (m | (1u << j)) : m;
-                qn += __popcll(ballot(pass));
             }
         } else if (cnt == kB) {
-            // a full batch past the own tile: |s' - t'|^2 < r_c^2  <=>  |s'|^2 - 2 s'.t' < r_c^2 - |t'|^2,
-            // for 32 sources x 64 targets by eight v_mfma_f64_16x16x4f64 (sources as rows, targets
-            // as columns).  On gfx950 lane l = 16 kq + i supplies A[i][kq] and B[kq][i] and receives
-            // D[4 r + kq][i], r = 0..3.  Batches start at ring slot 0 or 32 (32 entries at a time
-            // from a 64-slot ring), so the batch's slots need no wrap.  Source row rho of block mb is
-            // loaded from slot 16 mb + 4 (rho % 4) + rho / 4, so that result item r of lane (kq, i)
-            // -- row 4 r + kq -- is slot 16 mb + 4 kq + r: a lane's four items are four consecutive
-            // bits of the batch mask.
+            // a full batch past the own tile: |s' - t'|^2 < r_c^2  <=>  |s'|^2 - 2 s'.t' + |t'|^2 - r_c^2 < 0,
+            // for 32 sources x 64 targets by eight v_mfma_f64_16x16x4f64 (sources as rows).  On gfx950 lane
+            // l = 16 kq + i supplies A[i][kq] and B[kq][i] and receives D[4 r + kq][i], r = 0..3.  Batches
+            // start at ring slot 0 or 32 (32 entries at a time from a 64-slot ring), so the batch's slots
+            // need no wrap.
             typedef double v4d __attribute__((ext_vector_type(4)));
+            // source operand A = (-2 x, -2 y, -2 z, 1): row rho of block mb is slot 8 (rho % 4) + 4 mb + rho / 4,
+            // so that result item r of lane (kq, i) -- row 4 r + kq -- is slot 8 kq + 4 mb + r: a lane's eight
+            // items are eight consecutive bits of the batch mask, and start from |s'|^2 of eight
+            // consecutive slots
             double av[2];
+            v4d cv[2];
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb) {
-                const int slot = rhead + 16 * mb + 4 * (mi & 3) + (mi >> 2);
-                const double x0 = ld1(ring[0][slot]), x1 = ld1(ring[1][slot]), x2 = ld1(ring[2][slot]);
-                av[mb] = mk == 0 ? x0 : mk == 1 ? x1 : mk == 2 ? x2 : fma(x0, x0, fma(x1, x1, x2 * x2));
+                const double xk = ld1(ring[mk < 3 ? mk : 0][rhead + 8 * (mi & 3) + 4 * mb + (mi >> 2)]);
+                av[mb] = mk < 3 ? -2.0 * xk : 1.0;
+                cv[mb] = *reinterpret_cast<const v4d*>(&ring[3][rhead + 8 * mk + 4 * mb]);
             }
-            // column block nb: targets 16 nb + i; operand B[kq][i] = -2 t'_kq (kq = 3: 1).  The bits of
-            // target 16 nb + i are spread over lanes (kq, i), kq = 0..3: OR over the four rows, kept
-            // by the lanes of row nb (the target's own lane)
+            // the sign bit of an item is its test.  The bits of target 16 nb + i are spread over lanes
+            // (kq, i), kq = 0..3: OR over the four rows, kept by the lanes of row nb (the target's own lane)
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
-                const double tk = tgt[mk < 3 ? mk : 0][16 * nb + mi];
-                const double bt = mk < 3 ? -2.0 * tk : 1.0;
-                const double lim = tgt[3][16 * nb + mi];
-                unsigned wv = 0;
+                unsigned v = 0;
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb) {
-                    const v4d dd = __builtin_amdgcn_mfma_f64_16x16x4f64(av[mb], bt, v4d{0.0, 0.0, 0.0, 0.0}, 0, 0, 0);
-                    unsigned nib = 0;
+                for (int mb = 1; mb >= 0; --mb) {
+                    const v4d dd = __builtin_amdgcn_mfma_f64_16x16x4f64(av[mb], bt[nb], cv[mb], 0, 0, 0);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const bool p = dd[r] < lim;
-                        nib |= p ? (1u << r) : 0u;
-                        qn += __popcll(ballot(p));
-                    }
-                    wv |= nib << (16 * mb + 4 * mk);
+                    for (int r = 3; r >= 0; --r)  // v = 2 v + sign
+                        v = __builtin_amdgcn_alignbit(v, (unsigned)__double2hiint(dd[r]), 31);
                 }
-                wv = or_rows4(wv);
-                m = mk == nb ? wv : m;
+                v = or_rows4(v << (8 * mk));
+                m = mk == nb ? v : m;
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             for (int j = 0; j < cnt; ++j) {
                 const int slot = (rhead + j) & (kSymRing - 1);
                 const double rx = tx[0] - ld1(ring[0][slot]), ry = tx[1] - ld1(ring[1][slot]), rz = tx[2] - ld1(ring[2][slot]);
-                const bool pass = rx * rx + ry * ry + rz * rz < a.rc2;
+                const bool pass = rx * rx + ry * ry + rz * rz < rc2;
                 m = pass ? (m | (1u << j)) : m;
-                qn += __popcll(ballot(pass));
             }
         }
+        const int c = __popc(m);
+        const int qn = wave_sum_i(c);
         const int rounds = (qn + kWave - 1) / kWave;
         // 2. a lane keeps up to `rounds` of its target's pairs, taken in cyclic order from its
-        //    (lane mod c)-th accepted source (c: its number of pairs), so that the lanes of a
-        //    half-wave start on different sources even when their accepted sets are alike (a
+        //    k-th accepted source, k = (lane mod 32) c / 32 (c: its number of pairs), so that the lanes
+        //    of a half-wave start on different sources even when their accepted sets are alike (a
         //    rotation by the lane number alone sent the lanes whose start lies outside a common
         //    band of accepted sources to the band's first source together: same-address LDS
         //    atomics); the excess goes to the queue, for lanes that run out of pairs of their own
-        const int c = __popc(m);
-        const int rot = c ? select_bit(m, lane % c) : 0;
+        const int rot = c ? select_bit(m, ((lane & 31) * c) >> 5) : 0;
         const unsigned rm0 = rot ? ((m >> rot) | (m << (kB - rot))) : m;
         unsigned rm = rm0;
         const int own_n = c < rounds ? c : rounds;
@@ -785,7 +832,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 apply_st<TF>(al, be, (TF)rx, (TF)ry, (TF)rz, ss, c0, c1, c2);
                 apply_st<TF>(al, be, (TF)rx, (TF)ry, (TF)rz, st, d0, d1, d2);
             } else {
-                Coef<TF, Lv>::eval(r2, a, a1, b);
+                PairCoef::eval(r2, a, a1, b);
                 apply<TF>(a1, b, (TF)rx, (TF)ry, (TF)rz, ld1(ringf[0][slot]), ld1(ringf[1][slot]), ld1(ringf[2][slot]), c0,
                           c1, c2);
                 apply<TF>(a1, b, (TF)rx, (TF)ry, (TF)rz, tf0, tf1, tf2, d0, d1, d2);
@@ -811,7 +858,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 // the target side summed straight into the FMAs: oacc += a1 f_s + b (r.f_s) r
                 const double rx = px - ld1(ring[0][slot]), ry = py - ld1(ring[1][slot]), rz = pz - ld1(ring[2][slot]);
                 double a1, b;
-                Coef<double, Lv>::eval(rx * rx + ry * ry + rz * rz, a, a1, b);
+                PairCoef::eval(rx * rx + ry * ry + rz * rz, a, a1, b);
                 const double s0 = ld1(ringf[0][slot]), s1 = ld1(ringf[1][slot]), s2 = ld1(ringf[2][slot]);
                 const double rs = (rx * s0 + ry * s1 + rz * s2) * b;
                 oacc[0] = fma(rs, rx, fma(a1, s0, oacc[0]));
@@ -971,6 +1018,11 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                         sx -= cen[0];
                         sy -= cen[1];
                         sz -= cen[2];
+                        if (kScaled) {
+                            sx *= a.kappa;
+                            sy *= a.kappa;
+                            sz *= a.kappa;
+                        }
                     }
                     // append in two halves so the 64-slot ring never holds more than 63
 #pragma unroll
@@ -982,6 +1034,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                             ring[0][slot] = sx;
                             ring[1][slot] = sy;
                             ring[2][slot] = sz;
+                            ring[3][slot] = sx * sx + sy * sy + sz * sz;
                             ringf[0][slot] = (TF)f0;
                             ringf[1][slot] = (TF)f1;
                             ringf[2][slot] = (TF)f2;
@@ -1033,15 +1086,22 @@ PairArgs pair_args(const Plan& pl, int lv)
     const double* ms = lv == 2 ? kScreenM64f : lv == 1 ? kScreenM64s : kScreenM64;
     const int ds = lv == 2 ? kScreenDeg64f : lv == 1 ? kScreenDeg64s : kScreenDeg64;
     for (int k = 0; k < kScreenDeg64; ++k) a.ms[k] = k < ds ? ms[k] : 0.0;
-    a.lead_s = lv == 2 ? kScreenLead64f : lv == 1 ? kScreenLead64s : kScreenLead64;
+    a.lead_st = lv == 2 ? kScreenLead64f : lv == 1 ? kScreenLead64s : kScreenLead64;
+    const double* mw = lv == 2 ? kScreenW2 : kScreenW1;
+    const int dw = lv == 2 ? kScreenDegW2 : kScreenDegW1;
+    for (int k = 0; k < kScreenDegW1; ++k) a.mw[k] = k < dw ? mw[k] : 0.0;
+    a.lead_s = lv == 2 ? kScreenLeadW2 : lv == 1 ? kScreenLeadW1 : kScreenLead64;
     const double* me = lv == 2 ? kExpM2 : kExpM1;
     const int de = lv == 2 ? kExpDeg2 : kExpDeg1;
     for (int k = 0; k < kExpDeg1; ++k) a.me[k] = k < de ? me[k] : 0.0;
     a.lead_e = lv == 0 ? 1.0 : lv == 2 ? kExpLead2 : kExpLead1;
     a.zc = -a.xi2 * kLog2e;
     a.zc32 = (float)a.zc;
-    a.g = kTwoOverSqrtPi / a.lead_s;
+    a.kappa = pl.xi * sqrt(kLog2e);
+    a.rc2s = a.rc2 * (a.xi2 * kLog2e);
+    a.g = kTwoOverSqrtPi / a.lead_st;
     a.h = a.four_xi_over_sqrtpi / a.lead_s;
+    a.hs = a.h / a.kappa;
     a.post = a.lead_s * a.lead_e;
     for (int k = 0; k <= kScreenDeg32; ++k) a.c32[k] = (float)kScreenC32[k];
     return a;
