@@ -64,6 +64,19 @@ __device__ inline int quad_lane(int v)
     return __builtin_amdgcn_update_dpp(0, v, kPerm, 0xf, 0xf, true);
 }
 
+// inclusive scan over the wave: rows of 16 by row_shr, then the rows' totals by the row broadcasts (DPP
+// operands of six additions; a shuffle form takes six dependent LDS round trips)
+__device__ inline int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2 and 3
+    return v;
+}
+
 // A block of kWaves waves owns one patch and the x-segment [x0, x0 + seg).  It takes the segment in
 // windows of up to kWindow slabs (their run table in LDS) and a window in passes.  In a pass every
 // wave spreads its share of the particles into a register window of kSlabs + P - 1 points, four slabs
@@ -79,13 +92,15 @@ __device__ inline int quad_lane(int v)
 //
 // What bounds it: FP64 FMAs at the patches' lane efficiency where particles are dense (c2: 3P FMAs of
 // 56 instructions per particle and patch, two waves per SIMD by the 6 (kSlabs + P - 1) accumulator
-// registers, VALU 67% busy); latency of the tables and staging where they are sparse.  A form that
-// merged and wrote one point per slab (four waves sharing every slab, four barriers each) spent
-// 14 thousand cycles a slab on 30 particles.  P2G ms with that form and with this one: 1e6 uniform on
-// 256^3, P = 16 3.01 -> 1.75, P = 8 (FP32) 2.17 -> 0.64; 24 systems of 5e3 on 64^3 0.85 -> 0.29; 1.5e5 on
-// 128 x 128 x 256 0.71 -> 0.37; 1e3 on 32^3 0.083 -> 0.032; dense grids: c2 1.46 -> 1.40, H 0.91 -> 0.76, c4
-// 4.38 -> 4.17, c3 8.8 -> 8.5; one loss: 2e4 in two clusters of five cells 0.46 -> 0.53 (few patches hold
-// everything, and a lone wave per SIMD pays the staging's latency).
+// registers, VALU 67% busy); latency of the tables, the staging and the merge where they are sparse (a
+// block of 176 particles, P = 12: 45 thousand cycles, of which 20 thousand in the merge and the table
+// before their loads were issued side by side).  A form that merged and wrote one point per slab (four
+// waves sharing every slab, four barriers each) spent 14 thousand cycles a slab on 30 particles.  P2G
+// ms with that form and with this one: 1e6 uniform on 256^3, P = 16 3.01 -> 1.54, P = 8 (FP32) 2.17 -> 0.53;
+// 24 systems of 5e3 on 64^3 0.85 -> 0.27; 1.5e5 on 128 x 128 x 256 0.71 -> 0.30; 1e3 on 32^3 0.083 -> 0.028;
+// dense grids: c2 1.46 -> 1.37, H 0.91 -> 0.75, c4 4.38 -> 4.07, c3 8.8 -> 8.0; one loss: 2e4 in two clusters of
+// five cells 0.46 -> 0.51 (few patches hold everything, and a lone wave per SIMD, which issues an FP64
+// instruction every eight cycles, pays the staging's latency).
 //
 // Staging: 16 particles at a time, four lanes each (two halves of the x weights, the y and the z
 // weights of the patch's lines, zero off the footprint), every lane by one recurrence of at most eight
@@ -105,7 +120,9 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
     // staged particle: P x weights, 8 y weights, 8 z weights, f (an odd row length: the rows of
     // consecutive particles start in different banks)
     constexpr int kRow = P + 2 * kPatch + 3;
-    constexpr int kStage = kWaves * kBatch * kRow, kMerge = kWaves * kPts * kWave;
+    // merge rows of a wave: its points, padded with zeros to whole rounds of the waves
+    constexpr int kRounds = (kPts + kWaves - 1) / kWaves, kRows = kRounds * kWaves;
+    constexpr int kStage = kWaves * kBatch * kRow, kMerge = kWaves * kRows * kWave;
     __shared__ double smem[kStage > kMerge ? kStage : kMerge];
     __shared__ int run_start[kTable], run_pre[kTable];
     __shared__ int slab_n[kWindow];
@@ -155,35 +172,46 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
         // run table of the window's slabs: one run per (window row, z-tile segment); entry r of slab s
         // holds the run's first particle and the number of the slab's particles before it, entry R ends
         // the slab's search
-        for (int s = wid; s < wn; s += kWaves) {
-            const int cx = wrapi(x0 + sb + s, M1);
-            int before = 0;
-            for (int r0 = 0; r0 < R; r0 += kWave) {
-                const int r = r0 + lane;
-                int len = 0, st = 0;
-                if (r < R) {
-                    const int iy = (r * nzs_inv) >> 16, zs = r - iy * nzs;
-                    const int cy = wrapi(y0 - P / 2 + iy, M2);
-                    const int zt = zt0 + zs;
-                    const int au = max(zlo, zt * B), bu = min(zhi, zt * B + B - 1);
-                    const int k0 = cell_key(cx, cy, wrapi(au, M3), g);
-                    st = start[k0];
-                    len = start[k0 + (bu - au) + 1] - st;
-                }
-                int inc = len;
+        // (a wave's slabs, every fourth of the window, side by side: their loads and scans overlap)
+        constexpr int kSide = kWindow / kWaves;
+        int before[kSide] = {};
+        for (int r0 = 0; r0 < R; r0 += kWave) {
+            const int r = r0 + lane;
+            const int iy = (r * nzs_inv) >> 16, zs = r - iy * nzs;
+            const int cy = wrapi(y0 - P / 2 + iy, M2);
+            const int zt = zt0 + zs;
+            const int au = max(zlo, zt * B), bu = min(zhi, zt * B + B - 1);
+            const int cz = wrapi(au, M3);
+            int st[kSide], len[kSide];
 #pragma unroll
-                for (int o = 1; o < kWave; o <<= 1) {
-                    const int y = __shfl_up(inc, o, kWave);
-                    if (lane >= o) inc += y;
+            for (int j = 0; j < kSide; ++j) {
+                const int s = wid + kWaves * j;
+                st[j] = len[j] = 0;
+                if (s < wn && r < R) {
+                    const int k0 = cell_key(wrapi(x0 + sb + s, M1), cy, cz, g);
+                    st[j] = start[k0];
+                    len[j] = start[k0 + (bu - au) + 1];
                 }
-                if (r < R) {
-                    run_start[s * (R + 1) + r] = st;
-                    run_pre[s * (R + 1) + r] = before + inc - len;
-                }
-                before += __shfl(inc, kWave - 1, kWave);
             }
-            if (lane == 0) {
-                slab_n[s] = before;
+#pragma unroll
+            for (int j = 0; j < kSide; ++j) {
+                const int s = wid + kWaves * j;
+                if (s >= wn) break;
+                const int n = len[j] - st[j];
+                const int inc = wave_scan(n);
+                if (r < R) {
+                    run_start[s * (R + 1) + r] = st[j];
+                    run_pre[s * (R + 1) + r] = before[j] + inc - n;
+                }
+                before[j] += __builtin_amdgcn_readlane(inc, kWave - 1);
+            }
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int j = 0; j < kSide; ++j) {
+                const int s = wid + kWaves * j;
+                if (s >= wn) break;
+                slab_n[s] = before[j];
                 run_pre[s * (R + 1) + R] = INT_MAX;
             }
         }
@@ -191,15 +219,17 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
 
         // one pass with four slabs per wave, or a pass per group of four slabs
         const int groups = wn / kSlabs;
+        const int in_slab = lane < wn ? slab_n[lane < wn ? lane : 0] : 0;
+        int in_group = in_slab + quad_lane<0xb1>(in_slab);
+        in_group += quad_lane<0x4e>(in_group);
         int most = 0, shared = 0;
-        for (int j = 0; j < groups; ++j) {
-            int c = 0;
 #pragma unroll
-            for (int k = 0; k < kSlabs; ++k) c += slab_n[j * kSlabs + k];
+        for (int j = 0; j < kWindow / kSlabs; ++j) {
+            const int c = __builtin_amdgcn_readlane(in_group, j * kSlabs);
             most = max(most, c);
-            shared += (c + kWaves - 1) / kWaves + kMergeCost;
+            shared += j < groups ? (c + kWaves - 1) / kWaves + kMergeCost : 0;
         }
-        const bool split = __builtin_amdgcn_readfirstlane(shared < most + kMergeCost ? 1 : 0) != 0;
+        const bool split = shared < most + kMergeCost;
         const int passes = split ? groups : 1, pn = split ? kSlabs : wn;
         for (int pass = 0; pass < passes; ++pass) {
             const int sa = (split ? pass : wid) * kSlabs;  // this wave's first slab
@@ -207,7 +237,7 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
             G[0] = 0;
 #pragma unroll
             for (int k = 0; k < kSlabs; ++k)
-                G[k + 1] = G[k] + (sa < wn ? __builtin_amdgcn_readfirstlane(slab_n[sa + k]) : 0);
+                G[k + 1] = G[k] + __builtin_amdgcn_readlane(in_slab, sa + k);
             const int all = G[kSlabs];
             const int share = split ? (all + kWaves - 1) / kWaves : all;
             const int fa = split ? min(all, wid * share) : 0, fb = split ? min(all, fa + share) : all;
@@ -327,27 +357,30 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
                 wave_lds_sync();
             }
 
-            // merge, one component at a time: wave w sums the points p = w, w + 4, ... of the pass over
-            // the carried sums and the waves in order
-            const int last = pn + P - 1;
+            // merge, one component at a time: wave w sums the points p = w, w + 4, ... of the pass over the
+            // carried sums and the waves in order (all of a point's loads before its sum)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 __syncthreads();
 #pragma unroll
-                for (int k = 0; k < kPts; ++k) smem[(wid * kPts + k) * kWave + lane] = acc[k][c];
+                for (int k = 0; k < kRows; ++k)
+                    smem[(wid * kRows + k) * kWave + lane] = k < kPts ? acc[k < kPts ? k : 0][c] : 0.0;
                 __syncthreads();
                 double v[kOut];
 #pragma unroll
-                for (int i = 0; i < kOut; ++i) {
-                    v[i] = i < kCarry ? carry[i < kCarry ? i : 0][c] : 0.0;
-                    const int p = wid + kWaves * i;
-                    if (p < last) {
+                for (int i = 0; i < kOut; ++i) v[i] = i < kCarry ? carry[i < kCarry ? i : 0][c] : 0.0;
+                const double* row = smem + wid * kWave + lane;  // of wave q's point wid + 4 d: row q kRows + 4 d
+                if (split) {
 #pragma unroll
-                        for (int q = 0; q < kWaves; ++q) {
-                            const int k = split ? p : p - q * kSlabs;
-                            if ((unsigned)k < (unsigned)kPts) v[i] += smem[(q * kPts + k) * kWave + lane];
-                        }
-                    }
+                    for (int i = 0; i < kRounds && i < kOut; ++i)
+#pragma unroll
+                        for (int q = 0; q < kWaves; ++q) v[i] += row[(q * kRows + i * kWaves) * kWave];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kOut; ++i)
+#pragma unroll
+                        for (int q = 0; q < kWaves; ++q)
+                            if (i - q >= 0 && i - q < kRounds) v[i] += row[(q * kRows + (i - q) * kWaves) * kWave];
                 }
 #pragma unroll
                 for (int i = 0; i < kWindow / kWaves; ++i) {
