@@ -607,11 +607,9 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
 constexpr int kSymRing = 64;
 constexpr int kTileSplit = 3;  // up to so many waves share a chunk by tiles, more by batches of sources
 constexpr int kFar = 1 << 30;  // ring key offset of sources outside the targets' own tile
-// Balanced drain: batches of 32 ring entries and one copy of the source
-// accumulators (a second copy, for lanes 32-63, was measured 2% slower: the LDS it takes
-// costs more occupancy than the atomic collisions it saves).  Queue bound: with c_t <= 32
-// pairs per lane, Q = sum c_t and R = ceil(Q / 64) rounds, the excess sum over c_t >= R
-// of (c_t - R) is at most Q (32 - R) / 32 <= 2 R (32 - R) <= 512.
+// Balanced drain: batches of 32 ring entries.  Queue bound: with c_t <= 32 pairs per lane,
+// Q = sum c_t and R = ceil(Q / 64) rounds, the excess sum over c_t >= R of (c_t - R) is at most
+// Q (32 - R) / 32 <= 2 R (32 - R) <= 512.
 constexpr int kBalBatch = 32;
 constexpr int kBalExcess = 512;
 static_assert(kBalBatch == 32 && kSymRing == 64, "the mask, ring and queue sizes assume 32-entry batches");
@@ -639,10 +637,13 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
     __shared__ __align__(32) double ring[4][kSymRing];  // s' (x, y, z) and |s'|^2
     __shared__ TF ringf[3][kSymRing];
     __shared__ int ringk[kSymRing];
-    // batch size and copies of the per-batch source accumulators (per component, copy, entry)
     constexpr int kB = kBalBatch;
-    constexpr int kCp = 1;
-    __shared__ double racc[3][kCp][kB];
+    // FP32: a second copy of the batch's source accumulators, for the odd lanes, rotated by half (its
+    // banks differ): the atomics' address and bank conflicts are most of the LDS pipeline's time (H P2P
+    // 9.78 -> 9.47 ms, c4 49.8 -> 48.0).  In FP64 it costs a wave per SIMD (16 take 10240 bytes each) and
+    // more than it saves: c2 17.6 -> 18.1 ms, and 17.8 with half the queue and two components copied.
+    constexpr int kCopied = !ST && std::is_same<TF, float>::value ? 3 : 0;  // components with two copies
+    __shared__ double racc[3 + kCopied][kB];
     __shared__ unsigned short queue[kBalExcess];
     static_assert(kSymRing == kWave, "one ring slot per lane");
 
@@ -689,7 +690,8 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
         tgt[d][lane] = tx[d];
         tgtf[d][lane] = (TF)me.f[d];
         acc[d][lane] = 0.0;
-        if (lane < kCp * kB) racc[d][lane / kB][lane % kB] = 0.0;
+        if (lane < kB) racc[d][lane] = 0.0;
+        if (d < kCopied && lane < kB) racc[3 + d][lane] = 0.0;
         oacc[d] = 0.0;
     }
     if (ST) {
@@ -782,12 +784,12 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
         const int qn = wave_sum_i(c);
         const int rounds = (qn + kWave - 1) / kWave;
         // 2. a lane keeps up to `rounds` of its target's pairs, taken in cyclic order from its
-        //    k-th accepted source, k = (lane mod 32) c / 32 (c: its number of pairs), so that the lanes
-        //    of a half-wave start on different sources even when their accepted sets are alike (a
+        //    (lane mod c)-th accepted source (c: its number of pairs), so that the lanes of a half-wave
+        //    start on different sources even when their accepted sets are alike (a
         //    rotation by the lane number alone sent the lanes whose start lies outside a common
         //    band of accepted sources to the band's first source together: same-address LDS
         //    atomics); the excess goes to the queue, for lanes that run out of pairs of their own
-        const int rot = c ? select_bit(m, ((lane & 31) * c) >> 5) : 0;
+        const int rot = c ? select_bit(m, lane % c) : 0;
         const unsigned rm0 = rot ? ((m >> rot) | (m << (kB - rot))) : m;
         unsigned rm = rm0;
         const int own_n = c < rounds ? c : rounds;
@@ -838,7 +840,11 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 apply<TF>(a1, b, (TF)rx, (TF)ry, (TF)rz, tf0, tf1, tf2, d0, d1, d2);
             }
         };
-        const int rq = lane / (kWave / kCp);
+        // the source accumulator of component d and batch entry sl that this lane adds to
+        const int odd = lane & 1, turned = odd * (kB / 2);
+        auto source_sum = [&](int d, int sl) -> double& {
+            return d < kCopied ? racc[d + (odd ? 3 : 0)][(sl + turned) & (kB - 1)] : racc[d][sl];
+        };
         // 3a. rounds in which every lane still takes a pair of its own target (about a third
         //     at uniform density): no queue, no ballot, and the target's position and force
         //     come from registers
@@ -865,9 +871,9 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 oacc[1] = fma(rs, ry, fma(a1, s1, oacc[1]));
                 oacc[2] = fma(rs, rz, fma(a1, s2, oacc[2]));
                 const double rt = (rx * mf0 + ry * mf1 + rz * mf2) * b;
-                atomicAdd(&racc[0][rq][sl], fma(a1, mf0, rt * rx));
-                atomicAdd(&racc[1][rq][sl], fma(a1, mf1, rt * ry));
-                atomicAdd(&racc[2][rq][sl], fma(a1, mf2, rt * rz));
+                atomicAdd(&source_sum(0, sl), fma(a1, mf0, rt * rx));
+                atomicAdd(&source_sum(1, sl), fma(a1, mf1, rt * ry));
+                atomicAdd(&source_sum(2, sl), fma(a1, mf2, rt * rz));
                 continue;
             }
             TF c0, c1, c2, d0, d1, d2;
@@ -875,9 +881,9 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
             oacc[0] += (double)c0;
             oacc[1] += (double)c1;
             oacc[2] += (double)c2;
-            atomicAdd(&racc[0][rq][sl], (double)d0);
-            atomicAdd(&racc[1][rq][sl], (double)d1);
-            atomicAdd(&racc[2][rq][sl], (double)d2);
+            atomicAdd(&source_sum(0, sl), (double)d0);
+            atomicAdd(&source_sum(1, sl), (double)d1);
+            atomicAdd(&source_sum(2, sl), (double)d2);
         }
         // 3b. the remaining rounds, one pair per lane: the lane's own target while it has
         //     pairs, then queue entries in order (target side by LDS atomics)
@@ -943,30 +949,31 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 atomicAdd(&acc[2][tt], (double)c2);
             }
             if (own || don) {
-                atomicAdd(&racc[0][rq][sl], (double)d0);
-                atomicAdd(&racc[1][rq][sl], (double)d1);
-                atomicAdd(&racc[2][rq][sl], (double)d2);
+                atomicAdd(&source_sum(0, sl), (double)d0);
+                atomicAdd(&source_sum(1, sl), (double)d1);
+                atomicAdd(&source_sum(2, sl), (double)d2);
             }
         }
         __syncthreads();
         // retire the cnt ring sources: their source-side sums go to u^N
         if (lane < cnt) {
             const int slot = (rhead + lane) & (kSymRing - 1);
-            double v0 = 0.0, v1 = 0.0, v2 = 0.0;
+            double v[3];
 #pragma unroll
-            for (int rq = 0; rq < kCp; ++rq) {
-                v0 += racc[0][rq][lane];
-                v1 += racc[1][rq][lane];
-                v2 += racc[2][rq][lane];
-                racc[0][rq][lane] = 0.0;
-                racc[1][rq][lane] = 0.0;
-                racc[2][rq][lane] = 0.0;
+            for (int d = 0; d < 3; ++d) {
+                v[d] = racc[d][lane];
+                racc[d][lane] = 0.0;
+                if (d < kCopied) {
+                    const int e = (lane + kB / 2) & (kB - 1);
+                    v[d] += racc[3 + d][e];
+                    racc[3 + d][e] = 0.0;
+                }
             }
-            if (v0 != 0.0 || v1 != 0.0 || v2 != 0.0) {
+            if (v[0] != 0.0 || v[1] != 0.0 || v[2] != 0.0) {
                 const int64_t jj = ringk[slot] & (kFar - 1);
-                unsafeAtomicAdd(&u_near[jj], post * v0);
-                unsafeAtomicAdd(&u_near[(int64_t)n + jj], post * v1);
-                unsafeAtomicAdd(&u_near[2 * (int64_t)n + jj], post * v2);
+                unsafeAtomicAdd(&u_near[jj], post * v[0]);
+                unsafeAtomicAdd(&u_near[(int64_t)n + jj], post * v[1]);
+                unsafeAtomicAdd(&u_near[2 * (int64_t)n + jj], post * v[2]);
             }
         }
         __syncthreads();

@@ -34,3 +34,25 @@ def test_split_chunks_match_oracle(n, n_max, one_tile, deterministic):
     if one_tile:
         x = 0.51 + 0.03 * x  # inside one cell of the 32^3 grid's coarsest and finest tiles
     assert near_error(x, f, n_max, deterministic) < 1e-12
+
+
+@pytest.mark.parametrize("tol,bound", [(1e-11, 1e-12), (1e-9, 1e-10), (1e-7, 1e-9)])
+def test_largest_queue_excess_matches_oracle(tol, bound):
+    """Chunks whose first half accepts every source of a neighbouring tile and whose second half
+    none: 32 pairs for half the lanes, the largest excess a batch can have (512 pairs)."""
+    import paper_2606_19059_amd as E
+
+    rng = np.random.default_rng(31)
+    parts = []
+    # per tile of 0.5: clusters of 32 near one corner and 32 near the opposite one (farther apart than
+    # r_c), and in the next tile along z 96 sources within r_c of the first cluster only
+    for corner, n in (((0.03, 0.03, 0.42), 32), ((0.45, 0.45, 0.02), 32), ((0.05, 0.05, 0.53), 96)):
+        parts.append(np.array(corner)[:, None] + 0.02 * rng.random((3, n)))
+    x = np.concatenate(parts, axis=1)
+    f = rng.standard_normal(x.shape)
+    pl = E.Plan(BOX, tol, xi=10.0, r_c=0.4, grid=(32, 32, 32), P=8, window_shape=4.8, n_max=x.shape[1])
+    assert pl.info["tile"] == 16
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    un = pl.eval_parts(d(x), d(f))[0].cpu().numpy()
+    ref = oracle.real_space(x, f, BOX, 10.0, 0.4)
+    assert np.max(np.abs(un - ref)) < bound * np.max(np.abs(ref))
