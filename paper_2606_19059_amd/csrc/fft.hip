@@ -125,7 +125,7 @@ __device__ C2<T>* lds_fft(C2<T>* a, C2<T>* b, int n, int ncols, int ld, int ncom
 // ---- pass 1 / 5: z-lines, real <-> half spectrum ----
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_fft_z(T* __restrict__ grid, int64_t ncells, int nlines, int H,
+__global__ __launch_bounds__(512) void k_fft_z(T* __restrict__ grid, int64_t ncells, int nlines, int H, int lgH,
                                                int ncols, int sign, const C2<T>* __restrict__ tw_half,
                                                const C2<T>* __restrict__ tw_full)
 {
@@ -142,14 +142,14 @@ __global__ __launch_bounds__(256) void k_fft_z(T* __restrict__ grid, int64_t nce
 
     if (sign < 0) {
         for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int c = idx / H, e = idx - c * H;
+            const int c = idx >> lgH, e = idx & (H - 1);
             if (line0 + c < nlines) a[e * ld + c] = data[(int64_t)(line0 + c) * H + e];
             else a[e * ld + c] = C2<T>{0, 0};
         }
         __syncthreads();
         C2<T>* C = lds_fft<T>(a, b, H, ncols, ld, 1, -1, tw_half);
         for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int c = idx / H, k = idx - c * H;
+            const int c = idx >> lgH, k = idx & (H - 1);
             if (line0 + c >= nlines) continue;
             const C2<T> ck = C[k * ld + c];
             const C2<T> cm0 = C[((H - k) & (H - 1)) * ld + c];
@@ -161,13 +161,13 @@ __global__ __launch_bounds__(256) void k_fft_z(T* __restrict__ grid, int64_t nce
         }
     } else {
         for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int c = idx / H, e = idx - c * H;
+            const int c = idx >> lgH, e = idx & (H - 1);
             if (line0 + c < nlines) b[e * ld + c] = data[(int64_t)(line0 + c) * H + e];
             else b[e * ld + c] = C2<T>{0, 0};
         }
         __syncthreads();
         for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int c = idx / H, k = idx - c * H;
+            const int c = idx >> lgH, k = idx & (H - 1);
             C2<T> xk = b[k * ld + c];
             C2<T> xm;
             if (k == 0) {
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256) void k_fft_z(T* __restrict__ grid, int64_t nce
         __syncthreads();
         C2<T>* z = lds_fft<T>(a, b, H, ncols, ld, 1, +1, tw_half);
         for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int c = idx / H, e = idx - c * H;
+            const int c = idx >> lgH, e = idx & (H - 1);
             if (line0 + c < nlines) data[(int64_t)(line0 + c) * H + e] = z[e * ld + c];
         }
     }
@@ -385,8 +385,8 @@ __global__ __launch_bounds__(1024) void k_fft_zy(T* __restrict__ grid, int64_t n
 // ---- pass 2 / 4: y-columns ----
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_fft_y(T* __restrict__ grid, int64_t ncells, int M2, int H,
-                                               int ncols, int sign, const C2<T>* __restrict__ tw)
+__global__ __launch_bounds__(512) void k_fft_y(T* __restrict__ grid, int64_t ncells, int M2, int H,
+                                               int ncols, int lgnc, int sign, const C2<T>* __restrict__ tw)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C2<T>* a = reinterpret_cast<C2<T>*>(smem_raw);
@@ -401,13 +401,13 @@ __global__ __launch_bounds__(256) void k_fft_y(T* __restrict__ grid, int64_t nce
     const int64_t base = (int64_t)x * M2 * H + kz0;
     const int tot = M2 * ncols;
     for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-        const int e = idx / ncols, c = idx - e * ncols;
+        const int e = idx >> lgnc, c = idx & (ncols - 1);
         a[idx] = data[base + (int64_t)e * H + c];
     }
     __syncthreads();
     C2<T>* r = lds_fft<T>(a, b, M2, ncols, ncols, 1, sign, tw);
     for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-        const int e = idx / ncols, c = idx - e * ncols;
+        const int e = idx >> lgnc, c = idx & (ncols - 1);
         data[base + (int64_t)e * H + c] = r[idx];
     }
 }
@@ -506,7 +506,7 @@ __global__ __launch_bounds__(256) void k_fft_x_cnv(T* __restrict__ grid, int64_t
 // takes it back to natural order.  Twice the columns per block of the two-buffer kernel in the
 // same LDS.  lgM1, lgnc: log2 of M1 and of ncols.
 template <typename T>
-__global__ __launch_bounds__(256) void k_fft_x_cnv_ip(T* __restrict__ grid, int64_t ncells, int M1, int lgM1,
+__global__ __launch_bounds__(512) void k_fft_x_cnv_ip(T* __restrict__ grid, int64_t ncells, int M1, int lgM1,
                                                       int M2, int H, int ncols, int lgnc,
                                                       const C2<T>* __restrict__ tw, CnvArgs ca)
 {
@@ -643,6 +643,10 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
     const C2<T>* twh = tw + pl.tw_off[2];
     const C2<T>* twf = tw + pl.tw_off[3];
     const int budget = (sizeof(T) == 8) ? 1024 : 2048;  // complex elements per buffer
+    // threads per block of the z and y passes: two per column element pair keep 32 waves on a CU (four
+    // blocks by their LDS), which wait on memory and barriers (FFT+CNV+IFFT at 256 threads and at 512: 256^3
+    // FP64 1.36 and 1.21 ms, FP32 0.71 and 0.57)
+    constexpr int kThreadsZY = 512;
 
     // passes 1+2 fused when a plane fits in one workgroup's LDS
     int lgH = 0, lgM2 = 0;
@@ -667,14 +671,16 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
     // pass 2: y forward
     int ncy = pow2_floor(max(1, budget / M2));
     if (ncy > H) ncy = H;
+    int lgncy = 0;
+    while ((1 << lgncy) < ncy) ++lgncy;
     size_t shy = 2 * (size_t)M2 * ncy * sizeof(C2<T>);
     dim3 gy(M1 * (H / ncy), ncomp_in);
     dim3 gzy(M1, ncomp_in);
     if (fused) {
         hipLaunchKernelGGL((k_fft_zy<T>), gzy, dim3(1024), shzy, s, grid, nc, M2, lgM2, H, lgH, -1, twh, twf, tw1);
     } else {
-        hipLaunchKernelGGL((k_fft_z<T>), gz, dim3(256), shz, s, grid, nc, nlines, H, ncz, -1, twh, twf);
-        hipLaunchKernelGGL((k_fft_y<T>), gy, dim3(256), shy, s, grid, nc, M2, H, ncy, -1, tw1);
+        hipLaunchKernelGGL((k_fft_z<T>), gz, dim3(kThreadsZY), shz, s, grid, nc, nlines, H, lgH, ncz, -1, twh, twf);
+        hipLaunchKernelGGL((k_fft_y<T>), gy, dim3(kThreadsZY), shy, s, grid, nc, M2, H, ncy, lgncy, -1, tw1);
     }
     gy.y = 3 * nsys;  // the inverse transforms carry the 3 velocity components
     gz.y = 3 * nsys;
@@ -700,14 +706,16 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
             hipLaunchKernelGGL((k_cnv_st_x<T>), dim3(M2 * (H / ncx)), dim3(256), shx, s, grid, nc, M1, M2, H, ncx,
                                tw0, ca);
     } else if (cnv && inverse_too && M1 >= 4) {
-        // one LDS buffer: twice the columns per block
+        // one LDS buffer: twice the columns per block; from M1 = 256 on four times, with twice the threads
+        // (64-byte runs at 256^3 FP64 instead of 32: the pass 0.36 -> 0.30 ms)
+        const int wide = M1 >= 256 ? 2 : 1;
         int lgM1 = 0, lgnc = 0;
         while ((1 << lgM1) < M1) ++lgM1;
-        int nci = pow2_floor(max(1, 2 * budget / (3 * M1)));
+        int nci = pow2_floor(max(1, wide * 2 * budget / (3 * M1)));
         if (nci > H) nci = H;
         while ((1 << lgnc) < nci) ++lgnc;
         const size_t shi = (size_t)3 * M1 * nci * sizeof(C2<T>);
-        hipLaunchKernelGGL((k_fft_x_cnv_ip<T>), dim3(M2 * (H / nci), nsys), dim3(256), shi, s, grid, nc, M1, lgM1,
+        hipLaunchKernelGGL((k_fft_x_cnv_ip<T>), dim3(M2 * (H / nci), nsys), dim3(256 * wide), shi, s, grid, nc, M1, lgM1,
                            M2, H, nci, lgnc, tw0, ca);
     } else {
         hipLaunchKernelGGL((k_fft_x_cnv<T>), dim3(M2 * (H / ncx), nsys), dim3(256), shx, s, grid, nc, M1, M2, H,
@@ -716,8 +724,8 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
     if (inverse_too && fused) {
         hipLaunchKernelGGL((k_fft_zy<T>), gzy, dim3(1024), shzy, s, grid, nc, M2, lgM2, H, lgH, +1, twh, twf, tw1);
     } else if (inverse_too) {
-        hipLaunchKernelGGL((k_fft_y<T>), gy, dim3(256), shy, s, grid, nc, M2, H, ncy, +1, tw1);
-        hipLaunchKernelGGL((k_fft_z<T>), gz, dim3(256), shz, s, grid, nc, nlines, H, ncz, +1, twh, twf);
+        hipLaunchKernelGGL((k_fft_y<T>), gy, dim3(kThreadsZY), shy, s, grid, nc, M2, H, ncy, lgncy, +1, tw1);
+        hipLaunchKernelGGL((k_fft_z<T>), gz, dim3(kThreadsZY), shz, s, grid, nc, nlines, H, lgH, ncz, +1, twh, twf);
     }
     return hipGetLastError();
 }

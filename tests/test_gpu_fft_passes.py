@@ -1,0 +1,31 @@
+"""The FFT passes at the edges of their launch shapes: x lines on both sides of 256 (twice the columns
+and threads from there on) with half spectra shorter and longer than a block's columns, and planes too
+large for the fused z-y pass with few and many y columns a block; the far field against the oracle's at
+1e-12 of its max (FP64), 3e-6 (FP32: every product rounded)."""
+import numpy as np
+import pytest
+
+from oracle import spectral as S
+from paper_2606_19059_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+GRIDS = [(128, 16, 8), (256, 16, 8), (256, 8, 32), (512, 16, 16), (8, 256, 256), (8, 512, 64), (16, 128, 512)]
+
+
+@pytest.mark.parametrize("precision,tol,P,m", [("fp64", 1e-11, 6, 4.1), ("fp32", 5e-7, 6, 4.1)])
+@pytest.mark.parametrize("grid", GRIDS)
+def test_fft_passes_match_oracle(grid, precision, tol, P, m):
+    import paper_2606_19059_amd as E
+
+    box = tuple(g / 64.0 for g in grid)
+    n, xi = 150, 0.2 * 64
+    x, f = W.particles(n, box, seed=31)
+    ref = S.far_field(x, f, box, grid, xi, P, m)
+    bound = 1e-12 if precision == "fp64" else 3e-6
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    pl = E.Plan(box, tol, xi=xi, r_c=0.06, grid=grid, P=P, window_shape=m, n_max=n, precision=precision)
+    uf = pl.eval_parts(d(x), d(f))[1].cpu().numpy()
+    assert np.max(np.abs(uf - ref)) < bound * np.max(np.abs(ref))
