@@ -17,12 +17,9 @@
 //   1. the wave loads 64 candidate sources at a time (one per lane), keeps those within
 //      r_c of the targets' bounding box and appends them, shifted into the targets'
 //      periodic frame, to an LDS ring;
-//   2. per 32 ring sources every lane tests its target against each source (r^2 < r_c^2,
-//      r^2 > 0) and the accepted (target, source) pairs are appended to an LDS queue in
-//      source-major order (ballot + lane-prefix count);
-//   3. the queue is drained 64 pairs at a time, one pair per lane, every lane busy; each
-//      result is added to its target's FP64 accumulator in LDS with ds_add_f64 (the pairs
-//      of one source have distinct targets, so conflicts are few).
+//   2. per 32 ring sources the accepted sources of each lane's target (r^2 < r_c^2, r^2 > 0) are
+//      found as a mask;
+//   3. the batch's pairs are evaluated one pair per lane, every lane busy (the balanced drain below).
 #include "internal.h"
 #include <algorithm>
 #include <type_traits>
@@ -48,7 +45,7 @@ namespace {
 // leading coefficients (screening.h), so that Horner starts with an addition (an FMA cannot take two
 // scalar-register coefficients).  The FP64 pair formula therefore returns its coefficients divided by
 // post; the kernels multiply each target's and source's sum by post once, at the end.
-// Levels 1 and 2 of the symmetric kernel work on positions scaled by kappa = xi sqrt(log2 e), which
+// Levels 1 and 2 work (without stresslet sources) on positions scaled by kappa = xi sqrt(log2 e), which
 // makes the exponent -r^2 itself and r the polynomials' variable (two multiplications per pair less).
 constexpr double kLog2e = 1.4426950408889634074;
 
@@ -218,8 +215,8 @@ __device__ inline double screen_w64(double X, const PairArgs& a)
 
 // Coefficients of G^N(r) f = a1 f + b (r.f) r for 0 < r^2 < r_c^2 (FP64), divided by post:
 // a1 = C/r - (4 xi/sqrt(pi)) e, b = C/r^3, with e = e^{-xi^2 r^2} = lead_e e' and C = e Q,
-// Q = lead_s Q'.  Scaled (levels 1 and 2): r2 is (kappa r)^2, and a1, b are for the scaled r.
-template <int Lv, bool Scaled>
+// Q = lead_s Q'.  Levels 1 and 2: r2 is (kappa r)^2, and a1, b are for the scaled r.
+template <int Lv>
 __device__ inline void coef64(double r2, const PairArgs& a, double& a1, double& b)
 {
     const double rinv = rsqrt_pos<Lv>(r2);
@@ -227,15 +224,12 @@ __device__ inline void coef64(double r2, const PairArgs& a, double& a1, double& 
     if constexpr (Lv == 0) {
         e = exp(-a.xi2 * r2);
         q = screen_q64<Lv>(a.xi * r2 * rinv, a);
-    } else if constexpr (Scaled) {
+    } else {
         e = exp2_lead<Lv>(-r2, a);
         q = screen_w64<Lv>(r2 * rinv, a);
-    } else {
-        e = exp2_lead<Lv>(a.zc * r2, a);
-        q = screen_w64<Lv>(a.kappa * r2 * rinv, a);
     }
     const double Cr = e * q * rinv;
-    a1 = fma(Scaled ? -a.hs : -a.h, e, Cr);
+    a1 = fma(Lv > 0 ? -a.hs : -a.h, e, Cr);
     b = Cr * (rinv * rinv);
 }
 
@@ -267,21 +261,21 @@ __device__ inline void coef32(double r2d, const PairArgs& a, float& a1, float& b
     b = Cr * (rinv * rinv);
 }
 
-// Pair coefficients in the formula precision TF (double: FP64 path at accuracy level Lv, on scaled
-// positions or not; float: FP32 bulk, Lv unused).
-template <typename TF, int Lv, bool Scaled>
+// Pair coefficients in the formula precision TF (double: FP64 path at accuracy level Lv; float: FP32
+// bulk, Lv unused).
+template <typename TF, int Lv>
 struct Coef;
 // post: the factor that the sums of eval's contributions take at the end
-template <int Lv, bool Scaled>
-struct Coef<double, Lv, Scaled> {
+template <int Lv>
+struct Coef<double, Lv> {
     __device__ static inline void eval(double r2, const PairArgs& a, double& a1, double& b)
     {
-        coef64<Lv, Scaled>(r2, a, a1, b);
+        coef64<Lv>(r2, a, a1, b);
     }
-    __device__ static inline double post(const PairArgs& a) { return Scaled ? a.post * a.kappa : a.post; }
+    __device__ static inline double post(const PairArgs& a) { return Lv > 0 ? a.post * a.kappa : a.post; }
 };
 template <int Lv>
-struct Coef<float, Lv, false> {
+struct Coef<float, Lv> {
     __device__ static inline void eval(double r2, const PairArgs& a, float& a1, float& b) { coef32(r2, a, a1, b); }
     __device__ static inline double post(const PairArgs&) { return 1.0; }
 };
@@ -369,38 +363,18 @@ __device__ inline void apply(TF a1, TF b, TF rx, TF ry, TF rz, TF f0, TF f1, TF 
 }
 
 constexpr int kRing = 128;   // LDS ring of filtered candidate sources
-constexpr int kTest = 32;    // sources tested per round (queue <= kTest * 64 pairs)
+constexpr int kTest = 32;    // sources tested per round
 
-// TF: precision of the pair formula and of the staged forces; TA: accumulator precision.
-// Positions and the r^2 < r_c^2 test are FP64 in both modes (same VALU rate as FP32).
-// Count: no pair formula; the wave only counts its accepted (target, source) pairs and adds
-// the count to *pair_count (one integer atomic per wave): the exact number of ordered pairs
-// the near-field sum runs over, for measurement.
-// NW waves share a chunk: wave w takes every NW-th batch of 64 candidate sources from batch w on, and
-// their sums are added in wave order (one block per chunk, so that small inputs, whose chunks do not
-// fill the chip, still have a fixed order of summation).
-template <typename TF, typename TA, int Lv, int NW, bool Count = false>
-__global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict__ rec,
-                                            const int* __restrict__ start,
-                                            const int* __restrict__ chunk_off, Geometry g,
-                                            PairArgs a, double* __restrict__ u_near,
-                                            unsigned long long* __restrict__ pair_count = nullptr)
+// The number of ordered pairs within the cutoff that the near-field sum runs over, for measurement: every
+// wave counts its targets' and adds the count to *pair_count (one integer atomic per wave).
+__global__ __launch_bounds__(64) void k_count_pairs(const Rec64* __restrict__ rec, const int* __restrict__ start,
+                                                    const int* __restrict__ chunk_off, Geometry g, PairArgs a,
+                                                    unsigned long long* __restrict__ pair_count)
 {
-    __shared__ double tgt_[NW][3][kWave];
-    __shared__ TA acc_[NW][3][kWave];
-    __shared__ double ring_[NW][3][kRing];
-    __shared__ TF ringf_[NW][3][kRing];
-    __shared__ unsigned short queue_[NW][kTest * kWave];
+    __shared__ double ring[3][kRing];
 
-    // plain block order: an XCD-aware order (each XCD sweeping a contiguous range) was
-    // measured 12% slower here, unlike in G2P
     const int wave = uniform_i((int)blockIdx.x);
-    const int wid = uniform_i((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
-    double(&tgt)[3][kWave] = tgt_[wid];
-    TA(&acc)[3][kWave] = acc_[wid];
-    double(&ring)[3][kRing] = ring_[wid];
-    TF(&ringf)[3][kRing] = ringf_[wid];
-    unsigned short(&queue)[kTest * kWave] = queue_[wid];
+    const int lane = threadIdx.x;
     const int total = chunk_off[g.ntiles * g.nsys];  // chunks of all systems
     if (wave >= total) return;
 
@@ -428,51 +402,18 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
         blo[d] = uniform_d(wave_min(me.x[d]));
         bhi[d] = uniform_d(wave_max(me.x[d]));
         tx[d] = active ? me.x[d] : 1e30;  // an inactive lane accepts no pair
-        tgt[d][lane] = tx[d];
-        acc[d][lane] = (TA)0;
     }
-    wave_lds_sync();
 
     int rhead = 0, rcount = 0;
-    int turn = wid;  // batches to pass over before the next of this wave's
     unsigned long long counted = 0;
 
-    // test the targets against ring sources [rhead, rhead + cnt), then drain the queue
+    // test the targets against ring sources [rhead, rhead + cnt)
     auto process = [&](int cnt) {
-        int qn = 0;
         for (int j = 0; j < cnt; ++j) {
             const int slot = (rhead + j) & (kRing - 1);
             const double rx = tx[0] - ld1(ring[0][slot]), ry = tx[1] - ld1(ring[1][slot]), rz = tx[2] - ld1(ring[2][slot]);
             const double r2 = rx * rx + ry * ry + rz * rz;
-            const bool pass = (r2 < a.rc2) && (r2 > 0.0);
-            const unsigned long long b = __ballot(pass);
-            if (!Count && pass) queue[qn + lanes_below(b)] = (unsigned short)(lane | (j << 6));
-            qn += __popcll(b);
-        }
-        if (Count) {
-            counted += (unsigned long long)qn;
-            wave_lds_sync();
-            return;
-        }
-        wave_lds_sync();
-        for (int q0 = 0; q0 < qn; q0 += kWave) {
-            const int k = q0 + lane;
-            if (k < qn) {
-                const int e = queue[k];
-                const int tt = e & (kWave - 1);
-                const int slot = (rhead + (e >> 6)) & (kRing - 1);
-                const double rx = ld1(tgt[0][tt]) - ld1(ring[0][slot]);
-                const double ry = ld1(tgt[1][tt]) - ld1(ring[1][slot]);
-                const double rz = ld1(tgt[2][tt]) - ld1(ring[2][slot]);
-                const double r2 = rx * rx + ry * ry + rz * rz;
-                TF a1, b, c0, c1, c2;
-                Coef<TF, Lv, false>::eval(r2, a, a1, b);
-                apply<TF>(a1, b, (TF)rx, (TF)ry, (TF)rz, ld1(ringf[0][slot]), ld1(ringf[1][slot]), ld1(ringf[2][slot]), c0,
-                          c1, c2);
-                atomicAdd(&acc[0][tt], (TA)c0);
-                atomicAdd(&acc[1][tt], (TA)c1);
-                atomicAdd(&acc[2][tt], (TA)c2);
-            }
+            counted += (unsigned long long)__popcll(__ballot((r2 < a.rc2) && (r2 > 0.0)));
         }
         wave_lds_sync();
     };
@@ -500,24 +441,14 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
                 const int nt = tbase + (wx * g.NT[1] + wy) * g.NT[2] + wz;
                 const int sa = start[nt * per], sb = start[(nt + 1) * per];
                 for (int base = sa; base < sb; base += kWave) {
-                    if (NW > 1) {
-                        if (turn > 0) {  // another wave of this chunk takes the batch
-                            --turn;
-                            continue;
-                        }
-                        turn = NW - 1;
-                    }
                     const int s = base + lane;
                     bool keep = false;
-                    double sx = 0, sy = 0, sz = 0, f0 = 0, f1 = 0, f2 = 0;
+                    double sx = 0, sy = 0, sz = 0;
                     if (s < sb) {
                         const Rec64& q = rec[s];
                         sx = q.x[0] + shx;
                         sy = q.x[1] + shy;
                         sz = q.x[2] + shz;
-                        f0 = q.f[0];
-                        f1 = q.f[1];
-                        f2 = q.f[2];
                         const double ex = fmax(0.0, fmax(blo[0] - sx, sx - bhi[0]));
                         const double ey = fmax(0.0, fmax(blo[1] - sy, sy - bhi[1]));
                         const double ez = fmax(0.0, fmax(blo[2] - sz, sz - bhi[2]));
@@ -529,9 +460,6 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
                         ring[0][slot] = sx;
                         ring[1][slot] = sy;
                         ring[2][slot] = sz;
-                        ringf[0][slot] = (TF)f0;
-                        ringf[1][slot] = (TF)f1;
-                        ringf[2][slot] = (TF)f2;
                     }
                     rcount += __popcll(b);
                     wave_lds_sync();
@@ -550,21 +478,7 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
         rhead = (rhead + c) & (kRing - 1);
         rcount -= c;
     }
-    if (Count) {
-        if (lane == 0 && counted > 0) atomicAdd(pair_count, counted);
-        return;
-    }
-    if (NW > 1) __syncthreads();
-    if (active && wid == 0) {
-        const double post = Coef<TF, Lv, false>::post(a);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            double v = (double)acc_[0][d][lane];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) v += (double)acc_[w][d][lane];
-            u_near[d * (int64_t)n + i] = post * v;
-        }
-    }
+    if (lane == 0 && counted > 0) atomicAdd(pair_count, counted);
 }
 
 // ---------------------------------------------------------------- symmetric form
@@ -575,7 +489,7 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
 // -D carries the same pairs.  The source side accumulates per ring entry in LDS and is
 // added to u^N with one FP64 atomic per component and source when the entry retires.
 // The sort zeroes u^N.  The order of those atomic additions varies between runs, so
-// results agree to rounding, not bitwise (the one-sided kernel above is the reproducible
+// results agree to rounding, not bitwise (the one-sided kernel below is the reproducible
 // variant).
 //
 // Balanced drain.  LDS traffic, not arithmetic, bounded an earlier form that put every
@@ -601,7 +515,7 @@ __global__ __launch_bounds__(64 * NW) void k_p2p(int n, const Rec64* __restrict_
 // source: c2 P2P 22.9 -> 21.3 ms, H 12.2 -> 11.3 ms.  The matrix instructions hold the SIMD for 64 cycles
 // each (no vector instruction issues meanwhile), so the test costs 128 + 75 issue slots per batch (128 +
 // 128 with comparisons and ballots); with the weighted polynomials on scaled positions c2 18.3 -> 17.85 ms,
-// c3 165 -> 161 ms.  The own tile, whose
+// c3 165 -> 161 ms when it was made.  The own tile, whose
 // pairs also need r > 0 and the index order, and the last, shorter batch keep the direct test;
 // the direct difference of repeated positions is exactly 0 also in the centred frame.
 constexpr int kSymRing = 64;
@@ -617,6 +531,46 @@ static_assert(kBalBatch == 32 && kSymRing == 64, "the mask, ring and queue sizes
 // wave ballot of a condition, without materialising it as an integer first
 __device__ inline unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
+// Cutoff test of a full batch past the own tile, |s' - t'|^2 < r_c^2  <=>  |s'|^2 - 2 s'.t' + |t'|^2 - r_c^2 < 0,
+// for 32 sources x 64 targets by eight v_mfma_f64_16x16x4f64 (sources as rows): the accepted sources of
+// each lane's target, as a mask.  On gfx950 lane l = 16 kq + i supplies A[i][kq] and B[kq][i] and
+// receives D[4 r + kq][i], r = 0..3.  Batches start at ring slot 0 or 32 (32 entries at a time from a
+// 64-slot ring), so the batch's slots need no wrap.  bt: the target operands (target_operands).
+__device__ inline unsigned accept_mask(double (&ring)[4][kSymRing], int rhead, const double (&bt)[4], int mi, int mk)
+{
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    unsigned m = 0;
+    // source operand A = (-2 x, -2 y, -2 z, 1): row rho of block mb is slot 8 (rho % 4) + 4 mb + rho / 4,
+    // so that result item r of lane (kq, i) -- row 4 r + kq -- is slot 8 kq + 4 mb + r: a lane's eight
+    // items are eight consecutive bits of the batch mask, and start from |s'|^2 of eight
+    // consecutive slots
+    double av[2];
+    v4d cv[2];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) {
+        const double xk = ld1(ring[mk < 3 ? mk : 0][rhead + 8 * (mi & 3) + 4 * mb + (mi >> 2)]);
+        av[mb] = mk < 3 ? -2.0 * xk : 1.0;
+        cv[mb] = *reinterpret_cast<const v4d*>(&ring[3][rhead + 8 * mk + 4 * mb]);
+    }
+    // the sign bit of an item is its test.  The bits of target 16 nb + i are spread over lanes
+    // (kq, i), kq = 0..3: OR over the four rows, kept by the lanes of row nb (the target's own lane)
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+        unsigned v = 0;
+#pragma unroll
+        for (int mb = 1; mb >= 0; --mb) {
+            const v4d dd = __builtin_amdgcn_mfma_f64_16x16x4f64(av[mb], bt[nb], cv[mb], 0, 0, 0);
+#pragma unroll
+            for (int r = 3; r >= 0; --r)  // v = 2 v + sign
+                v = __builtin_amdgcn_alignbit(v, (unsigned)__double2hiint(dd[r]), 31);
+        }
+        v = or_rows4(v << (8 * mk));
+        m = mk == nb ? v : m;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return m;
+}
+
 // ST: stresslet sources too (srec: sorted symmetric tensors, 6 per particle); T^N is odd,
 // so the source side of a pair takes -T^N(r) S_target.
 template <typename TF, int Lv, bool ST>
@@ -628,7 +582,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
 {
     constexpr int NS = ST ? 6 : 1;
     constexpr bool kScaled = !ST && std::is_same<TF, double>::value && Lv > 0;
-    using PairCoef = Coef<TF, Lv, kScaled>;
+    using PairCoef = Coef<TF, Lv>;
     __shared__ double tgt[3][kWave];  // t' (x, y, z)
     __shared__ TF tgtf[3][kWave];
     __shared__ TF tgts[NS][kWave];
@@ -738,40 +692,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 m = pass ? (m | (1u << j)) : m;
             }
         } else if (cnt == kB) {
-            // a full batch past the own tile: |s' - t'|^2 < r_c^2  <=>  |s'|^2 - 2 s'.t' + |t'|^2 - r_c^2 < 0,
-            // for 32 sources x 64 targets by eight v_mfma_f64_16x16x4f64 (sources as rows).  On gfx950 lane
-            // l = 16 kq + i supplies A[i][kq] and B[kq][i] and receives D[4 r + kq][i], r = 0..3.  Batches
-            // start at ring slot 0 or 32 (32 entries at a time from a 64-slot ring), so the batch's slots
-            // need no wrap.
-            typedef double v4d __attribute__((ext_vector_type(4)));
-            // source operand A = (-2 x, -2 y, -2 z, 1): row rho of block mb is slot 8 (rho % 4) + 4 mb + rho / 4,
-            // so that result item r of lane (kq, i) -- row 4 r + kq -- is slot 8 kq + 4 mb + r: a lane's eight
-            // items are eight consecutive bits of the batch mask, and start from |s'|^2 of eight
-            // consecutive slots
-            double av[2];
-            v4d cv[2];
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb) {
-                const double xk = ld1(ring[mk < 3 ? mk : 0][rhead + 8 * (mi & 3) + 4 * mb + (mi >> 2)]);
-                av[mb] = mk < 3 ? -2.0 * xk : 1.0;
-                cv[mb] = *reinterpret_cast<const v4d*>(&ring[3][rhead + 8 * mk + 4 * mb]);
-            }
-            // the sign bit of an item is its test.  The bits of target 16 nb + i are spread over lanes
-            // (kq, i), kq = 0..3: OR over the four rows, kept by the lanes of row nb (the target's own lane)
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                unsigned v = 0;
-#pragma unroll
-                for (int mb = 1; mb >= 0; --mb) {
-                    const v4d dd = __builtin_amdgcn_mfma_f64_16x16x4f64(av[mb], bt[nb], cv[mb], 0, 0, 0);
-#pragma unroll
-                    for (int r = 3; r >= 0; --r)  // v = 2 v + sign
-                        v = __builtin_amdgcn_alignbit(v, (unsigned)__double2hiint(dd[r]), 31);
-                }
-                v = or_rows4(v << (8 * mk));
-                m = mk == nb ? v : m;
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            m = accept_mask(ring, rhead, bt, mi, mk);
         } else {
             for (int j = 0; j < cnt; ++j) {
                 const int slot = (rhead + j) & (kSymRing - 1);
@@ -1076,6 +997,284 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
     }
 }
 
+// ---------------------------------------------------------------- one-sided form
+// The deterministic mode's kernel: a wave's targets meet every source around them (each pair is evaluated
+// from both of its sides), so that a sum is made by one block, in a fixed order: registers and the
+// wave's own LDS, no global atomics.  The balanced drain above without its source side: a lane keeps
+// up to R of its target's pairs, in the order of the ring (lanes that accept the same source read it
+// together), and the excess goes through the queue to lanes without pairs of their own.
+// The own tile comes first, so that only a wave's first batches need r > 0.  NW waves share a chunk, wave
+// w takes the sources w, w + NW, ... of a row, and their sums are added in wave order.
+// Sources are dealt one by one along a row of tiles, so that the waves of a chunk get alike shares of
+// every region around it (by batches of 64 in the order of the sort, the largest share of eight waves was
+// 1.39 times the mean at 3e4, and the block waits for it: 0.36 -> 0.31 ms at 3e4, 31.5 -> 29.2 at 1e6).
+// Bound by FP64 issue, and at small sizes by the waves in flight: 1e6 uniform at 1e-8, 128^3, 25.3 ms (33.9
+// with every pair through an LDS queue and its three LDS atomics); 3e4, KB, 0.31 (0.48).
+template <typename TF, int Lv, int NW>
+__global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k_p2p_one(int n, const Rec64* __restrict__ rec,
+                                                     const int* __restrict__ start,
+                                                     const int* __restrict__ chunk_off, Geometry g, PairArgs a,
+                                                     double* __restrict__ u_near)
+{
+    constexpr bool kScaled = std::is_same<TF, double>::value && Lv > 0;
+    using PairCoef = Coef<TF, Lv>;
+    constexpr int kB = kBalBatch;
+    __shared__ double tgt_[NW][3][kWave];  // t' (x, y, z)
+    __shared__ double acc_[NW][3][kWave];
+    __shared__ __align__(32) double ring_[NW][4][kSymRing];  // s' (x, y, z) and |s'|^2
+    __shared__ TF ringf_[NW][3][kSymRing];
+    __shared__ unsigned short queue_[NW][kBalExcess];
+
+    const int wave = uniform_i((int)blockIdx.x);
+    const int wid = uniform_i((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    double(&tgt)[3][kWave] = tgt_[wid];
+    double(&acc)[3][kWave] = acc_[wid];
+    double(&ring)[4][kSymRing] = ring_[wid];
+    TF(&ringf)[3][kSymRing] = ringf_[wid];
+    unsigned short(&queue)[kBalExcess] = queue_[wid];
+    const int total = chunk_off[g.ntiles * g.nsys];  // chunks of all systems
+    if (wave >= total) return;
+
+    // tile of this wave: largest t with chunk_off[t] <= wave
+    int lo = 0, hi = g.ntiles * g.nsys;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (chunk_off[mid] <= wave) lo = mid; else hi = mid;
+    }
+    const int t = lo;
+    const int per = 1 << (3 * g.log2B);
+    const int t_end = start[(t + 1) * per];
+    const int first = start[t * per] + (wave - chunk_off[t]) * kWave;
+    const int i = first + lane;
+    const bool active = i < t_end;
+    const Rec64 me = rec[active ? i : first];
+
+    // tile t of system sys (the systems of a batch have consecutive tile ranges)
+    const int sys = t / g.ntiles, tl = t - sys * g.ntiles, tbase = sys * g.ntiles;
+    const int tc[3] = {tl / (g.NT[1] * g.NT[2]), (tl / g.NT[2]) % g.NT[1], tl % g.NT[2]};
+    double w[3], blo[3], bhi[3], cen[3], tx[3], oacc[3];
+    const double rc2 = kScaled ? a.rc2s : a.rc2;  // of the (scaled) positions relative to the centre
+    double tlim = -rc2;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        w[d] = g.B * g.h[d];
+        blo[d] = uniform_d(wave_min(me.x[d]));
+        bhi[d] = uniform_d(wave_max(me.x[d]));
+        cen[d] = uniform_d(0.5 * (blo[d] + bhi[d]));
+        tx[d] = active ? me.x[d] - cen[d] : 1e30;  // an inactive lane accepts no pair
+        if (kScaled) tx[d] *= a.kappa;
+        tlim += tx[d] * tx[d];
+        tgt[d][lane] = tx[d];
+        acc[d][lane] = 0.0;
+        oacc[d] = 0.0;
+    }
+    wave_lds_sync();
+    const int mi = lane & 15, mk = lane >> 4;  // lane = 16 mk + mi
+    double bt[4];  // target operands of accept_mask
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+        const double l = __shfl(tlim, 16 * nb + mi, kWave);
+        bt[nb] = mk < 3 ? tgt[mk < 3 ? mk : 0][16 * nb + mi] : l;
+    }
+
+    int rhead = 0, rcount = 0;
+    int own_left = 0;  // ring entries of the own tile
+
+    auto process = [&](int cnt) {
+        unsigned m = 0;
+        if (own_left == 0 && cnt == kB) {
+            m = accept_mask(ring, rhead, bt, mi, mk);
+        } else {
+            for (int j = 0; j < cnt; ++j) {
+                const int slot = (rhead + j) & (kSymRing - 1);
+                const double rx = tx[0] - ld1(ring[0][slot]), ry = tx[1] - ld1(ring[1][slot]), rz = tx[2] - ld1(ring[2][slot]);
+                const double r2 = rx * rx + ry * ry + rz * rz;
+                const bool pass = (r2 < rc2) & (r2 > 0.0);
+                m = pass ? (m | (1u << j)) : m;
+            }
+        }
+        own_left = own_left > cnt ? own_left - cnt : 0;
+        const int c = __popc(m);
+        const int qn = wave_sum_i(c);
+        const int rounds = (qn + kWave - 1) / kWave;
+        const int own_n = c < rounds ? c : rounds;
+        // the excess, from the mask's upper end, to the queue
+        unsigned rm = m;
+        int ex = c - own_n;
+        int qx = 0;
+        for (;;) {
+            const bool wr = ex > 0;
+            const unsigned long long bw = ballot(wr);
+            if (bw == 0) break;
+            if (wr) {
+                const int p = 31 - __clz(rm);
+                rm ^= 1u << p;
+                queue[qx + lanes_below(bw)] = (unsigned short)(lane | (p << 6));
+                --ex;
+            }
+            qx += __popcll(bw);
+        }
+        wave_lds_sync();
+        // c = G^N(r) f_source of the pair (target at p, ring slot)
+        auto pair = [&](double p0, double p1, double p2, int slot, double& c0, double& c1, double& c2) {
+            const double rx = p0 - ld1(ring[0][slot]), ry = p1 - ld1(ring[1][slot]), rz = p2 - ld1(ring[2][slot]);
+            TF a1, b, e0, e1, e2;
+            PairCoef::eval(rx * rx + ry * ry + rz * rz, a, a1, b);
+            apply<TF>(a1, b, (TF)rx, (TF)ry, (TF)rz, ld1(ringf[0][slot]), ld1(ringf[1][slot]), ld1(ringf[2][slot]),
+                      e0, e1, e2);
+            c0 = (double)e0;
+            c1 = (double)e1;
+            c2 = (double)e2;
+        };
+        // rounds in which every lane takes a pair of its own target: summed in registers
+        const int own_all = wave_min_small(own_n);
+        double px = tx[0], py = tx[1], pz = tx[2];
+        for (int r = 0; r < own_all; ++r) {
+            const int slot = rhead + __builtin_ctz(rm);
+            rm &= rm - 1;
+            double c0, c1, c2;
+            pair(px, py, pz, slot, c0, c1, c2);
+            oacc[0] += c0;
+            oacc[1] += c1;
+            oacc[2] += c2;
+        }
+        // the rest: a lane without a pair of its own takes a queued one (its target by LDS atomics; a
+        // lane that is not own in a round is not own in any later one)
+        int qb = 0;
+        for (int r = own_all; r < rounds; ++r) {
+            const bool own = r < own_n;
+            const unsigned long long bi = ballot(!own);
+            const int q = qb + lanes_below(bi);
+            qb += __popcll(bi);
+            const bool don = !own && q < qx;
+            const int e = queue[q < qx ? q : 0];
+            const int tt = e & (kWave - 1);
+            const int slot = rhead + (own ? __builtin_ctz(rm) : (e >> 6) & (kB - 1));
+            if (!own) {
+                px = ld1(tgt[0][tt]);
+                py = ld1(tgt[1][tt]);
+                pz = ld1(tgt[2][tt]);
+            }
+            double c0, c1, c2;
+            pair(px, py, pz, slot, c0, c1, c2);
+            if (own) {
+                asm volatile("");  // keeps this a branch
+                oacc[0] += c0;
+                oacc[1] += c1;
+                oacc[2] += c2;
+                rm &= rm - 1;
+            }
+            if (don) {
+                atomicAdd(&acc[0][tt], c0);
+                atomicAdd(&acc[1][tt], c1);
+                atomicAdd(&acc[2][tt], c2);
+            }
+        }
+        wave_lds_sync();
+    };
+
+    // sources [sa, sb) of the tiles with the shift (shx, shy, shz)
+    auto sources = [&](int sa, int sb, double shx, double shy, double shz, bool own) {
+        for (int base = sa; base < sb; base += kWave * NW) {
+            const int s = base + lane * NW + wid;
+            bool keep = false;
+            double sx = 0, sy = 0, sz = 0, f0 = 0, f1 = 0, f2 = 0;
+            if (s < sb) {
+                const Rec64& q = rec[s];
+                sx = q.x[0] + shx;
+                sy = q.x[1] + shy;
+                sz = q.x[2] + shz;
+                f0 = q.f[0];
+                f1 = q.f[1];
+                f2 = q.f[2];
+                const double ex = fmax(0.0, fmax(blo[0] - sx, sx - bhi[0]));
+                const double ey = fmax(0.0, fmax(blo[1] - sy, sy - bhi[1]));
+                const double ez = fmax(0.0, fmax(blo[2] - sz, sz - bhi[2]));
+                keep = ex * ex + ey * ey + ez * ez < a.rc2;
+                sx -= cen[0];
+                sy -= cen[1];
+                sz -= cen[2];
+                if (kScaled) {
+                    sx *= a.kappa;
+                    sy *= a.kappa;
+                    sz *= a.kappa;
+                }
+            }
+            // append in two halves so the 64-slot ring never holds more than 63
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const bool mine = keep && ((lane >> 5) == half);
+                const unsigned long long bm = ballot(mine);
+                if (mine) {
+                    const int slot = (rhead + rcount + lanes_below(bm)) & (kSymRing - 1);
+                    ring[0][slot] = sx;
+                    ring[1][slot] = sy;
+                    ring[2][slot] = sz;
+                    ring[3][slot] = sx * sx + sy * sy + sz * sz;
+                    ringf[0][slot] = (TF)f0;
+                    ringf[1][slot] = (TF)f1;
+                    ringf[2][slot] = (TF)f2;
+                }
+                rcount += __popcll(bm);
+                if (own) own_left += __popcll(bm);
+                wave_lds_sync();
+                if (rcount >= kB) {
+                    process(kB);
+                    rhead = (rhead + kB) & (kSymRing - 1);
+                    rcount -= kB;
+                }
+            }
+        }
+    };
+    // the own tile (row -1), then the rows of tiles along z, whose consecutive tiles in reach (of one
+    // periodic image) are consecutive sources
+    const int ny = 2 * g.S[1] + 1, nrow = (2 * g.S[0] + 1) * ny;
+    for (int row = -1; row < nrow; ++row) {
+        const int dx = row < 0 ? 0 : row / ny - g.S[0], dy = row < 0 ? 0 : row % ny - g.S[1];
+        const int ux = tc[0] + dx, uy = tc[1] + dy;
+        const int fx = floor_div(ux, g.NT[0]), fy = floor_div(uy, g.NT[1]);
+        const double shx = fx * g.L[0], shy = fy * g.L[1];
+        const double gx = fmax(0.0, fmax(ux * w[0] - bhi[0], blo[0] - (ux + 1) * w[0]));
+        const double gy = fmax(0.0, fmax(uy * w[1] - bhi[1], blo[1] - (uy + 1) * w[1]));
+        if (gx * gx + gy * gy >= a.rc2) continue;
+        const int line = tbase + ((ux - fx * g.NT[0]) * g.NT[1] + uy - fy * g.NT[1]) * g.NT[2];
+        const int z0 = row < 0 ? 0 : -g.S[2], z1 = row < 0 ? 0 : g.S[2];
+        int sa = 0, sb = 0, image = 0;  // the run of tiles so far
+        for (int dz = z0; dz <= z1 + 1; ++dz) {
+            const int uz = tc[2] + dz, fz = floor_div(uz, g.NT[2]);
+            const double gz = fmax(0.0, fmax(uz * w[2] - bhi[2], blo[2] - (uz + 1) * w[2]));
+            const bool own = dx == 0 && dy == 0 && dz == 0;
+            const bool take = dz <= z1 && gx * gx + gy * gy + gz * gz < a.rc2 && own == (row < 0);
+            const int nt = line + uz - fz * g.NT[2];
+            if (take && sb > sa && fz == image) {
+                sb = start[(nt + 1) * per];
+                continue;
+            }
+            sources(sa, sb, shx, shy, image * g.L[2], row < 0);
+            sa = sb = 0;
+            if (take) {
+                sa = start[nt * per];
+                sb = start[(nt + 1) * per];
+                image = fz;
+            }
+        }
+    }
+    if (rcount > 0) process(rcount);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) acc[d][lane] += oacc[d];
+    if (NW > 1) __syncthreads();
+    if (active && wid == 0) {
+        const double post = PairCoef::post(a);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            double v = acc_[0][d][lane];
+#pragma unroll
+            for (int k = 1; k < NW; ++k) v += acc_[k][d][lane];
+            u_near[d * (int64_t)n + i] = post * v;
+        }
+    }
+}
+
 }  // namespace
 
 namespace {
@@ -1127,8 +1326,8 @@ hipError_t launch_count_pairs(const Plan& pl, const Work& w, int n, unsigned lon
         Geometry g = pl.g;
         g.nsys = nsys;
         const int64_t waves = (int64_t)g.ntiles * nsys + (n + kWave - 1) / kWave;
-        hipLaunchKernelGGL((k_p2p<double, double, 0, 1, true>), dim3((unsigned)waves), dim3(kWave), 0, s, n,
-                           (const Rec64*)w.rec, w.start, w.chunk_off, g, a, nullptr, count);
+        hipLaunchKernelGGL(k_count_pairs, dim3((unsigned)waves), dim3(kWave), 0, s, (const Rec64*)w.rec, w.start,
+                           w.chunk_off, g, a, count);
     }
     return hipGetLastError();
 }
@@ -1138,10 +1337,10 @@ static int pair_level(double tol) { return tol >= 1e-8 ? 2 : tol >= 1e-10 ? 1 : 
 
 // Waves per chunk of the deterministic kernel, by the plan alone (a system's sums must not depend on
 // what else is evaluated with it): more where even the plan's largest input has few chunks.  P2P ms at
-// 1 / 2 / 4 / 8 / 12 waves: 24 chunks (1e3 uniform, FP64) 0.232 / 0.137 / 0.088 / 0.072 / 0.066; 533 (3e4, KB)
-// 1.38 / 0.88 / 0.48 / 0.58 / 0.47; 3637 (2e5) 2.71 / 2.10 / 1.95 / 3.14 / 2.64; 19721 (1e6, 256^3) 6.63 / 6.43 /
-// 7.07 / 12.4 / 10.8, (1e6, 128^3) 35.8 / 33.9 / 34.3 / 56.3 / 47.0.  Four waves take 46 KB of LDS (three
-// blocks per CU), eight 92 KB (one).
+// 1 / 2 / 4 / 8 / 16 waves: 24 chunks (1e3 uniform, FP64) 0.214 / 0.123 / 0.078 / 0.064 / 0.074; 533 (3e4, KB)
+// 1.16 / 0.73 / 0.39 / 0.31 / 0.35; 1536 (6.6e4) 0.48 / 0.33 / 0.28 / 0.34 / 0.55; 3637 (2e5) 2.00 / 1.67 / 1.48 /
+// 1.67 / 2.34; 19721 (1e6, 256^3) 4.83 / 4.87 / 4.98 / 6.47 / 10.3, (1e6, 128^3) 26.4 / 26.0 / 25.3 / 29.2 / 39.6.
+// Blocks of four waves leave a CU room for five of them, of eight (61 KB of LDS) for two.
 template <typename TF, int Lv>
 void launch_p2p_det(const Plan& pl, const Work& w, int n, hipStream_t s, const Geometry& g, const PairArgs& a,
                     dim3 grid)
@@ -1149,11 +1348,10 @@ void launch_p2p_det(const Plan& pl, const Work& w, int n, hipStream_t s, const G
     const int64_t chunks = (int64_t)pl.g.ntiles + (pl.p.n_max + kWave - 1) / kWave;
     auto launch = [&](auto kernel, int nw) {
         hipLaunchKernelGGL(kernel, grid, dim3(nw * kWave), 0, s, n, (const Rec64*)w.rec, w.start, w.chunk_off, g, a,
-                           w.u_near, nullptr);
+                           w.u_near);
     };
-    if (chunks < 256) launch(k_p2p<TF, double, Lv, 12>, 12);
-    else if (chunks < 8192) launch(k_p2p<TF, double, Lv, 4>, 4);
-    else launch(k_p2p<TF, double, Lv, 2>, 2);
+    if (chunks < 1024) launch(k_p2p_one<TF, Lv, 8>, 8);
+    else launch(k_p2p_one<TF, Lv, 4>, 4);
 }
 
 template <typename TF, int Lv, bool ST>
