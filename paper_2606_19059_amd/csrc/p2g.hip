@@ -19,14 +19,13 @@ namespace {
 
 constexpr int kPatch = 8;     // lines per patch edge (8 x 8 = 64 lanes)
 constexpr int kWaves = 4;     // waves per block, all owning the block's lines
-constexpr int kSlabs = 4;     // slabs a wave spreads between two merges
+constexpr int kSlabs = 4;     // slabs of a pass, and points merged after it
 constexpr int kWindow = kWaves * kSlabs;  // most slabs whose runs are tabulated at a time
 constexpr int kBatch = 16;    // particles staged per wave and round, four lanes each
 constexpr int kMaxRuns = 320; // runs per slab (window rows x z-tile segments)
 constexpr int kTable = 1536;  // entries of the run table (a window has fewer slabs where runs are many)
-constexpr int kMergeCost = 16;  // cost of one merge of the waves' sums, in particles spread by one wave
 static_assert(kTable >= (kMaxRuns + 1) * kSlabs, "the runs of kSlabs slabs must fit the table");
-static_assert(kSlabs % kWaves == 0, "a carried point stays with its wave");
+static_assert(kSlabs == kWaves, "a merge gives each wave one point");
 
 // acc[k][c] += w_x[k] g_c for all k: lane i of every row of 16 lanes holds w_x[i], and the DPP
 // row_newbcast of v_fmac_f64 broadcasts w_x[k] from it, so that a particle's x weights take one LDS
@@ -78,33 +77,32 @@ __device__ inline int wave_scan(int v)
 }
 
 // A block of kWaves waves owns one patch and the x-segment [x0, x0 + seg).  It takes the segment in
-// windows of up to kWindow slabs (their run table in LDS) and a window in passes.  In a pass every
-// wave spreads its share of the particles into a register window of kSlabs + P - 1 points, four slabs
-// wide, without any barrier or output; then the waves' windows are merged through LDS in a fixed order,
-// the points that no later slab reaches are written, and the other P - 1 are carried to the next pass.
-// Either each wave takes four slabs of its own (one pass per window), or, where the slabs' particles
-// are so uneven (clusters) that the waves would wait for one of them, all waves share each group of
-// four slabs (a pass per group), whichever costs less for the window at hand.  The first and last
-// P - 1 points of a segment also receive from the neighbouring segments: they go, as partial sums, to
-// halo planes (head[s][k] and tail[s][k] hold the points x0 - P/2 + 1 + k and x1 - P/2 + 1 + k), and
-// k_p2g_halo_sum adds them into the grid.  Fold (M1 = 8 < P: one segment, shorter than the stencil):
-// the points are added modulo M1 instead, each wave keeping its two of the eight.
+// windows of up to kWindow slabs (their run table in LDS) and a window in passes of kSlabs slabs.  A wave
+// spreads a quarter of each slab's particles into its own register window of kSlabs + P - 1 points; after
+// a pass the waves' sums of the kSlabs points that no later slab reaches are added through LDS in a
+// fixed order and written, and the other P - 1 points stay in the waves' registers.  A point's four sums
+// run over the slabs' quarters in the order of the sort, whatever the lengths of passes and windows, so
+// that its value does not depend on them.  The first and last P - 1 points of a segment also receive from
+// the neighbouring segments: they go, as partial sums, to halo planes (head[s][k] and tail[s][k] hold
+// the points x0 - P/2 + 1 + k and x1 - P/2 + 1 + k), and k_p2g_halo_sum adds them into the grid.  Fold (M1
+// = 8 < P: one segment, shorter than the stencil): the points are added modulo M1 instead, each wave
+// keeping its two of the eight.
 //
 // What bounds it: FP64 FMAs at the patches' lane efficiency where particles are dense (c2: 3P FMAs of
-// 56 instructions per particle and patch, two waves per SIMD by the 6 (kSlabs + P - 1) accumulator
-// registers, VALU 67% busy); latency of the tables, the staging and the merge where they are sparse (a
-// block of 176 particles, P = 12: 45 thousand cycles, of which 20 thousand in the merge and the table
-// before their loads were issued side by side).  A form that merged and wrote one point per slab (four
-// waves sharing every slab, four barriers each) spent 14 thousand cycles a slab on 30 particles.  P2G
-// ms with that form and with this one: 1e6 uniform on 256^3, P = 16 3.01 -> 1.54, P = 8 (FP32) 2.17 -> 0.53;
-// 24 systems of 5e3 on 64^3 0.85 -> 0.27; 1.5e5 on 128 x 128 x 256 0.71 -> 0.30; 1e3 on 32^3 0.083 -> 0.028;
-// dense grids: c2 1.46 -> 1.37, H 0.91 -> 0.75, c4 4.38 -> 4.07, c3 8.8 -> 8.0; one loss: 2e4 in two clusters of
-// five cells 0.46 -> 0.51 (few patches hold everything, and a lone wave per SIMD, which issues an FP64
-// instruction every eight cycles, pays the staging's latency).
+// 3P + 7 instructions per particle and patch, two waves per SIMD by the 6 (kSlabs + P - 1) accumulator
+// registers); latency of the tables, the staging and the barriers where they are sparse, and the halo
+// planes' traffic (24 systems of 5e3 on 64^3: segments of 16 points, about 0.1 ms).  One pass per slab,
+// staged and merged by itself, spent 14 thousand cycles a slab on 30 particles; four slabs of its own
+// per wave and one merge per window took 0.27 ms for the 24 systems and 0.53 for 1e6 on 256^3 with P = 8, but
+// added a point's contributions in another order.  P2G ms with a pass per slab and with four: 1e6
+// uniform on 256^3, P = 16 3.01 -> 1.59, P = 8 (FP32) 2.17 -> 0.56; 24 systems of 5e3 0.85 -> 0.32; 1.5e5 on 128
+// x 128 x 256 0.71 -> 0.33; 1e3 on 32^3 0.083 -> 0.031; dense grids: c2 1.46 -> 1.34, H 0.91 -> 0.75, c4 4.38 ->
+// 4.15, c3 8.8 -> 7.9; one loss: 2e4 in two clusters of five cells 0.46 -> 0.54 (few patches hold everything, and
+// a lone wave per SIMD, which issues an FP64 instruction every eight cycles, pays the staging's latency).
 //
-// Staging: 16 particles at a time, four lanes each (two halves of the x weights, the y and the z
-// weights of the patch's lines, zero off the footprint), every lane by one recurrence of at most eight
-// steps; the next particles' records are fetched while these are spread.
+// Staging: 16 particles at a time, four lanes each (two halves of the x weights, the y weights of the
+// patch's lines, and their z weights times f, zero off the footprint), every lane by one recurrence of
+// at most eight steps; the next particles' records are fetched while these are spread, across passes.
 template <typename TG, int P, bool Fold>
 __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(const Rec64* __restrict__ rec,
                                                            const int* __restrict__ start, Geometry g,
@@ -114,18 +112,16 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
                                                            int64_t grid_stride, int64_t halo_stride)
 {
     constexpr int W = kPatch + P - 1;
-    constexpr int kPts = kSlabs + P - 1;                             // points of a wave's register window
-    constexpr int kOut = (kWindow + P - 1 + kWaves - 1) / kWaves;    // points a wave merges, at most
-    constexpr int kCarry = (P - 1 + kWaves - 1) / kWaves;            // points a wave carries
-    // staged particle: P x weights, 8 y weights, 8 z weights, f (an odd row length: the rows of
-    // consecutive particles start in different banks)
-    constexpr int kRow = P + 2 * kPatch + 3;
-    // merge rows of a wave: its points, padded with zeros to whole rounds of the waves
-    constexpr int kRounds = (kPts + kWaves - 1) / kWaves, kRows = kRounds * kWaves;
-    constexpr int kStage = kWaves * kBatch * kRow, kMerge = kWaves * kRows * kWave;
-    __shared__ double smem[kStage > kMerge ? kStage : kMerge];
+    constexpr int kPts = kSlabs + P - 1;  // points of a wave's register window
+    // staged particle: P x weights, 8 y weights, 8 z weights times each component of f (an odd row
+    // length: the rows of consecutive particles start in different banks)
+    constexpr int kRow = P + 4 * kPatch + 1;
+    constexpr int kOut = kSlabs * 3 * kWave;  // sums of a wave's finished points
+    constexpr int kMine = kBatch * kRow > kOut ? kBatch * kRow : kOut;
+    __shared__ double smem[kWaves * kMine];
     __shared__ int run_start[kTable], run_pre[kTable];
     __shared__ int slab_n[kWindow];
+    __shared__ int slab_end[kWaves][kWindow], slab_at[kWaves][kWindow];
 
     // system blockIdx.y of a batch: its cell list, grid and halo planes
     start += (int64_t)blockIdx.y * g.ncells;
@@ -153,7 +149,7 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
     const int role = lane & 3, axis = role < 2 ? 0 : role - 1;
     const double h = g.h[axis];
     const double e2 = exp(-2.0 * wa.beta);  // ratio of consecutive Gaussian recurrence factors
-    double* const row0 = smem + wid * kBatch * kRow;
+    double* const row0 = smem + wid * kMine;
     double* const mine = row0 + (lane >> 2) * kRow;
 
     const int64_t nc = g.ncells;
@@ -163,10 +159,37 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
     double* const head = halo + (int64_t)sx * hk * 3 * m23;
     double* const tail = halo + ((int64_t)gridDim.x / (npy * npz) + sx) * hk * 3 * m23;
 
-    double carry[kCarry][3];
+    double acc[kPts][3];
 #pragma unroll
-    for (int i = 0; i < kCarry; ++i) carry[i][0] = carry[i][1] = carry[i][2] = 0.0;
+    for (int k = 0; k < kPts; ++k) acc[k][0] = acc[k][1] = acc[k][2] = 0.0;
     double folded[2][3] = {};  // Fold: points wid and wid + 4 modulo 8
+
+    // The waves' first kSlabs points are added in wave order, point wid by this wave, and the windows move
+    // on by kSlabs points.
+    double v[3];
+    auto merge = [&]() {
+#pragma unroll
+        for (int k = 0; k < kSlabs; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) row0[(k * 3 + c) * kWave + lane] = acc[k][c];
+        __syncthreads();
+        double a[kWaves][3];
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) a[q][c] = smem[q * kMine + (wid * 3 + c) * kWave + lane];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            v[c] = a[0][c];
+#pragma unroll
+            for (int q = 1; q < kWaves; ++q) v[c] += a[q][c];
+        }
+#pragma unroll
+        for (int k = 0; k < kPts; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acc[k][c] = k + kSlabs < kPts ? acc[k + kSlabs < kPts ? k + kSlabs : 0][c] : 0.0;
+        __syncthreads();
+    };
 
     for (int sb = 0; sb < seg; sb += wn) {
         // run table of the window's slabs: one run per (window row, z-tile segment); entry r of slab s
@@ -217,201 +240,168 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
         }
         __syncthreads();
 
-        // one pass with four slabs per wave, or a pass per group of four slabs
-        const int groups = wn / kSlabs;
         const int in_slab = lane < wn ? slab_n[lane < wn ? lane : 0] : 0;
-        int in_group = in_slab + quad_lane<0xb1>(in_slab);
-        in_group += quad_lane<0x4e>(in_group);
-        int most = 0, shared = 0;
-#pragma unroll
-        for (int j = 0; j < kWindow / kSlabs; ++j) {
-            const int c = __builtin_amdgcn_readlane(in_group, j * kSlabs);
-            most = max(most, c);
-            shared += j < groups ? (c + kWaves - 1) / kWaves + kMergeCost : 0;
+        // this wave's quarter of the slab: particles [qa, qa + qn)
+        const int quarter = (in_slab + kWaves - 1) / kWaves;
+        const int qa = min(in_slab, wid * quarter), qn = min(in_slab, qa + quarter) - qa;
+        const int ends = wave_scan(qn);  // of the wave's quarters one after the other
+        if (lane < kWindow) {
+            slab_end[wid][lane] = ends;
+            slab_at[wid][lane] = qa + qn - ends;
         }
-        const bool split = shared < most + kMergeCost;
-        const int passes = split ? groups : 1, pn = split ? kSlabs : wn;
-        for (int pass = 0; pass < passes; ++pass) {
-            const int sa = (split ? pass : wid) * kSlabs;  // this wave's first slab
-            int G[kSlabs + 1];  // particles of its slabs before slab k
-            G[0] = 0;
-#pragma unroll
-            for (int k = 0; k < kSlabs; ++k)
-                G[k + 1] = G[k] + __builtin_amdgcn_readlane(in_slab, sa + k);
-            const int all = G[kSlabs];
-            const int share = split ? (all + kWaves - 1) / kWaves : all;
-            const int fa = split ? min(all, wid * share) : 0, fb = split ? min(all, fa + share) : all;
+        wave_lds_sync();
+        const int all = __builtin_amdgcn_readlane(ends, kWindow - 1);
 
-            double acc[kPts][3];
-#pragma unroll
-            for (int k = 0; k < kPts; ++k) acc[k][0] = acc[k][1] = acc[k][2] = 0.0;
-
-            // A particle of the wave's share, from its place in the order of the slabs' run tables
-            // (places past the last repeat it): its index, and the stencil offset of this lane's first
-            // weight (for z without the cell's offset in its tile).  The four lanes of a particle search
-            // its run together, four ways a step.
-            int idx = 0, off = 0;
-            auto locate = [&](int base) {
-                const int flat = min(base + (lane >> 2), fb - 1);
-                int k = 0, at = 0;
-#pragma unroll
-                for (int j = 1; j < kSlabs; ++j)
-                    if (flat >= G[j]) {
-                        k = j;
-                        at = G[j];
-                    }
-                const int tb = (sa + k) * (R + 1), t = flat - at;
-                int lo = 0;
-                auto step = [&](int s) {
-                    int below = run_pre[tb + min(lo + s * (role + 1), R)] <= t ? 1 : 0;
-                    below += quad_lane<0xb1>(below);  // lane ^ 1
-                    below += quad_lane<0x4e>(below);  // lane ^ 2
-                    lo += s * below;
-                };
-                if (R > 256) step(256);
-                step(64);
-                step(16);
-                step(4);
-                step(1);
-                idx = run_start[tb + lo] + (t - run_pre[tb + lo]);
-                const int iy = (lo * nzs_inv) >> 16, zs = lo - iy * nzs;
-                off = role < 2 ? role * (P / 2) : role == 2 ? P - 1 - iy : z0 + P / 2 - 1 - (zt0 + zs) * B;
+        // A particle of the wave's share, from its place in the order of the slabs' run tables
+        // (places past the last repeat it): its index, and the stencil offset of this lane's first
+        // weight (for z without the cell's offset in its tile).  The four lanes of a particle search
+        // its run together, four ways a step.
+        int idx = 0, off = 0;
+        auto locate = [&](int base) {
+            const int flat = min(base + (lane >> 2), all - 1);
+            // its slab: the number of slabs that end at or before it, four ways a step
+            int k = 0;
+            auto slab_step = [&](int s) {
+                int below = slab_end[wid][min(k + s * (role + 1), kWindow) - 1] <= flat ? 1 : 0;
+                below += quad_lane<0xb1>(below);
+                below += quad_lane<0x4e>(below);
+                k += s * below;
             };
-            struct Part {  // what this lane reads of a particle
-                double x, f0, f1, f2;
-                int c, off;
-            } p;
-            auto fetch = [&]() {
-                const Rec64& q = rec[idx];
-                p.x = q.x[axis];
-                p.c = q.c[axis];
-                p.off = off;
-                if (role == 3) {
-                    const double* f = sv ? sv + 6 * (int64_t)idx + sv_off : q.f;
-                    p.f0 = f[0];
-                    p.f1 = f[1];
-                    p.f2 = f[2];
-                }
+            slab_step(4);
+            slab_step(1);
+            const int tb = k * (R + 1), t = flat + slab_at[wid][k];
+            int lo = 0;
+            auto step = [&](int s) {
+                int below = run_pre[tb + min(lo + s * (role + 1), R)] <= t ? 1 : 0;
+                below += quad_lane<0xb1>(below);  // lane ^ 1
+                below += quad_lane<0x4e>(below);  // lane ^ 2
+                lo += s * below;
             };
-            auto stage = [&]() {
-                const double t = p.x / h - (double)p.c;
-                const int j0 = p.off - (role == 3 ? (p.c & (B - 1)) : 0);
-                const unsigned support = t == 0.0 ? P - 1 : P;  // open: no weight at distance P/2
-                double* const to = mine + (role < 2 ? role * (P / 2) : P + (role - 2) * kPatch);
-                if (!wa.kb) {
-                    // w(u + 1) = w(u) exp(-beta (2u + 1)) from u0, the distance of offset j0
-                    const double u0 = (double)(j0 - (P / 2 - 1)) - t;
-                    double w = exp(-wa.beta * u0 * u0);
-                    double r = exp(-wa.beta * (2.0 * u0 + 1.0));
-#pragma unroll
-                    for (int l = 0; l < kPatch; ++l) {
-                        if (l < P / 2 || role >= 2) to[l] = (unsigned)(j0 + l) < support ? w : 0.0;
-                        w *= r;
-                        r *= e2;
-                    }
-                } else {
-#pragma unroll
-                    for (int l = 0; l < kPatch; ++l) {
-                        const int j = j0 + l;
-                        if (l < P / 2 || role >= 2)
-                            to[l] = (unsigned)j < support ? window_weight_one<double, P>(j, t, wa) : 0.0;
-                    }
-                }
-                if (role == 3) {
-                    mine[P + 2 * kPatch] = p.f0;
-                    mine[P + 2 * kPatch + 1] = p.f1;
-                    mine[P + 2 * kPatch + 2] = p.f2;
-                }
-            };
-
-            if (fa < fb) {
-                locate(fa);
-                fetch();
+            if (R > 256) step(256);
+            step(64);
+            step(16);
+            step(4);
+            step(1);
+            idx = run_start[tb + lo] + (t - run_pre[tb + lo]);
+            const int iy = (lo * nzs_inv) >> 16, zs = lo - iy * nzs;
+            off = role < 2 ? role * (P / 2) : role == 2 ? P - 1 - iy : z0 + P / 2 - 1 - (zt0 + zs) * B;
+        };
+        struct Part {  // what this lane reads of a particle
+            double x, f0, f1, f2;
+            int c, off;
+        } p;
+        auto fetch = [&]() {
+            const Rec64& q = rec[idx];
+            p.x = q.x[axis];
+            p.c = q.c[axis];
+            p.off = off;
+            p.f0 = 1.0;
+            if (role == 3) {
+                const double* f = sv ? sv + 6 * (int64_t)idx + sv_off : q.f;
+                p.f0 = f[0];
+                p.f1 = f[1];
+                p.f2 = f[2];
             }
-            for (int base = fa; base < fb; base += kBatch) {
-                const int cnt = min(kBatch, fb - base);
-                locate(base + kBatch);
+        };
+        auto stage = [&]() {
+            const double t = p.x / h - (double)p.c;
+            const int j0 = p.off - (role == 3 ? (p.c & (B - 1)) : 0);
+            const unsigned support = t == 0.0 ? P - 1 : P;  // open: no weight at distance P/2
+            double* const to = mine + (role < 2 ? role * (P / 2) : P + (role - 2) * kPatch);
+            auto put = [&](int l, double w) {
+                if (l < P / 2 || role >= 2) to[l] = w * p.f0;  // (times 1 for the x and y weights)
+                if (role == 3) {
+                    to[kPatch + l] = w * p.f1;
+                    to[2 * kPatch + l] = w * p.f2;
+                }
+            };
+            if (!wa.kb) {
+                // w(u + 1) = w(u) exp(-beta (2u + 1)) from u0, the distance of offset j0
+                const double u0 = (double)(j0 - (P / 2 - 1)) - t;
+                double w = exp(-wa.beta * u0 * u0);
+                double r = exp(-wa.beta * (2.0 * u0 + 1.0));
+#pragma unroll
+                for (int l = 0; l < kPatch; ++l) {
+                    put(l, (unsigned)(j0 + l) < support ? w : 0.0);
+                    w *= r;
+                    r *= e2;
+                }
+            } else {
+#pragma unroll
+                for (int l = 0; l < kPatch; ++l) {
+                    const int j = j0 + l;
+                    if (l < P / 2 || role >= 2)
+                        put(l, (unsigned)j < support ? window_weight_one<double, P>(j, t, wa) : 0.0);
+                }
+            }
+        };
+
+        if (all > 0) {
+            locate(0);
+            fetch();
+        }
+        int base = 0;
+        for (int sa = 0; sa < wn; sa += kSlabs) {
+            int end[kSlabs];
+#pragma unroll
+            for (int k = 0; k < kSlabs; ++k) end[k] = __builtin_amdgcn_readlane(ends, sa + k);
+            while (base < end[kSlabs - 1]) {
+                const int cnt = min(kBatch, end[kSlabs - 1] - base);
+                locate(base + cnt);
                 stage();
                 wave_lds_sync();
                 fetch();
                 // single-value LDS loads (a paired load occupies the LDS pipeline twice as long), those of
                 // particle q + 1 ahead of the sums of particle q
                 const double* r = row0;
-                double nx = ld1(r[lane & 15]), ny = ld1(r[P + ly]), nz = ld1(r[P + kPatch + lz]);
-                double n0 = ld1(r[P + 2 * kPatch]), n1 = ld1(r[P + 2 * kPatch + 1]), n2 = ld1(r[P + 2 * kPatch + 2]);
+                double nx = ld1(r[lane & 15]), ny = ld1(r[P + ly]);
+                double n0 = ld1(r[P + kPatch + lz]), n1 = ld1(r[P + 2 * kPatch + lz]), n2 = ld1(r[P + 3 * kPatch + lz]);
                 int q = 0;
 #pragma unroll
                 for (int k = 0; k < kSlabs; ++k)
-                    for (const int qe = min(cnt, G[k + 1] - base); q < qe; ++q) {
-                        const double w = nx, wyz = ny * nz;
-                        const double g0 = wyz * n0, g1 = wyz * n1, g2 = wyz * n2;
+                    for (const int qe = min(cnt, end[k] - base); q < qe; ++q) {
+                        const double w = nx;
+                        const double g0 = ny * n0, g1 = ny * n1, g2 = ny * n2;
                         r = row0 + min(q + 1, kBatch - 1) * kRow;
                         nx = ld1(r[lane & 15]);
                         ny = ld1(r[P + ly]);
-                        nz = ld1(r[P + kPatch + lz]);
-                        n0 = ld1(r[P + 2 * kPatch]);
-                        n1 = ld1(r[P + 2 * kPatch + 1]);
-                        n2 = ld1(r[P + 2 * kPatch + 2]);
+                        n0 = ld1(r[P + kPatch + lz]);
+                        n1 = ld1(r[P + 2 * kPatch + lz]);
+                        n2 = ld1(r[P + 3 * kPatch + lz]);
                         spread<0, P>(acc + k, w, g0, g1, g2);
                     }
+                base += cnt;
                 wave_lds_sync();
             }
-
-            // merge, one component at a time: wave w sums the points p = w, w + 4, ... of the pass over the
-            // carried sums and the waves in order (all of a point's loads before its sum)
+            merge();
+            const int at = sb + sa + wid;  // point of the segment
+            if constexpr (Fold) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                __syncthreads();
-#pragma unroll
-                for (int k = 0; k < kRows; ++k)
-                    smem[(wid * kRows + k) * kWave + lane] = k < kPts ? acc[k < kPts ? k : 0][c] : 0.0;
-                __syncthreads();
-                double v[kOut];
-#pragma unroll
-                for (int i = 0; i < kOut; ++i) v[i] = i < kCarry ? carry[i < kCarry ? i : 0][c] : 0.0;
-                const double* row = smem + wid * kWave + lane;  // of wave q's point wid + 4 d: row q kRows + 4 d
-                if (split) {
-#pragma unroll
-                    for (int i = 0; i < kRounds && i < kOut; ++i)
-#pragma unroll
-                        for (int q = 0; q < kWaves; ++q) v[i] += row[(q * kRows + i * kWaves) * kWave];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < kOut; ++i)
-#pragma unroll
-                        for (int q = 0; q < kWaves; ++q)
-                            if (i - q >= 0 && i - q < kRounds) v[i] += row[(q * kRows + (i - q) * kWaves) * kWave];
+                for (int c = 0; c < 3; ++c) {
+                    if (at & kWaves) folded[1][c] += v[c];
+                    else folded[0][c] += v[c];
                 }
+            } else {
 #pragma unroll
-                for (int i = 0; i < kWindow / kWaves; ++i) {
-                    const int p = wid + kWaves * i;
-                    if (p < pn) {
-                        const int at = sb + pass * kSlabs + p;  // point of the segment
-                        if constexpr (Fold) {
-                            if (at & kWaves) folded[1][c] += v[i];
-                            else folded[0][c] += v[i];
-                        } else if (at < hk) (head + ((int64_t)at * 3 + c) * m23)[line] = v[i];
-                        else (grid + (c * nc + (int64_t)(x0 - P / 2 + 1 + at) * m23))[line] = (TG)v[i];
-                    }
-                }
-                // the points past the pass's slabs are carried
-#pragma unroll
-                for (int i = 0; i < kCarry; ++i) {
-                    double s = 0.0;
-#pragma unroll
-                    for (int j = 1; j <= kWindow / kWaves; ++j)
-                        if (i + j < kOut && pn == j * kWaves) s = v[i + j < kOut ? i + j : 0];
-                    carry[i][c] = s;
+                for (int c = 0; c < 3; ++c) {
+                    if (at < hk) (head + ((int64_t)at * 3 + c) * m23)[line] = v[c];
+                    else (grid + (c * nc + (int64_t)(x0 - P / 2 + 1 + at) * m23))[line] = (TG)v[c];
                 }
             }
-            __syncthreads();
+        }
+    }
+    // the points past the segment's slabs
+#pragma unroll
+    for (int i = 0; i * kSlabs < P - 1; ++i) {
+        merge();
+        const int p = i * kSlabs + wid;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if constexpr (Fold) folded[i & 1][c] += v[c];  // (point 8 + p)
+            else if (p < hk) (tail + ((int64_t)p * 3 + c) * m23)[line] = v[c];
         }
     }
     if constexpr (Fold) {
-#pragma unroll
-        for (int i = 0; i < kCarry; ++i)  // points 8 + wid + 4 i
-#pragma unroll
-            for (int c = 0; c < 3; ++c) folded[i & 1][c] += carry[i][c];
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -419,15 +409,6 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
                 const int x = wrapi(wid + kWaves * i - P / 2 + 1, M1);
                 (grid + (c * nc + (int64_t)x * m23))[line] = (TG)folded[i][c];
             }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kCarry; ++i) {
-            const int p = wid + kWaves * i;
-            if (p < hk) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) (tail + ((int64_t)p * 3 + c) * m23)[line] = carry[i][c];
-            }
-        }
     }
 }
 
