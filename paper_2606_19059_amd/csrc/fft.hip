@@ -46,6 +46,23 @@ __device__ inline C2<T> cadd(C2<T> a, C2<T> b) { return {a.x + b.x, a.y + b.y}; 
 template <typename T>
 __device__ inline C2<T> csub(C2<T> a, C2<T> b) { return {a.x - b.x, a.y - b.y}; }
 
+// to(idx, from(idx)) for the block's indices below tot, four loads at a time before their stores (a loop
+// of single loads waits for each of them in turn)
+template <typename From, typename To>
+__device__ inline void copy4(int tot, From from, To to)
+{
+    const int bd = blockDim.x;
+    int idx = threadIdx.x;
+    for (; idx + 3 * bd < tot; idx += 4 * bd) {
+        const auto v0 = from(idx), v1 = from(idx + bd), v2 = from(idx + 2 * bd), v3 = from(idx + 3 * bd);
+        to(idx, v0);
+        to(idx + bd, v1);
+        to(idx + 2 * bd, v2);
+        to(idx + 3 * bd, v3);
+    }
+    for (; idx < tot; idx += bd) to(idx, from(idx));
+}
+
 // Batched Stockham FFT of ncomp x ncols columns of length n stored as
 // a[(comp * n + e) * ld + c] (n and ncols powers of two, ld >= ncols the row stride).  sign = -1 forward, +1
 // inverse (unnormalised).  `b` is scratch of the same size.  Returns the buffer holding
@@ -141,11 +158,12 @@ __global__ __launch_bounds__(512) void k_fft_z(T* __restrict__ grid, int64_t nce
     const int tot = H * ncols;
 
     if (sign < 0) {
-        for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int c = idx >> lgH, e = idx & (H - 1);
-            if (line0 + c < nlines) a[e * ld + c] = data[(int64_t)(line0 + c) * H + e];
-            else a[e * ld + c] = C2<T>{0, 0};
-        }
+        copy4(
+            tot,
+            [&](int idx) {
+                return line0 + (idx >> lgH) < nlines ? data[(int64_t)line0 * H + idx] : C2<T>{0, 0};
+            },
+            [&](int idx, C2<T> v) { a[(idx & (H - 1)) * ld + (idx >> lgH)] = v; });
         __syncthreads();
         C2<T>* C = lds_fft<T>(a, b, H, ncols, ld, 1, -1, tw_half);
         for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
@@ -160,11 +178,12 @@ __global__ __launch_bounds__(512) void k_fft_z(T* __restrict__ grid, int64_t nce
             data[(int64_t)(line0 + c) * H + k] = cadd(E, cmul(tw_full[k], O));
         }
     } else {
-        for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int c = idx >> lgH, e = idx & (H - 1);
-            if (line0 + c < nlines) b[e * ld + c] = data[(int64_t)(line0 + c) * H + e];
-            else b[e * ld + c] = C2<T>{0, 0};
-        }
+        copy4(
+            tot,
+            [&](int idx) {
+                return line0 + (idx >> lgH) < nlines ? data[(int64_t)line0 * H + idx] : C2<T>{0, 0};
+            },
+            [&](int idx, C2<T> v) { b[(idx & (H - 1)) * ld + (idx >> lgH)] = v; });
         __syncthreads();
         for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
             const int c = idx >> lgH, k = idx & (H - 1);
@@ -309,10 +328,9 @@ __global__ __launch_bounds__(1024) void k_fft_zy(T* __restrict__ grid, int64_t n
     const int tot = M2 * H;
     const int half = H >> 1;
     if (sign < 0) {
-        for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int y = idx >> lgH, p = idx & (H - 1);
-            a[y * ld + p] = data[y * H + brev_bits(p, lgH)];
-        }
+        copy4(
+            tot, [&](int idx) { return data[(idx & ~(H - 1)) + brev_bits(idx & (H - 1), lgH)]; },
+            [&](int idx, C2<T> v) { a[(idx >> lgH) * ld + (idx & (H - 1))] = v; });
         __syncthreads();
         lds_fft_inplace<T, true>(a, H, lgH, M2, lgM2, ld, 1, -1, tw_half);
         // half spectrum of the real line from the length-H transform C of its even/odd pairs:
@@ -341,10 +359,9 @@ __global__ __launch_bounds__(1024) void k_fft_zy(T* __restrict__ grid, int64_t n
             data[brev_bits(p, lgM2) * H + kz] = a[p * ld + kz];
         }
     } else {
-        for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-            const int p = idx >> lgH, kz = idx & (H - 1);
-            a[p * ld + kz] = data[brev_bits(p, lgM2) * H + kz];
-        }
+        copy4(
+            tot, [&](int idx) { return data[brev_bits(idx >> lgH, lgM2) * H + (idx & (H - 1))]; },
+            [&](int idx, C2<T> v) { a[(idx >> lgH) * ld + (idx & (H - 1))] = v; });
         __syncthreads();
         lds_fft_inplace<T, true>(a, M2, lgM2, H, lgH, 1, ld, +1, tw_y);
         // the inverse of the unpacking: C_k = E_k + i O_k with E_k = X_k + conj X_{H-k},
@@ -400,10 +417,9 @@ __global__ __launch_bounds__(512) void k_fft_y(T* __restrict__ grid, int64_t nce
     const int kz0 = (bx - x * tiles_per_x) * ncols;
     const int64_t base = (int64_t)x * M2 * H + kz0;
     const int tot = M2 * ncols;
-    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-        const int e = idx >> lgnc, c = idx & (ncols - 1);
-        a[idx] = data[base + (int64_t)e * H + c];
-    }
+    copy4(
+        tot, [&](int idx) { return data[base + (int64_t)(idx >> lgnc) * H + (idx & (ncols - 1))]; },
+        [&](int idx, C2<T> v) { a[idx] = v; });
     __syncthreads();
     C2<T>* r = lds_fft<T>(a, b, M2, ncols, ncols, 1, sign, tw);
     for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
@@ -444,8 +460,8 @@ __device__ inline void cnv_point(C2<T>* r, int per, int idx, int kx, int kz, dou
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_fft_x_cnv(T* __restrict__ grid, int64_t ncells, int M1, int M2,
-                                                   int H, int ncols, int do_cnv, int do_inv,
+__global__ __launch_bounds__(256) void k_fft_x_cnv(T* __restrict__ grid, int64_t ncells, int M1, int lgM1, int M2,
+                                                   int H, int ncols, int lgnc, int do_cnv, int do_inv,
                                                    const C2<T>* __restrict__ tw, CnvArgs ca)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -461,12 +477,11 @@ __global__ __launch_bounds__(256) void k_fft_x_cnv(T* __restrict__ grid, int64_t
     const int kz0 = (bx - ky * tiles_per_y) * ncols;
     const int64_t rowstride = (int64_t)M2 * H;  // complex elements between consecutive x
     const int tot = 3 * per;
-    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-        const int comp = idx / per, rem = idx - comp * per;
-        const int e = rem / ncols, c = rem - e * ncols;
-        const C2<T>* data = reinterpret_cast<const C2<T>*>(grid + comp * ncells);
-        a[idx] = data[(int64_t)e * rowstride + (int64_t)ky * H + kz0 + c];
-    }
+    auto at = [&](int idx) -> C2<T>& {
+        const int comp = idx >> (lgM1 + lgnc), e = (idx & (per - 1)) >> lgnc, c = idx & (ncols - 1);
+        return reinterpret_cast<C2<T>*>(grid + comp * ncells)[(int64_t)e * rowstride + (int64_t)ky * H + kz0 + c];
+    };
+    copy4(tot, at, [&](int idx, C2<T> v) { a[idx] = v; });
     __syncthreads();
     C2<T>* r = lds_fft<T>(a, b, M1, ncols, ncols, 3, -1, tw);
     if (do_cnv) {
@@ -474,7 +489,7 @@ __global__ __launch_bounds__(256) void k_fft_x_cnv(T* __restrict__ grid, int64_t
         const double k1 = ca.twopi_over_L[1] * kys;
         const double e1 = ca.E1[ky];
         for (int idx = threadIdx.x; idx < per; idx += blockDim.x) {
-            const int kx = idx / ncols, c = idx - kx * ncols;
+            const int kx = idx >> lgnc, c = idx & (ncols - 1);
             const int kz = kz0 + c;
             const int kxs = (kx < M1 / 2) ? kx : kx - M1;
             const double k0 = ca.twopi_over_L[0] * kxs;
@@ -483,12 +498,7 @@ __global__ __launch_bounds__(256) void k_fft_x_cnv(T* __restrict__ grid, int64_t
         __syncthreads();
     }
     if (do_inv) r = lds_fft<T>(r, (r == a) ? b : a, M1, ncols, ncols, 3, +1, tw);
-    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-        const int comp = idx / per, rem = idx - comp * per;
-        const int e = rem / ncols, c = rem - e * ncols;
-        C2<T>* data = reinterpret_cast<C2<T>*>(grid + comp * ncells);
-        data[(int64_t)e * rowstride + (int64_t)ky * H + kz0 + c] = r[idx];
-    }
+    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) at(idx) = r[idx];
 }
 
 // ---- pass 3 for combined single and double layer sources ----
@@ -520,12 +530,11 @@ __global__ __launch_bounds__(512) void k_fft_x_cnv_ip(T* __restrict__ grid, int6
     const int kz0 = (bx - ky * tiles_per_y) * ncols;
     const int64_t rowstride = (int64_t)M2 * H;  // complex elements between consecutive x
     const int tot = 3 * per;
-    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-        const int comp = idx / per, rem = idx - comp * per;
-        const int e = rem >> lgnc, c = rem & (ncols - 1);
-        const C2<T>* data = reinterpret_cast<const C2<T>*>(grid + comp * ncells);
-        a[idx] = data[(int64_t)e * rowstride + (int64_t)ky * H + kz0 + c];
-    }
+    auto at = [&](int idx) -> C2<T>& {
+        const int comp = idx >> (lgM1 + lgnc), e = (idx & (per - 1)) >> lgnc, c = idx & (ncols - 1);
+        return reinterpret_cast<C2<T>*>(grid + comp * ncells)[(int64_t)e * rowstride + (int64_t)ky * H + kz0 + c];
+    };
+    copy4(tot, at, [&](int idx, C2<T> v) { a[idx] = v; });
     __syncthreads();
     lds_fft_inplace<T, false>(a, M1, lgM1, ncols, lgnc, 1, ncols, -1, tw, 3, per);
     const int kys = (ky < M2 / 2) ? ky : ky - M2;
@@ -539,17 +548,12 @@ __global__ __launch_bounds__(512) void k_fft_x_cnv_ip(T* __restrict__ grid, int6
     }
     __syncthreads();
     lds_fft_inplace<T, true>(a, M1, lgM1, ncols, lgnc, 1, ncols, +1, tw, 3, per);
-    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-        const int comp = idx / per, rem = idx - comp * per;
-        const int e = rem >> lgnc, c = rem & (ncols - 1);
-        C2<T>* data = reinterpret_cast<C2<T>*>(grid + comp * ncells);
-        data[(int64_t)e * rowstride + (int64_t)ky * H + kz0 + c] = a[idx];
-    }
+    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) at(idx) = a[idx];
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_cnv_st_x(T* __restrict__ grid, int64_t ncells, int M1, int M2, int H,
-                                                  int ncols, const C2<T>* __restrict__ tw, CnvArgs ca)
+__global__ __launch_bounds__(256) void k_cnv_st_x(T* __restrict__ grid, int64_t ncells, int M1, int lgM1, int M2, int H,
+                                                  int ncols, int lgnc, const C2<T>* __restrict__ tw, CnvArgs ca)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int per = M1 * ncols;
@@ -566,7 +570,7 @@ __global__ __launch_bounds__(256) void k_cnv_st_x(T* __restrict__ grid, int64_t 
     const double k1 = ca.twopi_over_L[1] * kys;
     const double e1 = ca.E1[ky];
     for (int idx = threadIdx.x; idx < per; idx += blockDim.x) {
-        const int kx = idx / ncols, c = idx - kx * ncols;
+        const int kx = idx >> lgnc, c = idx & (ncols - 1);
         const int kz = kz0 + c;
         const int kxs = (kx < M1 / 2) ? kx : kx - M1;
         const double k0 = ca.twopi_over_L[0] * kxs;
@@ -607,10 +611,8 @@ __global__ __launch_bounds__(256) void k_cnv_st_x(T* __restrict__ grid, int64_t 
     C2<T>* r = lds_fft<T>(a, b, M1, ncols, ncols, 3, +1, tw);
     const int tot = 3 * per;
     for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-        const int comp = idx / per, rem = idx - comp * per;
-        const int e = rem / ncols, c = rem - e * ncols;
-        C2<T>* data = reinterpret_cast<C2<T>*>(grid + comp * ncells);
-        data[(int64_t)e * rowstride + (int64_t)ky * H + kz0 + c] = r[idx];
+        const int comp = idx >> (lgM1 + lgnc), e = (idx & (per - 1)) >> lgnc, c = idx & (ncols - 1);
+        reinterpret_cast<C2<T>*>(grid + comp * ncells)[(int64_t)e * rowstride + (int64_t)ky * H + kz0 + c] = r[idx];
     }
 }
 
@@ -645,7 +647,7 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
     const int budget = (sizeof(T) == 8) ? 1024 : 2048;  // complex elements per buffer
     // threads per block of the z and y passes: two per column element pair keep 32 waves on a CU (four
     // blocks by their LDS), which wait on memory and barriers (FFT+CNV+IFFT at 256 threads and at 512: 256^3
-    // FP64 1.36 and 1.21 ms, FP32 0.71 and 0.57)
+    // FP64 1.36 and 1.21 ms, FP32 0.71 and 0.57; four loads at a time then 1.11 -> 1.09 and 0.61 -> 0.54)
     constexpr int kThreadsZY = 512;
 
     // passes 1+2 fused when a plane fits in one workgroup's LDS
@@ -676,8 +678,13 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
     size_t shy = 2 * (size_t)M2 * ncy * sizeof(C2<T>);
     dim3 gy(M1 * (H / ncy), ncomp_in);
     dim3 gzy(M1, ncomp_in);
+    // threads per block of the fused pass: 256 where eight small planes fit a CU and there are that many
+    // (their waits overlap; 24 systems of 64^3 in FP32, both passes: 0.141 -> 0.097 ms), else 1024 (64 x 64 x 128
+    // FP32 alone 0.039 ms with 1024, 0.045 with 256)
+    const bool many = 8 * shzy <= (size_t)lds_per_block() && (int64_t)M1 * ncomp_in >= 8 * 256;
+    const dim3 tzy(many ? 256 : 1024);
     if (fused) {
-        hipLaunchKernelGGL((k_fft_zy<T>), gzy, dim3(1024), shzy, s, grid, nc, M2, lgM2, H, lgH, -1, twh, twf, tw1);
+        hipLaunchKernelGGL((k_fft_zy<T>), gzy, tzy, shzy, s, grid, nc, M2, lgM2, H, lgH, -1, twh, twf, tw1);
     } else {
         hipLaunchKernelGGL((k_fft_z<T>), gz, dim3(kThreadsZY), shz, s, grid, nc, nlines, H, lgH, ncz, -1, twh, twf);
         hipLaunchKernelGGL((k_fft_y<T>), gy, dim3(kThreadsZY), shy, s, grid, nc, M2, H, ncy, lgncy, -1, tw1);
@@ -689,6 +696,9 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
     int ncx = pow2_floor(max(1, budget / (3 * M1)));
     if (ncx > H) ncx = H;
     size_t shx = 2 * (size_t)3 * M1 * ncx * sizeof(C2<T>);
+    int lgM1 = 0, lgncx = 0;
+    while ((1 << lgM1) < M1) ++lgM1;
+    while ((1 << lgncx) < ncx) ++lgncx;
     CnvArgs ca;
     for (int d = 0; d < 3; ++d) ca.twopi_over_L[d] = 2.0 * M_PI / g.L[d];
     ca.inv4xi2 = 1.0 / (4.0 * pl.xi * pl.xi);
@@ -701,16 +711,15 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
         // inverse x transform
         for (int grp = 0; grp < 3; ++grp)
             hipLaunchKernelGGL((k_fft_x_cnv<T>), dim3(M2 * (H / ncx)), dim3(256), shx, s,
-                               grid + (int64_t)3 * grp * nc, nc, M1, M2, H, ncx, 0, 0, tw0, ca);
+                               grid + (int64_t)3 * grp * nc, nc, M1, lgM1, M2, H, ncx, lgncx, 0, 0, tw0, ca);
         if (cnv && inverse_too)
-            hipLaunchKernelGGL((k_cnv_st_x<T>), dim3(M2 * (H / ncx)), dim3(256), shx, s, grid, nc, M1, M2, H, ncx,
-                               tw0, ca);
+            hipLaunchKernelGGL((k_cnv_st_x<T>), dim3(M2 * (H / ncx)), dim3(256), shx, s, grid, nc, M1, lgM1, M2, H,
+                               ncx, lgncx, tw0, ca);
     } else if (cnv && inverse_too && M1 >= 4) {
         // one LDS buffer: twice the columns per block; from M1 = 256 on four times, with twice the threads
         // (64-byte runs at 256^3 FP64 instead of 32: the pass 0.36 -> 0.30 ms)
         const int wide = M1 >= 256 ? 2 : 1;
-        int lgM1 = 0, lgnc = 0;
-        while ((1 << lgM1) < M1) ++lgM1;
+        int lgnc = 0;
         int nci = pow2_floor(max(1, wide * 2 * budget / (3 * M1)));
         if (nci > H) nci = H;
         while ((1 << lgnc) < nci) ++lgnc;
@@ -718,11 +727,11 @@ hipError_t launch_fgc_t(const Plan& pl, const Work& w, hipStream_t s, bool inver
         hipLaunchKernelGGL((k_fft_x_cnv_ip<T>), dim3(M2 * (H / nci), nsys), dim3(256 * wide), shi, s, grid, nc, M1, lgM1,
                            M2, H, nci, lgnc, tw0, ca);
     } else {
-        hipLaunchKernelGGL((k_fft_x_cnv<T>), dim3(M2 * (H / ncx), nsys), dim3(256), shx, s, grid, nc, M1, M2, H,
-                           ncx, cnv ? 1 : 0, inverse_too ? 1 : 0, tw0, ca);
+        hipLaunchKernelGGL((k_fft_x_cnv<T>), dim3(M2 * (H / ncx), nsys), dim3(256), shx, s, grid, nc, M1, lgM1, M2, H,
+                           ncx, lgncx, cnv ? 1 : 0, inverse_too ? 1 : 0, tw0, ca);
     }
     if (inverse_too && fused) {
-        hipLaunchKernelGGL((k_fft_zy<T>), gzy, dim3(1024), shzy, s, grid, nc, M2, lgM2, H, lgH, +1, twh, twf, tw1);
+        hipLaunchKernelGGL((k_fft_zy<T>), gzy, tzy, shzy, s, grid, nc, M2, lgM2, H, lgH, +1, twh, twf, tw1);
     } else if (inverse_too) {
         hipLaunchKernelGGL((k_fft_y<T>), gy, dim3(kThreadsZY), shy, s, grid, nc, M2, H, ncy, lgncy, +1, tw1);
         hipLaunchKernelGGL((k_fft_z<T>), gz, dim3(kThreadsZY), shz, s, grid, nc, nlines, H, lgH, ncz, +1, twh, twf);

@@ -29,3 +29,22 @@ def test_fft_passes_match_oracle(grid, precision, tol, P, m):
     pl = E.Plan(box, tol, xi=xi, r_c=0.06, grid=grid, P=P, window_shape=m, n_max=n, precision=precision)
     uf = pl.eval_parts(d(x), d(f))[1].cpu().numpy()
     assert np.max(np.abs(uf - ref)) < bound * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-11), ("fp32", 5e-7)])
+def test_many_small_planes_equal_systems_alone(precision, tol):
+    """A batch with enough small planes for the fused pass's narrow blocks: its grids are those of the
+    systems alone (wide blocks), bit for bit."""
+    import paper_2606_19059_amd as E
+
+    box, grid, sizes = (0.5, 0.25, 0.25), (32, 16, 16), [60 + k for k in range(24)]
+    x, f = W.particles(sum(sizes), box, seed=41)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    pl = E.Plan(box, tol, xi=0.2 * 64, r_c=0.1, grid=grid, P=6, window_shape=4.1, n_max=100, precision=precision,
+                deterministic=True)
+    u = pl.eval_batch(d(x), d(f), sizes).cpu()
+    at = 0
+    for n in sizes:
+        one = pl.eval(d(x[:, at:at + n]), d(f[:, at:at + n])).cpu()
+        assert torch.equal(u[:, at:at + n], one)
+        at += n
