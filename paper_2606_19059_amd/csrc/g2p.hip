@@ -21,13 +21,14 @@ namespace ewald {
 
 namespace {
 
-// Window weights and stencil anchors of NG consecutive sorted targets sg, sg + 1, ... (those
-// at or past s1 repeat target s1 - 1), by `lanes` threads of which this is number `lane`: sw[q][d][1 + j]
+// Window weights and stencil anchors of NG consecutive targets sg, sg + 1, ... of the order (nullptr: the
+// sorted one; those at or past s1 repeat target s1 - 1), by `lanes` threads of which this is number `lane`: sw[q][d][1 + j]
 // is the weight of stencil offset j along axis d of target q, between two zeros (sw[q][d][0] and
 // sw[q][d][P + 1], which serve all offsets off the stencil), anc[q][d] the (unwrapped) first
 // stencil cell.
 template <typename T, int P, int NG>
-__device__ inline void stage_weights(const typename RecView<T>::Rec* __restrict__ rec, const Geometry& g,
+__device__ inline void stage_weights(const typename RecView<T>::Rec* __restrict__ rec,
+                                     const int* __restrict__ order, const Geometry& g,
                                      const WinArgs<T>& wa, int sg, int s1, T (*sw)[3][P + 2], int (*anc)[3],
                                      int lane, int lanes)
 {
@@ -40,7 +41,8 @@ __device__ inline void stage_weights(const typename RecView<T>::Rec* __restrict_
             const int qq = k / 6, d = (k >> 1) % 3, up = k & 1;
             int c[3];
             T t[3], f[3];
-            RecView<T>::load(rec[min(sg + qq, s1 - 1)], g, c, t, f);
+            const int s = min(sg + qq, s1 - 1);
+            RecView<T>::load(rec[order ? order[s] : s], g, c, t, f);
             const T td = (d == 0) ? t[0] : (d == 1 ? t[1] : t[2]);
             const T sgn = up ? (T)1 : (T)-1;
             const T u0 = (T)up - td;  // distance of offset P/2 - 1 + up
@@ -61,7 +63,8 @@ __device__ inline void stage_weights(const typename RecView<T>::Rec* __restrict_
             const int qq = k / (3 * P), d = (k / P) % 3, jj = k % P;
             int c[3];
             T t[3], f[3];
-            RecView<T>::load(rec[min(sg + qq, s1 - 1)], g, c, t, f);
+            const int s = min(sg + qq, s1 - 1);
+            RecView<T>::load(rec[order ? order[s] : s], g, c, t, f);
             const T td = (d == 0) ? t[0] : (d == 1 ? t[1] : t[2]);
             sw[qq][d][1 + jj] = window_weight_one<T, P>(jj, td, wa);
             if (jj == 0) {
@@ -152,7 +155,8 @@ constexpr int g2p_waves()
 
 template <typename T, typename TG, int P, int NB, bool Split>
 __global__ __launch_bounds__(kMWaves * 64) __attribute__((amdgpu_waves_per_eu(g2p_waves<T, TG, P, NB>())))
-void k_g2p_mfma(const typename RecView<T>::Rec* __restrict__ rec, const int* __restrict__ start,
+void k_g2p_mfma(const typename RecView<T>::Rec* __restrict__ rec, const int* __restrict__ order,
+                const int* __restrict__ start,
                 const int* __restrict__ chunk_off, const TG* __restrict__ grid, Geometry g, WinArgs<T> wa,
                 double self_coef, const double* __restrict__ u_near, const double* __restrict__ f_in,
                 double* __restrict__ u, double* __restrict__ u_near_out, double* __restrict__ u_far_out, int n)
@@ -189,10 +193,10 @@ void k_g2p_mfma(const typename RecView<T>::Rec* __restrict__ rec, const int* __r
     T (*swq)[3][P + 2] = sw[set];
     int (*ancq)[3] = anc[set];
     if constexpr (Split) {
-        stage_weights<T, P, kMG>(rec, g, wa, sg, s1, swq, ancq, (int)threadIdx.x, kMWaves * kWave);
+        stage_weights<T, P, kMG>(rec, order, g, wa, sg, s1, swq, ancq, (int)threadIdx.x, kMWaves * kWave);
         __syncthreads();
     } else {
-        stage_weights<T, P, kMG>(rec, g, wa, sg, s1, swq, ancq, lane, kWave);
+        stage_weights<T, P, kMG>(rec, order, g, wa, sg, s1, swq, ancq, lane, kWave);
         wave_lds_sync();
     }
 
@@ -337,7 +341,61 @@ void k_g2p_mfma(const typename RecView<T>::Rec* __restrict__ rec, const int* __r
                 v2 = p[r][2];
             }
         }
-        if (s < s1) write_target(s, rec[s].orig, n, v0, v1, v2, self_coef, u_near, f_in, u, u_near_out, u_far_out);
+        if (s < s1) {
+            const int at = order ? order[s] : s;
+            write_target(at, rec[at].orig, n, v0, v1, v2, self_coef, u_near, f_in, u, u_near_out, u_far_out);
+        }
+    }
+}
+
+// The order in which G2P takes a tile's targets, for FP64 grids: strips of a quarter of the tile's x-cells,
+// in each by y (every other strip backwards), then x, so that 16 consecutive targets cover a square of the
+// (x, y) plane.  Their box, whose U_x U_y points are the contraction's length, is smaller than in the
+// sort's Morton order of the (x, y) columns: 379 points on average where a tile of 16^3 cells holds 244,
+// against 435 (G2P, with this kernel: 1e6 on 256^3 2.01 -> 1.88 ms, 1.5e5 on 128 x 128 x 256 0.38 -> 0.35, c2
+// 1.11 -> 1.06, c4 3.46 -> 3.34).  FP32 grids keep the sort's order, and with it the order of their FP32 sums.
+constexpr int kOrderThreads = 512;
+__global__ __launch_bounds__(kOrderThreads) void k_target_order(const Rec64* __restrict__ rec,
+                                                                const int* __restrict__ start, Geometry g,
+                                                                int* __restrict__ order)
+{
+    __shared__ int first[256], place[256], wave_n[kOrderThreads / kWave];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int B = g.B, lB = g.log2B, per = 1 << (3 * lB);
+    const int* lines = start + (int64_t)blockIdx.x * per;  // of this tile's cells
+    const int a = lines[0], b = lines[per];
+    if (a >= b) return;
+    if (b - a > 8 * B * B) {  // dense: 16 targets fill two columns or fewer in any order
+        for (int i = a + tid; i < b; i += kOrderThreads) order[i] = i;
+        return;
+    }
+    const int w = max(1, B >> 2), lw = max(0, lB - 2);
+    // line (x, y) of place tid: tid = (strip, y, x in the strip)
+    const int strip = tid >> (lw + lB), yy = (tid >> lw) & (B - 1);
+    const int x = strip * w + (tid & (w - 1)), y = (strip & 1) ? B - 1 - yy : yy;
+    const int line = morton2(x, y);  // of the sort's order
+    int n = 0, at = 0;
+    if (tid < B * B) {
+        at = lines[line * B];
+        n = lines[line * B + B] - at;
+    }
+    int inc = n;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int v = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += v;
+    }
+    if (lane == kWave - 1) wave_n[wid] = inc;
+    __syncthreads();
+    for (int k = 0; k < wid; ++k) inc += wave_n[k];
+    if (tid < B * B) {
+        first[line] = at;
+        place[line] = a + inc - n;
+    }
+    __syncthreads();
+    for (int i = a + tid; i < b; i += kOrderThreads) {
+        const int l = morton2(rec[i].c[0] & (B - 1), rec[i].c[1] & (B - 1));
+        order[place[l] + i - first[l]] = i;
     }
 }
 
@@ -350,12 +408,20 @@ hipError_t launch_g2p_mfma(const Plan& pl, const Work& w, int n, const double* f
     // an upper bound on the chunks (each tile has at most one short chunk); blocks past the
     // actual count exit at once
     const int64_t blocks = (int64_t)g.ntiles * g.nsys + (n + kWave - 1) / kWave;
+    int* order = nullptr;
     auto launch = [&](auto kernel, int64_t nb) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kMWaves * kWave), 0, s,
-                           (const typename RecView<T>::Rec*)w.rec, w.start, w.chunk_off, (const TG*)w.grid, g,
+                           (const typename RecView<T>::Rec*)w.rec, order, w.start, w.chunk_off, (const TG*)w.grid, g,
                            make_win_args<T>(pl), pl.info.self_coef, w.u_near, f, u, un, uf, n);
     };
     if constexpr (std::is_same<TG, double>::value) {
+        // the targets' order (see k_target_order) pays for its launch from some 3e4 particles on (by the plan
+        // alone; ms without / with: 4e3 0.034 / 0.036, 1.6e4 0.052 / 0.051, 5e4 0.160 / 0.149)
+        if (pl.p.n_max >= 32768) {
+            order = w.perm;  // not used after the sort
+            hipLaunchKernelGGL(k_target_order, dim3((unsigned)(g.ntiles * g.nsys)), dim3(kOrderThreads), 0, s,
+                               (const Rec64*)w.rec, w.start, g, order);
+        }
         // by the plan alone, so that a system's result does not depend on what is evaluated with it:
         // plans of up to 131072 particles (ms of the two forms: 1e3 0.044 / 0.017, 1.6e4 at 1e-8 0.076 / 0.050,
         // 6.6e4 0.198 / 0.173; 2.6e5 on 128^3 0.404 / 0.450, c2 1.11 / 1.29, c4 3.48 / 4.01), and sparse

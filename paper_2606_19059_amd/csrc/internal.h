@@ -140,7 +140,7 @@ struct Plan {
 // Device pointers carved out of the caller's workspace.
 struct Work {
     int* key;        // [n]   sort key of each input particle; after the sort, its sorted position
-    int* perm;       // [n]   original indices, cell by cell
+    int* perm;       // [n]   original indices, cell by cell; after the sort, the order of G2P's targets
     int* count;      // [ncells]   histogram
     int* start;      // [ncells+1] exclusive scan of count
     int* chunk_off;  // [ntiles+1] P2P wave work-list offsets

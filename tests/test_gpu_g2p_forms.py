@@ -33,3 +33,20 @@ def test_g2p_forms_match_oracle(grid, n_wave, n_split, tile, precision, tol, P, 
         assert n_max != n_wave or pl.info["tile"] == tile
         uf = pl.eval_parts(d(x), d(f))[1].cpu().numpy()
         assert np.max(np.abs(uf - ref)) < bound * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("grid,tile", [((16, 16, 16), 2), ((32, 32, 32), 4), ((64, 64, 32), 8), ((128, 128, 64), 16)])
+def test_target_order_of_dense_tiles_matches_oracle(grid, tile):
+    """Tiles on both sides of the density from which G2P keeps the sort's order (8 targets per column of a
+    tile): each target still gets its own far field."""
+    import paper_2606_19059_amd as E
+
+    box = tuple(g / 64.0 for g in grid)
+    n, xi = 700 + 9 * tile * tile, 0.2 * 64
+    x, f = W.particles(n, box, seed=43)
+    x[:, 700:] = (tile + tile * (x[:, 700:] / np.array(box)[:, None])) / 64.0  # one tile's cells
+    ref = S.far_field(x, f, box, grid, xi, 6, 4.1)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    pl = E.Plan(box, 1e-11, xi=xi, r_c=0.2, grid=grid, P=6, window_shape=4.1, n_max=140_000)
+    uf = pl.eval_parts(d(x), d(f))[1].cpu().numpy()
+    assert np.max(np.abs(uf - ref)) < 1e-12 * np.max(np.abs(ref))
