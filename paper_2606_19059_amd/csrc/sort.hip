@@ -85,7 +85,7 @@ __global__ void k_scatter(int n, const int* __restrict__ key, const int* __restr
 constexpr int kCellSerial = 16;
 constexpr int kCellMid = 256;
 constexpr int kBigThreads = 256;
-constexpr int kBigRun = 8192;  // ints sorted in LDS at once (32 KB)
+constexpr int kBigRun = 4096;  // ints sorted in LDS at once (two buffers of 16 KB)
 
 __host__ __device__ inline int64_t mid_list_cap(int64_t n) { return n / (kCellSerial + 1) + 1; }
 __host__ __device__ inline int64_t big_list_cap(int64_t n) { return n / (kCellMid + 1) + 1; }
@@ -109,7 +109,7 @@ __device__ void sort_mid_cells(const int* __restrict__ start, int* __restrict__ 
         for (int k = 0; k < kPer; ++k) {
             const int i = lane + k * kWave;
             v[k] = i < m ? perm[a + i] : 0;
-            if (i < m) s[i] = v[k];
+            s[i] = i < m ? v[k] : INT_MAX;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -117,10 +117,12 @@ __device__ void sort_mid_cells(const int* __restrict__ start, int* __restrict__ 
         int rank[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; ++k) rank[k] = 0;
-        for (int t = 0; t < m; ++t) {
-            const int o = s[t];
+        for (int t = 0; t < m; t += 8) {
+            const int4 o = *reinterpret_cast<const int4*>(s + t), p = *reinterpret_cast<const int4*>(s + t + 4);
 #pragma unroll
-            for (int k = 0; k < kPer; ++k) rank[k] += (o < v[k]) ? 1 : 0;
+            for (int k = 0; k < kPer; ++k)
+                rank[k] += (o.x < v[k]) + (o.y < v[k]) + (o.z < v[k]) + (o.w < v[k]) + (p.x < v[k]) + (p.y < v[k]) +
+                           (p.z < v[k]) + (p.w < v[k]);
         }
 #pragma unroll
         for (int k = 0; k < kPer; ++k)
@@ -144,8 +146,42 @@ __device__ inline int count_below(const int* __restrict__ a, int len, int v)
     return lo;
 }
 
-// One block per listed cell (size > kCellMid): runs of kBigRun indices are sorted in LDS
-// (bitonic network, padded to a power of two), then merged pairwise, each index placed at
+// One pass of a merge sort in LDS: src[0, len) holds ascending runs of w (distinct values), dst gets runs
+// of 2 w.  Each value goes to its offset in its own run plus the number of smaller values in the other,
+// found by halving steps; a thread searches for eight values at a time, whose reads overlap.
+__device__ inline void merge_runs(const int* src, int* dst, int len, int w)
+{
+    constexpr int kSide = 8;
+    for (int i0 = threadIdx.x; i0 < len; i0 += kSide * kBigThreads) {
+        int val[kSide], at[kSide], other[kSide], n[kSide], pos[kSide];
+#pragma unroll
+        for (int q = 0; q < kSide; ++q) {
+            const int i = min(i0 + q * kBigThreads, len - 1);
+            const int lo = i & ~(2 * w - 1), mid = min(lo + w, len), hi = min(lo + 2 * w, len);
+            val[q] = src[i];
+            at[q] = i < mid ? i : lo + i - mid;  // plus pos: its place
+            other[q] = i < mid ? mid : lo;
+            n[q] = i < mid ? hi - mid : mid - lo;
+            pos[q] = 0;
+        }
+        for (int step = w; step >= 1; step >>= 1) {
+#pragma unroll
+            for (int q = 0; q < kSide; ++q) {
+                const int to = pos[q] + step;
+                const int o = src[min(other[q] + to, len) - 1];
+                pos[q] = (to <= n[q]) & (o < val[q]) ? to : pos[q];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kSide; ++q)
+            if (i0 + q * kBigThreads < len) dst[at[q] + pos[q]] = val[q];
+    }
+    __syncthreads();
+}
+
+// One block per listed cell (size > kCellMid): runs of kBigRun indices are sorted in LDS (runs of 64
+// by counting, one per wave and turn, then merged pairwise: 2e4 particles in two clusters, cells of up to
+// 1.8e3, 64 us by a bitonic network and 23 us so), then merged pairwise, each index placed at
 // its rank in the merged run (its offset in its own run plus the count of smaller indices
 // in the other, by binary search), ping-ponging between the cell's range of `perm` and
 // the same range of `scratch`.
@@ -154,31 +190,32 @@ __device__ void sort_big_cells(const int* __restrict__ start, int* __restrict__ 
 {
     const int nbig = lists[1];
     const int tid = threadIdx.x;
-    for (int q = block; q < nbig; q += blocks) {
+    for (int q = blocks - 1 - block; q < nbig; q += blocks) {  // from the last block on: the first have the others
         const int c = lists[2 + mid_cap + q];
         const int a = start[c], m = start[c + 1] - a;
         int* v = perm + a;
         for (int r0 = 0; r0 < m; r0 += kBigRun) {
             const int len = min(kBigRun, m - r0);
-            int p2 = 1;
-            while (p2 < len) p2 <<= 1;
-            for (int i = tid; i < p2; i += kBigThreads) s[i] = i < len ? v[r0 + i] : INT_MAX;
+            for (int i = tid; i < len; i += kBigThreads) s[i] = v[r0 + i];
             __syncthreads();
-            for (int k = 2; k <= p2; k <<= 1)
-                for (int j = k >> 1; j > 0; j >>= 1) {
-                    for (int i = tid; i < p2; i += kBigThreads) {
-                        const int l = i ^ j;
-                        if (l > i) {
-                            const int x = s[i], y = s[l];
-                            if ((x > y) == ((i & k) == 0)) {
-                                s[i] = y;
-                                s[l] = x;
-                            }
-                        }
-                    }
-                    __syncthreads();
-                }
-            for (int i = tid; i < len; i += kBigThreads) v[r0 + i] = s[i];
+            const int lane = tid & (kWave - 1);
+            for (int b = tid - lane; b < len; b += kBigThreads) {
+                const int val = b + lane < len ? s[b + lane] : INT_MAX;
+                int below = 0;
+#pragma unroll
+                for (int k = 0; k < kWave; ++k) below += __builtin_amdgcn_readlane(val, k) < val ? 1 : 0;
+                wave_lds_sync();
+                if (b + lane < len) s[b + below] = val;
+            }
+            __syncthreads();
+            int *from = s, *to = s + kBigRun;
+            for (int w = kWave; w < len; w *= 2) {
+                merge_runs(from, to, len, w);
+                int* t = from;
+                from = to;
+                to = t;
+            }
+            for (int i = tid; i < len; i += kBigThreads) v[r0 + i] = from[i];
             __syncthreads();
         }
         int* src = v;
@@ -381,7 +418,7 @@ __global__ void __launch_bounds__(kBigThreads) k_order_cells(const int* __restri
                                                              int* __restrict__ scratch, const int* __restrict__ lists,
                                                              int64_t mid_cap, Geometry g, int* __restrict__ chunk_off)
 {
-    __shared__ int s[kBigRun];
+    __shared__ __align__(16) int s[2 * kBigRun];
     static_assert(kBigRun >= kBigThreads / kWave * kCellMid, "one LDS row per wave");
     if (blockIdx.x == 0) {
         if (!chunk_off) return;
