@@ -763,14 +763,17 @@ int run(ewald_plan_t plan, int64_t n64, const double* x, const double* f, void* 
         }
         mark(2);
     }
-    if ((e = launch_p2g(*pl, w, n, s, st, nsys)) != hipSuccess) return hip_fail(e, "P2G");
+    // the points that two of P2G's segments share: added by the FFT's first pass, or apart where the grid
+    // itself is asked for and with stresslet sources
+    const bool open = what != Out::Spread && !st;
+    if ((e = launch_p2g(*pl, w, n, s, st, nsys, open)) != hipSuccess) return hip_fail(e, "P2G");
     mark(3);
     const size_t gbytes = (size_t)pl->info.grid_bytes;
     if (what == Out::Spread) {
         e = hipMemcpyAsync(o1, w.grid, gbytes, hipMemcpyDeviceToDevice, s);
         return e == hipSuccess ? EWALD_OK : hip_fail(e, "grid copy");
     }
-    if ((e = launch_fgc(*pl, w, s, true, true, st, nsys)) != hipSuccess) return hip_fail(e, "FFT/CNV/IFFT");
+    if ((e = launch_fgc(*pl, w, s, true, true, st, nsys, open)) != hipSuccess) return hip_fail(e, "FFT/CNV/IFFT");
     mark(4);
     if (what == Out::FarGrid) {
         e = hipMemcpyAsync(o1, w.grid, gbytes, hipMemcpyDeviceToDevice, s);

@@ -173,9 +173,11 @@ hipError_t launch_p2p(const Plan& pl, const Work& w, int n, hipStream_t s, bool 
 // exact number of ordered pairs (i != j, all images) with 0 < |r| < r_c, written to *count
 hipError_t launch_count_pairs(const Plan& pl, const Work& w, int n, unsigned long long* count, hipStream_t s,
                               int nsys = 1);
-hipError_t launch_p2g(const Plan& pl, const Work& w, int n, hipStream_t s, bool st, int nsys = 1);
+// `open` (without stresslet sources): the points next to the segment boundaries stay apart in the halo
+// planes, for a launch_fgc with `open` (which reads them from there) to follow
+hipError_t launch_p2g(const Plan& pl, const Work& w, int n, hipStream_t s, bool st, int nsys = 1, bool open = false);
 hipError_t launch_fgc(const Plan& pl, const Work& w, hipStream_t s, bool inverse_too, bool cnv, bool st,
-                      int nsys = 1);
+                      int nsys = 1, bool open = false);
 hipError_t launch_g2p(const Plan& pl, const Work& w, int n, const double* f, double* u,
                       double* u_near_out, double* u_far_out, const Batch& b, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int64_t count, int value, hipStream_t s);

@@ -84,7 +84,8 @@ __device__ inline int wave_scan(int v)
 // run over the slabs' quarters in the order of the sort, whatever the lengths of passes and windows, so
 // that its value does not depend on them.  The first and last P - 1 points of a segment also receive from
 // the neighbouring segments: they go, as partial sums, to halo planes (head[s][k] and tail[s][k] hold
-// the points x0 - P/2 + 1 + k and x1 - P/2 + 1 + k), and k_p2g_halo_sum adds them into the grid.  Fold (M1
+// the points x0 - P/2 + 1 + k and x1 - P/2 + 1 + k), and the first FFT pass adds them as it reads (k_p2g_halo_sum into the grid, with stresslet sources or
+// where the grid itself is asked for).  Fold (M1
 // = 8 < P: one segment, shorter than the stencil): the points are added modulo M1 instead, each wave
 // keeping its two of the eight.
 //
@@ -438,7 +439,7 @@ __global__ __launch_bounds__(256) void k_p2g_halo_sum(const double* __restrict__
 
 
 template <typename TG, int P>
-hipError_t launch_p2g_t(const Plan& pl, const Work& w, hipStream_t s, bool st, int nsys)
+hipError_t launch_p2g_t(const Plan& pl, const Work& w, hipStream_t s, bool st, int nsys, bool open)
 {
     const Geometry& g = pl.g;
     const int npy = g.M[1] / kPatch, npz = g.M[2] / kPatch;
@@ -463,6 +464,7 @@ hipError_t launch_p2g_t(const Plan& pl, const Work& w, hipStream_t s, bool st, i
         };
         if (halo) {
             sweep(k_p2g_sweep<TG, P, false>);
+            if (open) continue;  // the first FFT pass adds them (the stresslet sweeps share one buffer)
             hipLaunchKernelGGL((k_p2g_halo_sum<TG>), dim3(fix_blocks, nsys), dim3(256), 0, s, (const double*)halo,
                                nseg, seg, P, g, grid, gstride, hstride);
         } else if constexpr (P > 8) {
@@ -475,16 +477,16 @@ hipError_t launch_p2g_t(const Plan& pl, const Work& w, hipStream_t s, bool st, i
 }
 
 template <typename T>
-hipError_t launch_p2g_p(const Plan& pl, const Work& w, hipStream_t s, bool st, int nsys)
+hipError_t launch_p2g_p(const Plan& pl, const Work& w, hipStream_t s, bool st, int nsys, bool open)
 {
     switch (pl.P) {
-    case 4: return launch_p2g_t<T, 4>(pl, w, s, st, nsys);
-    case 6: return launch_p2g_t<T, 6>(pl, w, s, st, nsys);
-    case 8: return launch_p2g_t<T, 8>(pl, w, s, st, nsys);
-    case 10: return launch_p2g_t<T, 10>(pl, w, s, st, nsys);
-    case 12: return launch_p2g_t<T, 12>(pl, w, s, st, nsys);
-    case 14: return launch_p2g_t<T, 14>(pl, w, s, st, nsys);
-    case 16: return launch_p2g_t<T, 16>(pl, w, s, st, nsys);
+    case 4: return launch_p2g_t<T, 4>(pl, w, s, st, nsys, open);
+    case 6: return launch_p2g_t<T, 6>(pl, w, s, st, nsys, open);
+    case 8: return launch_p2g_t<T, 8>(pl, w, s, st, nsys, open);
+    case 10: return launch_p2g_t<T, 10>(pl, w, s, st, nsys, open);
+    case 12: return launch_p2g_t<T, 12>(pl, w, s, st, nsys, open);
+    case 14: return launch_p2g_t<T, 14>(pl, w, s, st, nsys, open);
+    case 16: return launch_p2g_t<T, 16>(pl, w, s, st, nsys, open);
     default: return hipErrorInvalidValue;
     }
 }
@@ -511,11 +513,11 @@ int64_t p2g_halo_elems(const Plan& pl)
     return 2 * (int64_t)(pl.g.M[0] / seg) * (pl.P - 1) * 3 * pl.g.M[1] * pl.g.M[2];
 }
 
-hipError_t launch_p2g(const Plan& pl, const Work& w, int n, hipStream_t s, bool st, int nsys)
+hipError_t launch_p2g(const Plan& pl, const Work& w, int n, hipStream_t s, bool st, int nsys, bool open)
 {
     (void)n;
-    if (pl.grid64) return launch_p2g_p<double>(pl, w, s, st, nsys);
-    return launch_p2g_p<float>(pl, w, s, st, nsys);
+    if (pl.grid64) return launch_p2g_p<double>(pl, w, s, st, nsys, open);
+    return launch_p2g_p<float>(pl, w, s, st, nsys, open);
 }
 
 }  // namespace ewald
