@@ -94,12 +94,13 @@ __device__ inline int wave_scan(int v)
 // registers); latency of the tables, the staging and the barriers where they are sparse, and the halo
 // planes' traffic (24 systems of 5e3 on 64^3: segments of 16 points, about 0.1 ms).  One pass per slab,
 // staged and merged by itself, spent 14 thousand cycles a slab on 30 particles; four slabs of its own
-// per wave and one merge per window took 0.27 ms for the 24 systems and 0.53 for 1e6 on 256^3 with P = 8, but
-// added a point's contributions in another order.  P2G ms with a pass per slab and with four: 1e6
-// uniform on 256^3, P = 16 3.01 -> 1.59, P = 8 (FP32) 2.17 -> 0.56; 24 systems of 5e3 0.85 -> 0.32; 1.5e5 on 128
-// x 128 x 256 0.71 -> 0.33; 1e3 on 32^3 0.083 -> 0.031; dense grids: c2 1.46 -> 1.34, H 0.91 -> 0.75, c4 4.38 ->
-// 4.15, c3 8.8 -> 7.9; one loss: 2e4 in two clusters of five cells 0.46 -> 0.54 (few patches hold everything, and
-// a lone wave per SIMD, which issues an FP64 instruction every eight cycles, pays the staging's latency).
+// per wave and one merge per window took 0.05 ms less for the 24 systems and 0.03 for 1e6 on 256^3 with P = 8, but
+// added a point's contributions in another order.  P2G ms with a pass per slab and with four
+// (and the halo planes added by the FFT, 0.03 ms of it for the 24 systems): 1e6 uniform on 256^3, P = 16 3.01 ->
+// 1.56, P = 8 (FP32) 2.17 -> 0.56; 24 systems of 5e3 0.85 -> 0.27; 1.5e5 on 128 x 128 x 256 0.71 -> 0.31; 1e3 on 32^3
+// 0.083 -> 0.028; dense grids: c2 1.46 -> 1.32, H 0.91 -> 0.73, c4 4.38 -> 4.09, c3 8.8 -> 8.0; one loss: 2e4 in two
+// clusters of five cells 0.46 -> 0.53 (few patches hold everything, and a lone wave per SIMD, which issues an FP64
+// instruction every eight cycles, pays the staging's latency).
 //
 // Staging: 16 particles at a time, four lanes each (two halves of the x weights, the y weights of the
 // patch's lines, and their z weights times f, zero off the footprint), every lane by one recurrence of
