@@ -519,7 +519,7 @@ __global__ __launch_bounds__(64) void k_count_pairs(const Rec64* __restrict__ re
 // pairs also need r > 0 and the index order, and the last, shorter batch keep the direct test;
 // the direct difference of repeated positions is exactly 0 also in the centred frame.
 constexpr int kSymRing = 64;
-constexpr int kTileSplit = 3;  // up to so many waves share a chunk by tiles, more by batches of sources
+constexpr int kUnit = 8;  // consecutive sources dealt at a time to the waves of a chunk (a cache line of u^N)
 constexpr int kFar = 1 << 30;  // ring key offset of sources outside the targets' own tile
 // Balanced drain: batches of 32 ring entries.  Queue bound: with c_t <= 32 pairs per lane,
 // Q = sum c_t and R = ceil(Q / 64) rounds, the excess sum over c_t >= R of (c_t - R) is at most
@@ -578,7 +578,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                                                 const double* __restrict__ srec,
                                                 const int* __restrict__ start,
                                                 const int* __restrict__ chunk_off, Geometry g,
-                                                PairArgs a, double* __restrict__ u_near, int nsplit)
+                                                PairArgs a, double* __restrict__ u_near, int nsplit, bool by_unit)
 {
     constexpr int NS = ST ? 6 : 1;
     constexpr bool kScaled = !ST && std::is_same<TF, double>::value && Lv > 0;
@@ -604,8 +604,11 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
     // plain block order: an XCD-aware order (each XCD sweeping a contiguous range) was
     // measured 12% slower here, unlike in G2P
     // nsplit waves share a chunk, each taking every nsplit-th of its neighbour tiles (shorter waves: a
-    // smaller tail when the last waves of the launch run), or, where small inputs are split further, every
-    // nsplit-th batch of 64 candidate sources (their sources may all lie in a tile or two)
+    // smaller tail when the last waves of the launch run), or, by_unit, every nsplit-th unit of kUnit
+    // consecutive sources, counted through the tiles: small inputs, whose sources may all lie in a tile or
+    // two, and whose longest wave is the launch.  Batches of 64 left uneven shares (1e3: 0.037 -> 0.027 ms, 3e4 0.222 ->
+    // 0.159, 2e4 in two clusters 0.300 -> 0.264, 1.5e5 0.436 -> 0.426, 24 systems 0.182 -> 0.161); single sources spread the
+    // waves' atomics on u^N over eight times the cache lines (the clusters 0.345).
     const int wave = uniform_i((int)blockIdx.x) / nsplit;
     const int part = uniform_i((int)blockIdx.x) % nsplit;
     const int lane = threadIdx.x;
@@ -667,8 +670,8 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
     const double post = ST ? 1.0 : PairCoef::post(a);
 
     int rhead = 0, rcount = 0;
-    const bool by_tile = nsplit <= kTileSplit;
-    int turn = part;  // tiles or batches to pass over before the next of this wave's
+    const int lane_at = by_unit ? (lane / kUnit) * kUnit * nsplit + lane % kUnit : lane;
+    int turn = part;  // tiles or units to pass over before the next of this wave's
     auto skip = [&]() {
         const bool other = turn > 0;  // another wave of this chunk takes it
         turn = other ? turn - 1 : nsplit - 1;
@@ -920,15 +923,16 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 const double shz = fz * g.L[2];
                 const double gz = fmax(0.0, fmax(uz * w[2] - bhi[2], blo[2] - (uz + 1) * w[2]));
                 if (gx * gx + gy * gy + gz * gz >= a.rc2) continue;
-                if (by_tile && skip()) continue;
+                if (!by_unit && skip()) continue;
                 const bool own = (dx == 0 && dy == 0 && dz == 0);
                 const int nt = tbase + (wx * g.NT[1] + wy) * g.NT[2] + wz;
                 // own tile: sources below the first target can pair with none of them
                 const int sa = own ? first : start[nt * per], sb = start[(nt + 1) * per];
                 const int koff = own ? 0 : kFar;
-                for (int base = sa; base < sb; base += kWave) {
-                    if (!by_tile && skip()) continue;
-                    const int s = base + lane;
+                const int step = by_unit ? kWave * nsplit : kWave;
+                int base = by_unit ? sa + turn * kUnit : sa;
+                for (; base < sb; base += step) {
+                    const int s = base + lane_at;
                     bool keep = false;
                     double sx = 0, sy = 0, sz = 0, f0 = 0, f1 = 0, f2 = 0;
                     if (s < sb) {
@@ -980,6 +984,10 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                             rcount -= kB;
                         }
                     }
+                }
+                if (by_unit) {
+                    turn = (base - sa) / kUnit - (sb - sa + kUnit - 1) / kUnit;
+                    while (turn >= nsplit) turn -= nsplit;
                 }
             }
         }
@@ -1355,10 +1363,11 @@ void launch_p2p_det(const Plan& pl, const Work& w, int n, hipStream_t s, const G
 }
 
 template <typename TF, int Lv, bool ST>
-void launch_p2p_sym(const Work& w, int n, hipStream_t s, const Geometry& g, const PairArgs& a, dim3 grid, int split)
+void launch_p2p_sym(const Work& w, int n, hipStream_t s, const Geometry& g, const PairArgs& a, dim3 grid, int split,
+                    bool by_unit)
 {
     hipLaunchKernelGGL((k_p2p_sym<TF, Lv, ST>), grid, dim3(kWave), 0, s, n, (const Rec64*)w.rec, w.srec, w.start,
-                       w.chunk_off, g, a, w.u_near, split);
+                       w.chunk_off, g, a, w.u_near, split, by_unit);
 }
 
 hipError_t launch_p2p(const Plan& pl, const Work& w, int n, hipStream_t s, bool st, int nsys)
@@ -1382,34 +1391,40 @@ hipError_t launch_p2p(const Plan& pl, const Work& w, int n, hipStream_t s, bool 
         }
         return hipGetLastError();
     }
-    // Symmetric kernel: waves per chunk.  Three shorten the launch's tail; more (then dealt batches of
-    // sources instead of tiles) fill the chip where the chunks are few, and even out the chunks of
-    // clustered inputs, until a wave's own start and end outweigh its share.  P2P ms at 3 / 5 / 7 / 13 /
-    // 33 waves per chunk: 24 chunks (1e3 uniform, FP64) 0.081 / 0.066 / 0.068 / 0.049 / 0.039; 441 (2e4 in
-    // 2 clusters, FP32) 1.00 / 0.76 / 0.54 / 0.35 / 0.30 (2.97 with six by tiles); 1536 (6.6e4 uniform, FP32)
-    // 0.61 / 0.55 / 0.51 / 0.54 / 0.66; 3368 (1.5e5, FP64) 0.49 / 0.44 / 0.45 / 0.51 / 0.76; 19721 (1e6, 1e-8,
-    // 256^3) 3.67 / 3.79 / 3.89 / 4.36 / 6.18.  Odd, so that the waves of a chunk, consecutive blocks, spread
+    // Symmetric kernel: waves per chunk.  Three shorten the launch's tail; more fill the chip where the chunks
+    // are few, and even out the chunks of clustered inputs, until a wave's own start and end outweigh its
+    // share.  P2P ms at 3 / 5 / 7 / 13 / 21 / 33 / 65 waves per chunk: 24 chunks (1e3 uniform, FP64) 0.061 / 0.046 /
+    // 0.041 / 0.034 / 0.029 / 0.027 / 0.024; 441 (2e4 in 2 clusters, FP32) 1.01 / 0.61 / 0.55 / 0.36 / 0.26 / 0.27 / 0.26;
+    // 533 (3e4 uniform, FP64) 0.23 / 0.19 / 0.16 / 0.16 / 0.16 / 0.19 / 0.26; 1544 (6.6e4, FP32) 0.56 / 0.54 / 0.54 / 0.59 /
+    // 0.67 / 0.76 / 1.08; 3412 (24 systems of 5e3, FP32) 0.16 / 0.17 / 0.19 / 0.25 / 0.31 / 0.40 / 0.66; 3368 (1.5e5, FP64) 0.426 /
+    // 0.418 / 0.449 / 0.54 / 0.69 / 0.83 / 1.26; 40 (2e3) at 33 / 49 / 65 0.039 / 0.032 / 0.033, 62 (3.4e3) 0.042 / 0.051 /
+    // 0.047.  Odd, so that the waves of a chunk, consecutive blocks, spread
     // over the XCDs (with 8 or 16, all the chunks' first waves, the heaviest, meet on one).
     // With stresslet sources fewer waves fit a CU (16 KB of LDS each) and the pairs cost more: 1294 chunks
-    // (5e4 at 1e-8) 0.26 / 0.23 / 0.24 / 0.27 / 0.45, 5200 (3e5, FP32) 1.89 / 1.73 / 1.70 / 1.82 / 2.31.
-    const int64_t fill = ((st ? 11520 : 23040) / waves - 1) | 1;
-    const int64_t least = st && waves < 8192 ? 5 : kTileSplit;
-    const int kSplit = (int)std::min<int64_t>(33, std::max(least, fill));
+    // (5e4 at 1e-8) 0.218 / 0.216 / 0.239 / 0.30 / 0.35 / 0.44, 5200 (3e5, FP32) 1.70 / 1.64 / 1.67 / 1.70 / 1.88 / 2.22.
+    // What is dealt: units of kUnit sources below 8192 chunks (see the kernel), neighbour tiles above, where a
+    // wave's compact batches are worth more than even shares (three waves, tiles / units: 5200 chunks 1.36 / 1.24,
+    // 3e5 in 30 clusters, FP64 11.4 / 7.9; 19721 (1e6), 256^3 FP64 3.50 / 3.61, c2 17.6 / 18.4, H 9.47 / 9.93; 78884
+    // (c4) 48.0 / 50.3).
+    const int64_t fill = ((st ? 4608 : 9216) / waves) | 1;
+    const int64_t least = st && waves < 8192 ? 5 : 3, most = waves <= 48 ? 49 : 33;
+    const int kSplit = (int)std::min<int64_t>(most, std::max(least, fill));
+    const bool by_unit = waves < 8192;
     const dim3 sgrid((unsigned)(waves * kSplit));
     if (st) {
         switch (lv) {
-        case 0: launch_p2p_sym<double, 0, true>(w, n, s, g, a, sgrid, kSplit); break;
-        case 1: launch_p2p_sym<double, 1, true>(w, n, s, g, a, sgrid, kSplit); break;
-        case 2: launch_p2p_sym<double, 2, true>(w, n, s, g, a, sgrid, kSplit); break;
-        default: launch_p2p_sym<float, 0, true>(w, n, s, g, a, sgrid, kSplit); break;
+        case 0: launch_p2p_sym<double, 0, true>(w, n, s, g, a, sgrid, kSplit, by_unit); break;
+        case 1: launch_p2p_sym<double, 1, true>(w, n, s, g, a, sgrid, kSplit, by_unit); break;
+        case 2: launch_p2p_sym<double, 2, true>(w, n, s, g, a, sgrid, kSplit, by_unit); break;
+        default: launch_p2p_sym<float, 0, true>(w, n, s, g, a, sgrid, kSplit, by_unit); break;
         }
         return hipGetLastError();
     }
     switch (lv) {
-    case 0: launch_p2p_sym<double, 0, false>(w, n, s, g, a, sgrid, kSplit); break;
-    case 1: launch_p2p_sym<double, 1, false>(w, n, s, g, a, sgrid, kSplit); break;
-    case 2: launch_p2p_sym<double, 2, false>(w, n, s, g, a, sgrid, kSplit); break;
-    default: launch_p2p_sym<float, 0, false>(w, n, s, g, a, sgrid, kSplit); break;
+    case 0: launch_p2p_sym<double, 0, false>(w, n, s, g, a, sgrid, kSplit, by_unit); break;
+    case 1: launch_p2p_sym<double, 1, false>(w, n, s, g, a, sgrid, kSplit, by_unit); break;
+    case 2: launch_p2p_sym<double, 2, false>(w, n, s, g, a, sgrid, kSplit, by_unit); break;
+    default: launch_p2p_sym<float, 0, false>(w, n, s, g, a, sgrid, kSplit, by_unit); break;
     }
     return hipGetLastError();
 }
