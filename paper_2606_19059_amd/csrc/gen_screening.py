@@ -17,7 +17,7 @@ It also prints the polynomials of 2^s on |s| <= 1/2 for the reduced-cost exponen
 degrees at 50 digits, in the monomial basis of s, divided by their leading coefficients
 (kExpLead*).
 
-The reduced-cost FP64 pairs take erfcx(x) + (2/sqrt(pi)) x itself as a polynomial (kScreenW*), in
+The reduced-cost FP64 pairs take erfcx(x) + (2/sqrt(pi)) x itself as a polynomial (kScreenV*), in
 X = x sqrt(log2 e) (so that e^{-x^2} = 2^{-X^2}), divided by its leading coefficient: the minimax
 polynomial under the weight e^{-x^2} that multiplies it (Remez exchange at 50 digits), which needs no
 reciprocal.  Run: python gen_screening.py > screening.h
@@ -32,8 +32,11 @@ XMAX = mp.mpf(13) / 2
 DEGREES = {"64": 16, "64s": 12, "64f": 10, "32": 11}
 # degree of the polynomial of 2^s, |s| <= 1/2: "1" for 1e-10 <= tol < 1e-8, "2" for tol >= 1e-8
 EXP_DEGREES = {"1": 8, "2": 7}
-# degree of the weighted polynomials, by the same levels
-WEIGHTED_DEGREES = {"1": 18, "2": 15}
+# degrees of the weighted polynomials, by the same levels: V, which the kernels take, and W, one degree
+# lower, which no kernel takes.  W's largest error is below that of the Moebius form (64s, 64f), but it is as
+# large over the whole range where that one falls: the root of the integral of dC^2, which is what enters a
+# sum over uniform pairs, is 1.9 (level 1) and 1.7 times (level 2) as large.  V's is half as large.
+WEIGHTED_DEGREES = {"W1": 18, "W2": 15, "V1": 19, "V2": 16}
 
 
 def weighted_remez(fun, weight, deg, xmax):
@@ -125,7 +128,7 @@ def main():
     print("// leading coefficient (kScreenLead*; kScreenM*[k], k < deg, the leading 1 implicit);")
     print("// FP32 in u = A t + B (kScreenC32).  2^s for |s| <= 1/2: kExpLead* x monic kExpM*.")
     print("// erfcx(x) + 2x/sqrt(pi), minimax under the weight e^{-x^2}, in X = x sqrt(log2 e):")
-    print("// kScreenLeadW* x monic kScreenW*.")
+    print("// kScreenLeadV* x monic kScreenV* (W: one degree lower, not taken by any kernel).")
     print("#pragma once")
     print("namespace ewald {")
     print("constexpr double kScreenK = %d;" % K)
@@ -157,9 +160,9 @@ def main():
                            lambda x: mp.exp(-x * x), deg, XMAX)
         c = [v / scale ** k for k, v in enumerate(c)]
         lead = c[deg]
-        print("constexpr int kScreenDegW%s = %d;" % (tag, deg))
-        print("constexpr double kScreenLeadW%s = %.17g;" % (tag, float(lead)))
-        print(arr("kScreenW%s" % tag, [v / lead for v in c[:deg]]))
+        print("constexpr int kScreenDeg%s = %d;" % (tag, deg))
+        print("constexpr double kScreenLead%s = %.17g;" % (tag, float(lead)))
+        print(arr("kScreen%s" % tag, [v / lead for v in c[:deg]]))
     print("}  // namespace ewald")
 
 

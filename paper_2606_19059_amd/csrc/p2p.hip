@@ -30,21 +30,24 @@ namespace ewald {
 namespace {
 
 // Accuracy levels of the FP64 pair formula (template argument Lv), chosen from the plan's tol so
-// that the formula's own error stays 30-40 times below it:
+// that the formula's own error stays at least 30 times below it:
 //   0 (tol < 1e-10): degree-16 screening polynomial (|dC| < 5e-15), library exponential, two
 //     Newton steps on the hardware reciprocal, third-order rsqrt correction;
 //   1 (1e-10 <= tol < 1e-8): erfcx(x) + 2x/sqrt(pi) as a polynomial in x fitted under the weight
-//     e^{-x^2} (degree 18, |dC| < 2.8e-12), e^{-y} = 2^z (z = -y log2 e) as 2^n times a degree-8
+//     e^{-x^2} (degree 19, |dC| < 7.2e-13), e^{-y} = 2^z (z = -y log2 e) as 2^n times a degree-8
 //     Chebyshev polynomial of 2^s, z = n + s, n = rint(z) (relative error 1.1e-12; no range checks:
 //     -61 < z <= 0 on the P2P range), one Newton step on rsqrt;
-//   2 (tol >= 1e-8): degree 15 (|dC| < 1.6e-10) and a degree-7 polynomial of 2^s (5.6e-11), else as
+//   2 (tol >= 1e-8): degree 16 (|dC| < 4.0e-11) and a degree-7 polynomial of 2^s (5.6e-11), else as
 //     level 1.
-// The weighted polynomial needs no reciprocal: 15 instructions against 16 (one of them quarter rate)
-// with the degree-10 polynomial in (x - 3)/(x + 3) that level 2 took before (|dC| < 3e-10; stresslet
-// pairs still take that form and its degree-12 sibling).  All polynomials are stored divided by their
-// leading coefficients (screening.h), so that Horner starts with an addition (an FMA cannot take two
-// scalar-register coefficients).  The FP64 pair formula therefore returns its coefficients divided by
-// post; the kernels multiply each target's and source's sum by post once, at the end.
+// The weighted polynomial needs no reciprocal: 16 instructions, as with the degree-10 polynomial in
+// (x - 3)/(x + 3) (stresslet pairs take that form and its degree-12 sibling), of which one is
+// quarter rate.  With the exponential, |dC| at levels 1 and 2: at most 1.6e-12 and 8.0e-11 (4.3e-12 and
+// 2.9e-10 for those forms), for x > 1 9.5e-13 and 5.4e-11 (1.1e-12 and 7.4e-11), and
+// (integral of dC^2 dx)^1/2, which enters a sum over uniform pairs, 1.2e-12 and 6.7e-11 (2.3e-12 and 1.3e-10).
+// The minimax error is flat, so that beyond x = 2, where the others fall with C itself, it is the larger.
+// All polynomials are stored divided by their leading coefficients (screening.h), so that Horner
+// starts with an addition (an FMA cannot take two scalar-register coefficients).  The FP64 pair formula
+// therefore returns its coefficients divided by post; the kernels multiply each target's and source's sum by post once, at the end.
 // Levels 1 and 2 work (without stresslet sources) on positions scaled by kappa = xi sqrt(log2 e), which
 // makes the exponent -r^2 itself and r the polynomials' variable (two multiplications per pair less).
 constexpr double kLog2e = 1.4426950408889634074;
@@ -64,7 +67,7 @@ struct PairArgs {
     // takes them as an operand, no per-pair register copies); mw: the weighted screening polynomial of
     // levels 1 and 2, c32: the FP32 formula's
     double ms[kScreenDeg64];
-    double mw[kScreenDegW1];
+    double mw[kScreenDegV1];
     double me[kExpDeg1];
     float c32[kScreenDeg32 + 1];
     float zc32;  // FP32 formula: -xi^2 log2 e
@@ -206,7 +209,7 @@ __device__ inline double rsqrt_pos(double r2)
 template <int Lv>
 __device__ inline double screen_w64(double X, const PairArgs& a)
 {
-    constexpr int deg = Lv == 1 ? kScreenDegW1 : kScreenDegW2;
+    constexpr int deg = Lv == 1 ? kScreenDegV1 : kScreenDegV2;
     double q = X + a.mw[deg - 1];
 #pragma unroll
     for (int k = deg - 2; k >= 0; --k) q = fma(q, X, a.mw[k]);
@@ -1301,10 +1304,10 @@ PairArgs pair_args(const Plan& pl, int lv)
     const int ds = lv == 2 ? kScreenDeg64f : lv == 1 ? kScreenDeg64s : kScreenDeg64;
     for (int k = 0; k < kScreenDeg64; ++k) a.ms[k] = k < ds ? ms[k] : 0.0;
     a.lead_st = lv == 2 ? kScreenLead64f : lv == 1 ? kScreenLead64s : kScreenLead64;
-    const double* mw = lv == 2 ? kScreenW2 : kScreenW1;
-    const int dw = lv == 2 ? kScreenDegW2 : kScreenDegW1;
-    for (int k = 0; k < kScreenDegW1; ++k) a.mw[k] = k < dw ? mw[k] : 0.0;
-    a.lead_s = lv == 2 ? kScreenLeadW2 : lv == 1 ? kScreenLeadW1 : kScreenLead64;
+    const double* mw = lv == 2 ? kScreenV2 : kScreenV1;
+    const int dw = lv == 2 ? kScreenDegV2 : kScreenDegV1;
+    for (int k = 0; k < kScreenDegV1; ++k) a.mw[k] = k < dw ? mw[k] : 0.0;
+    a.lead_s = lv == 2 ? kScreenLeadV2 : lv == 1 ? kScreenLeadV1 : kScreenLead64;
     const double* me = lv == 2 ? kExpM2 : kExpM1;
     const int de = lv == 2 ? kExpDeg2 : kExpDeg1;
     for (int k = 0; k < kExpDeg1; ++k) a.me[k] = k < de ? me[k] : 0.0;
