@@ -48,8 +48,12 @@ namespace {
 // All polynomials are stored divided by their leading coefficients (screening.h), so that Horner
 // starts with an addition (an FMA cannot take two scalar-register coefficients).  The FP64 pair formula
 // therefore returns its coefficients divided by post; the kernels multiply each target's and source's sum by post once, at the end.
-// Levels 1 and 2 work (without stresslet sources) on positions scaled by kappa = xi sqrt(log2 e), which
-// makes the exponent -r^2 itself and r the polynomials' variable (two multiplications per pair less).
+// Levels 1 and 2 work (without stresslet sources) on positions scaled by a power of two p near
+// kappa = xi sqrt(log2 e), which makes r the variable of polynomials whose coefficients the host multiplies by
+// powers of kappa / p: one multiplication per pair less, whatever the box's size.  A power of two, so that
+// the scaled positions and their differences are exact: scaling by kappa itself, which would save the
+// exponent's multiplication too, rounds every position once more, and the distance of two points 1e-8 apart
+// in a chunk of edge 1/8 was then off by 1.4e-10 at the median (4e-17 so).
 constexpr double kLog2e = 1.4426950408889634074;
 
 struct PairArgs {
@@ -61,11 +65,11 @@ struct PairArgs {
     // C'/r - h e' with h = (4 xi/sqrt(pi))/lead_s
     double zc, g, h, post, lead_s, lead_e;
     double lead_st;  // leading coefficient of ms (stresslet pairs)
-    // scaled form: kappa, the cutoff (kappa r_c)^2, h / kappa; the sums' factor is post kappa
-    double kappa, rc2s, hs;
+    // scaled form (see above): p, the cutoff (p r_c)^2, h / p, zc / p^2; the sums' factor is post p
+    double scale, rc2s, hs, zs;
     // polynomials passed by value, so that the coefficients sit in scalar registers (an FMA then
     // takes them as an operand, no per-pair register copies); mw: the weighted screening polynomial of
-    // levels 1 and 2, c32: the FP32 formula's
+    // levels 1 and 2 in the scaled r, c32: the FP32 formula's
     double ms[kScreenDeg64];
     double mw[kScreenDegV1];
     double me[kExpDeg1];
@@ -205,20 +209,20 @@ __device__ inline double rsqrt_pos(double r2)
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// (erfcx(x) + 2x/sqrt(pi)) / lead_s at X = x sqrt(log2 e): the weighted polynomial of screening.h
+// (erfcx(x) + 2x/sqrt(pi)) / lead_s at the scaled r: the weighted polynomial of screening.h
 template <int Lv>
-__device__ inline double screen_w64(double X, const PairArgs& a)
+__device__ inline double screen_w64(double r, const PairArgs& a)
 {
     constexpr int deg = Lv == 1 ? kScreenDegV1 : kScreenDegV2;
-    double q = X + a.mw[deg - 1];
+    double q = r + a.mw[deg - 1];
 #pragma unroll
-    for (int k = deg - 2; k >= 0; --k) q = fma(q, X, a.mw[k]);
+    for (int k = deg - 2; k >= 0; --k) q = fma(q, r, a.mw[k]);
     return q;
 }
 
 // Coefficients of G^N(r) f = a1 f + b (r.f) r for 0 < r^2 < r_c^2 (FP64), divided by post:
 // a1 = C/r - (4 xi/sqrt(pi)) e, b = C/r^3, with e = e^{-xi^2 r^2} = lead_e e' and C = e Q,
-// Q = lead_s Q'.  Levels 1 and 2: r2 is (kappa r)^2, and a1, b are for the scaled r.
+// Q = lead_s Q'.  Levels 1 and 2: r2 is (p r)^2, and a1, b are for the scaled r.
 template <int Lv>
 __device__ inline void coef64(double r2, const PairArgs& a, double& a1, double& b)
 {
@@ -228,7 +232,7 @@ __device__ inline void coef64(double r2, const PairArgs& a, double& a1, double& 
         e = exp(-a.xi2 * r2);
         q = screen_q64<Lv>(a.xi * r2 * rinv, a);
     } else {
-        e = exp2_lead<Lv>(-r2, a);
+        e = exp2_lead<Lv>(a.zs * r2, a);
         q = screen_w64<Lv>(r2 * rinv, a);
     }
     const double Cr = e * q * rinv;
@@ -275,7 +279,7 @@ struct Coef<double, Lv> {
     {
         coef64<Lv>(r2, a, a1, b);
     }
-    __device__ static inline double post(const PairArgs& a) { return Lv > 0 ? a.post * a.kappa : a.post; }
+    __device__ static inline double post(const PairArgs& a) { return Lv > 0 ? a.post * a.scale : a.post; }
 };
 template <int Lv>
 struct Coef<float, Lv> {
@@ -645,7 +649,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
         bhi[d] = uniform_d(wave_max(me.x[d]));
         cen[d] = uniform_d(0.5 * (blo[d] + bhi[d]));
         tx[d] = active ? me.x[d] - cen[d] : 1e30;  // an inactive lane accepts no pair
-        if (kScaled) tx[d] *= a.kappa;
+        if (kScaled) tx[d] *= a.scale;
         tlim += tx[d] * tx[d];
         tgt[d][lane] = tx[d];
         tgtf[d][lane] = (TF)me.f[d];
@@ -954,9 +958,9 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                         sy -= cen[1];
                         sz -= cen[2];
                         if (kScaled) {
-                            sx *= a.kappa;
-                            sy *= a.kappa;
-                            sz *= a.kappa;
+                            sx *= a.scale;
+                            sy *= a.scale;
+                            sz *= a.scale;
                         }
                     }
                     // append in two halves so the 64-slot ring never holds more than 63
@@ -1073,7 +1077,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
         bhi[d] = uniform_d(wave_max(me.x[d]));
         cen[d] = uniform_d(0.5 * (blo[d] + bhi[d]));
         tx[d] = active ? me.x[d] - cen[d] : 1e30;  // an inactive lane accepts no pair
-        if (kScaled) tx[d] *= a.kappa;
+        if (kScaled) tx[d] *= a.scale;
         tlim += tx[d] * tx[d];
         tgt[d][lane] = tx[d];
         acc[d][lane] = 0.0;
@@ -1206,9 +1210,9 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
                 sy -= cen[1];
                 sz -= cen[2];
                 if (kScaled) {
-                    sx *= a.kappa;
-                    sy *= a.kappa;
-                    sz *= a.kappa;
+                    sx *= a.scale;
+                    sy *= a.scale;
+                    sz *= a.scale;
                 }
             }
             // append in two halves so the 64-slot ring never holds more than 63
@@ -1306,19 +1310,23 @@ PairArgs pair_args(const Plan& pl, int lv)
     a.lead_st = lv == 2 ? kScreenLead64f : lv == 1 ? kScreenLead64s : kScreenLead64;
     const double* mw = lv == 2 ? kScreenV2 : kScreenV1;
     const int dw = lv == 2 ? kScreenDegV2 : kScreenDegV1;
-    for (int k = 0; k < kScreenDegV1; ++k) a.mw[k] = k < dw ? mw[k] : 0.0;
-    a.lead_s = lv == 2 ? kScreenLeadV2 : lv == 1 ? kScreenLeadV1 : kScreenLead64;
+    // X = kappa r = ratio (scale r): the monic polynomial in X is ratio^dw times the one of these coefficients
+    const double kappa = pl.xi * sqrt(kLog2e);
+    a.scale = exp2(rint(log2(kappa)));
+    const double ratio = kappa / a.scale;
+    for (int k = 0; k < kScreenDegV1; ++k) a.mw[k] = k < dw ? mw[k] * pow(ratio, k - dw) : 0.0;
+    a.lead_s = lv == 0 ? kScreenLead64 : (lv == 2 ? kScreenLeadV2 : kScreenLeadV1) * pow(ratio, dw);
     const double* me = lv == 2 ? kExpM2 : kExpM1;
     const int de = lv == 2 ? kExpDeg2 : kExpDeg1;
     for (int k = 0; k < kExpDeg1; ++k) a.me[k] = k < de ? me[k] : 0.0;
     a.lead_e = lv == 0 ? 1.0 : lv == 2 ? kExpLead2 : kExpLead1;
     a.zc = -a.xi2 * kLog2e;
     a.zc32 = (float)a.zc;
-    a.kappa = pl.xi * sqrt(kLog2e);
-    a.rc2s = a.rc2 * (a.xi2 * kLog2e);
+    a.rc2s = a.rc2 * (a.scale * a.scale);
+    a.zs = a.zc / (a.scale * a.scale);
     a.g = kTwoOverSqrtPi / a.lead_st;
     a.h = a.four_xi_over_sqrtpi / a.lead_s;
-    a.hs = a.h / a.kappa;
+    a.hs = a.h / a.scale;
     a.post = a.lead_s * a.lead_e;
     for (int k = 0; k <= kScreenDeg32; ++k) a.c32[k] = (float)kScreenC32[k];
     return a;
