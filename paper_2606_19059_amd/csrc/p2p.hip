@@ -542,8 +542,11 @@ __device__ inline unsigned long long ballot(bool p) { return __builtin_amdgcn_ba
 // for 32 sources x 64 targets by eight v_mfma_f64_16x16x4f64 (sources as rows): the accepted sources of
 // each lane's target, as a mask.  On gfx950 lane l = 16 kq + i supplies A[i][kq] and B[kq][i] and
 // receives D[4 r + kq][i], r = 0..3.  Batches start at ring slot 0 or 32 (32 entries at a time from a
-// 64-slot ring), so the batch's slots need no wrap.  bt: the target operands (target_operands).
-__device__ inline unsigned accept_mask(double (&ring)[4][kSymRing], int rhead, const double (&bt)[4], int mi, int mk)
+// 64-slot ring), so the batch's slots need no wrap.  bt: the target operands.  off:
+// coordinate mk (below 3) of the centre in the frame of ring[0..2], which s' and t' are relative to (0:
+// the ring is centred itself).
+__device__ inline unsigned accept_mask(double (&ring)[4][kSymRing], int rhead, const double (&bt)[4], int mi, int mk,
+                                       double off)
 {
     typedef double v4d __attribute__((ext_vector_type(4)));
     unsigned m = 0;
@@ -556,7 +559,7 @@ __device__ inline unsigned accept_mask(double (&ring)[4][kSymRing], int rhead, c
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
         const double xk = ld1(ring[mk < 3 ? mk : 0][rhead + 8 * (mi & 3) + 4 * mb + (mi >> 2)]);
-        av[mb] = mk < 3 ? -2.0 * xk : 1.0;
+        av[mb] = mk < 3 ? -2.0 * (xk - off) : 1.0;
         cv[mb] = *reinterpret_cast<const v4d*>(&ring[3][rhead + 8 * mk + 4 * mb]);
     }
     // the sign bit of an item is its test.  The bits of target 16 nb + i are spread over lanes
@@ -702,7 +705,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 m = pass ? (m | (1u << j)) : m;
             }
         } else if (cnt == kB) {
-            m = accept_mask(ring, rhead, bt, mi, mk);
+            m = accept_mask(ring, rhead, bt, mi, mk, 0.0);
         } else {
             for (int j = 0; j < cnt; ++j) {
                 const int slot = (rhead + j) & (kSymRing - 1);
@@ -1034,9 +1037,9 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
     constexpr bool kScaled = std::is_same<TF, double>::value && Lv > 0;
     using PairCoef = Coef<TF, Lv>;
     constexpr int kB = kBalBatch;
-    __shared__ double tgt_[NW][3][kWave];  // t' (x, y, z)
+    __shared__ double tgt_[NW][3][kWave];  // (x, y, z)
     __shared__ double acc_[NW][3][kWave];
-    __shared__ __align__(32) double ring_[NW][4][kSymRing];  // s' (x, y, z) and |s'|^2
+    __shared__ __align__(32) double ring_[NW][4][kSymRing];  // (x, y, z) and |s'|^2
     __shared__ TF ringf_[NW][3][kSymRing];
     __shared__ unsigned short queue_[NW][kBalExcess];
 
@@ -1068,28 +1071,32 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
     const int sys = t / g.ntiles, tl = t - sys * g.ntiles, tbase = sys * g.ntiles;
     const int tc[3] = {tl / (g.NT[1] * g.NT[2]), (tl / g.NT[2]) % g.NT[1], tl % g.NT[2]};
     double w[3], blo[3], bhi[3], cen[3], tx[3], oacc[3];
-    const double rc2 = kScaled ? a.rc2s : a.rc2;  // of the (scaled) positions relative to the centre
+    // Positions are the particles' own (times the power of two of the reduced-cost levels), so that the
+    // differences of the pairs are the direct ones, exact for close pairs and 0 for a target and its own
+    // record; the matrix test alone takes them relative to the centre of the targets' bounding box (t', s').
+    const double rc2 = kScaled ? a.rc2s : a.rc2, scale = kScaled ? a.scale : 1.0;
     double tlim = -rc2;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         w[d] = g.B * g.h[d];
         blo[d] = uniform_d(wave_min(me.x[d]));
         bhi[d] = uniform_d(wave_max(me.x[d]));
-        cen[d] = uniform_d(0.5 * (blo[d] + bhi[d]));
-        tx[d] = active ? me.x[d] - cen[d] : 1e30;  // an inactive lane accepts no pair
-        if (kScaled) tx[d] *= a.scale;
-        tlim += tx[d] * tx[d];
+        cen[d] = uniform_d(0.5 * (blo[d] + bhi[d]) * scale);
+        tx[d] = active ? me.x[d] * scale : 1e30;  // an inactive lane accepts no pair
+        const double tc = tx[d] - cen[d];
+        tlim += tc * tc;
         tgt[d][lane] = tx[d];
         acc[d][lane] = 0.0;
         oacc[d] = 0.0;
     }
     wave_lds_sync();
     const int mi = lane & 15, mk = lane >> 4;  // lane = 16 mk + mi
+    const double cen_k = mk == 0 ? cen[0] : mk == 1 ? cen[1] : cen[2];
     double bt[4];  // target operands of accept_mask
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) {
         const double l = __shfl(tlim, 16 * nb + mi, kWave);
-        bt[nb] = mk < 3 ? tgt[mk < 3 ? mk : 0][16 * nb + mi] : l;
+        bt[nb] = mk < 3 ? tgt[mk < 3 ? mk : 0][16 * nb + mi] - cen_k : l;
     }
 
     int rhead = 0, rcount = 0;
@@ -1098,7 +1105,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
     auto process = [&](int cnt) {
         unsigned m = 0;
         if (own_left == 0 && cnt == kB) {
-            m = accept_mask(ring, rhead, bt, mi, mk);
+            m = accept_mask(ring, rhead, bt, mi, mk, cen_k);
         } else {
             for (int j = 0; j < cnt; ++j) {
                 const int slot = (rhead + j) & (kSymRing - 1);
@@ -1206,14 +1213,9 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
                 const double ey = fmax(0.0, fmax(blo[1] - sy, sy - bhi[1]));
                 const double ez = fmax(0.0, fmax(blo[2] - sz, sz - bhi[2]));
                 keep = ex * ex + ey * ey + ez * ez < a.rc2;
-                sx -= cen[0];
-                sy -= cen[1];
-                sz -= cen[2];
-                if (kScaled) {
-                    sx *= a.scale;
-                    sy *= a.scale;
-                    sz *= a.scale;
-                }
+                sx *= scale;
+                sy *= scale;
+                sz *= scale;
             }
             // append in two halves so the 64-slot ring never holds more than 63
 #pragma unroll
@@ -1225,7 +1227,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
                     ring[0][slot] = sx;
                     ring[1][slot] = sy;
                     ring[2][slot] = sz;
-                    ring[3][slot] = sx * sx + sy * sy + sz * sz;
+                    const double cx = sx - cen[0], cy = sy - cen[1], cz = sz - cen[2];
+                    ring[3][slot] = cx * cx + cy * cy + cz * cz;
                     ringf[0][slot] = (TF)f0;
                     ringf[1][slot] = (TF)f1;
                     ringf[2][slot] = (TF)f2;

@@ -1,11 +1,12 @@
-"""Nearly touching particles: the near field of pairs 1e-10 apart, dominated by each particle's partner,
+"""Nearly touching particles: the near field of pairs 1e-10 (FP32, deterministic: 1e-12) apart, dominated by each particle's partner,
 against the oracle's real-space sum, particle by particle.  The difference of two such positions is
 exact in FP64, and has to reach the pair formula so.
 
 The symmetric kernel takes positions relative to the centre of a chunk's targets, which rounds few of
 them (those near a face of the box): the median error is that of the pair formula (full FP64 1e-13;
 reduced-cost levels 1e-11 and 5e-10, the screening polynomial's and the exponential's error at
-r = 0; FP32 2e-6)."""
+r = 0; FP32 2e-6).  The deterministic kernel takes the particles' own positions: the same bounds hold for
+every particle."""
 import numpy as np
 import pytest
 
@@ -40,3 +41,10 @@ def pair_errors(sep, n, n_max, xi, deterministic, precision, tol):
 @pytest.mark.parametrize("xi,n_max", [(9.0, 1500), (14.0, 1500), (18.0, 200_000)])
 def test_close_pairs_match_oracle(xi, n_max, precision, tol, bound):
     assert np.median(pair_errors(1e-10, 1500, n_max, xi, False, precision, tol)) < bound
+
+
+@pytest.mark.parametrize("precision,tol,bound", VARIANTS)
+@pytest.mark.parametrize("xi,n_max", [(9.0, 1500), (14.0, 200_000)])
+def test_close_pairs_deterministic_match_oracle(xi, n_max, precision, tol, bound):
+    sep = 1e-12 if precision == "fp32" else 1e-10
+    assert np.max(pair_errors(sep, 1500, n_max, xi, True, precision, tol)) < bound
