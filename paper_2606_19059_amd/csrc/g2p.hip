@@ -355,6 +355,7 @@ void k_g2p_mfma(const typename RecView<T>::Rec* __restrict__ rec, const int* __r
 // against 435 (G2P, with this kernel: 1e6 on 256^3 2.01 -> 1.88 ms, 1.5e5 on 128 x 128 x 256 0.38 -> 0.35, c2
 // 1.11 -> 1.06, c4 3.46 -> 3.34).  FP32 grids keep the sort's order, and with it the order of their FP32 sums.
 constexpr int kOrderThreads = 512;
+constexpr int kOrderBlocks = 1 << 20;  // most blocks (times their threads within a launch's 2^32)
 __global__ __launch_bounds__(kOrderThreads) void k_target_order(const Rec64* __restrict__ rec,
                                                                 const int* __restrict__ start, Geometry g,
                                                                 int* __restrict__ order)
@@ -362,40 +363,43 @@ __global__ __launch_bounds__(kOrderThreads) void k_target_order(const Rec64* __r
     __shared__ int first[256], place[256], wave_n[kOrderThreads / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int B = g.B, lB = g.log2B, per = 1 << (3 * lB);
-    const int* lines = start + (int64_t)blockIdx.x * per;  // of this tile's cells
-    const int a = lines[0], b = lines[per];
-    if (a >= b) return;
-    if (b - a > 8 * B * B) {  // dense: 16 targets fill two columns or fewer in any order
-        for (int i = a + tid; i < b; i += kOrderThreads) order[i] = i;
-        return;
-    }
     const int w = max(1, B >> 2), lw = max(0, lB - 2);
     // line (x, y) of place tid: tid = (strip, y, x in the strip)
     const int strip = tid >> (lw + lB), yy = (tid >> lw) & (B - 1);
     const int x = strip * w + (tid & (w - 1)), y = (strip & 1) ? B - 1 - yy : yy;
     const int line = morton2(x, y);  // of the sort's order
-    int n = 0, at = 0;
-    if (tid < B * B) {
-        at = lines[line * B];
-        n = lines[line * B + B] - at;
-    }
-    int inc = n;
+    for (int t = blockIdx.x; t < g.ntiles * g.nsys; t += gridDim.x) {
+        const int* lines = start + (int64_t)t * per;  // of this tile's cells
+        const int a = lines[0], b = lines[per];
+        if (a >= b) continue;
+        if (b - a > 8 * B * B) {  // dense: 16 targets fill two columns or fewer in any order
+            for (int i = a + tid; i < b; i += kOrderThreads) order[i] = i;
+            continue;
+        }
+        int n = 0, at = 0;
+        if (tid < B * B) {
+            at = lines[line * B];
+            n = lines[line * B + B] - at;
+        }
+        int inc = n;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int v = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc += v;
-    }
-    if (lane == kWave - 1) wave_n[wid] = inc;
-    __syncthreads();
-    for (int k = 0; k < wid; ++k) inc += wave_n[k];
-    if (tid < B * B) {
-        first[line] = at;
-        place[line] = a + inc - n;
-    }
-    __syncthreads();
-    for (int i = a + tid; i < b; i += kOrderThreads) {
-        const int l = morton2(rec[i].c[0] & (B - 1), rec[i].c[1] & (B - 1));
-        order[place[l] + i - first[l]] = i;
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int v = __shfl_up(inc, o, kWave);
+            if (lane >= o) inc += v;
+        }
+        if (lane == kWave - 1) wave_n[wid] = inc;
+        __syncthreads();
+        for (int k = 0; k < wid; ++k) inc += wave_n[k];
+        if (tid < B * B) {
+            first[line] = at;
+            place[line] = a + inc - n;
+        }
+        __syncthreads();
+        for (int i = a + tid; i < b; i += kOrderThreads) {
+            const int l = morton2(rec[i].c[0] & (B - 1), rec[i].c[1] & (B - 1));
+            order[place[l] + i - first[l]] = i;
+        }
+        __syncthreads();  // before the next tile's
     }
 }
 
@@ -419,8 +423,8 @@ hipError_t launch_g2p_mfma(const Plan& pl, const Work& w, int n, const double* f
         // alone; ms without / with: 4e3 0.034 / 0.036, 1.6e4 0.052 / 0.051, 5e4 0.160 / 0.149)
         if (pl.p.n_max >= 32768) {
             order = w.perm;  // not used after the sort
-            hipLaunchKernelGGL(k_target_order, dim3((unsigned)(g.ntiles * g.nsys)), dim3(kOrderThreads), 0, s,
-                               (const Rec64*)w.rec, w.start, g, order);
+            hipLaunchKernelGGL(k_target_order, dim3((unsigned)std::min(g.ntiles * g.nsys, kOrderBlocks)),
+                               dim3(kOrderThreads), 0, s, (const Rec64*)w.rec, w.start, g, order);
         }
         // by the plan alone, so that a system's result does not depend on what is evaluated with it:
         // plans of up to 131072 particles (ms of the two forms: 1e3 0.044 / 0.017, 1.6e4 at 1e-8 0.076 / 0.050,
