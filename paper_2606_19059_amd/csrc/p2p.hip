@@ -416,12 +416,15 @@ __global__ __launch_bounds__(64) void k_count_pairs(const Rec64* __restrict__ re
 
     // test the targets against ring sources [rhead, rhead + cnt)
     auto process = [&](int cnt) {
+        int qn = 0;
         for (int j = 0; j < cnt; ++j) {
             const int slot = (rhead + j) & (kRing - 1);
             const double rx = tx[0] - ld1(ring[0][slot]), ry = tx[1] - ld1(ring[1][slot]), rz = tx[2] - ld1(ring[2][slot]);
             const double r2 = rx * rx + ry * ry + rz * rz;
-            counted += (unsigned long long)__popcll(__ballot((r2 < a.rc2) && (r2 > 0.0)));
+            const bool pass = (r2 < a.rc2) & (r2 > 0.0);
+            qn += __popcll(__ballot(pass));
         }
+        counted += (unsigned long long)qn;
         wave_lds_sync();
     };
 
