@@ -100,7 +100,8 @@ __device__ inline int wave_scan(int v)
 // 1.56, P = 8 (FP32) 2.17 -> 0.56; 24 systems of 5e3 0.85 -> 0.27; 1.5e5 on 128 x 128 x 256 0.71 -> 0.31; 1e3 on 32^3
 // 0.083 -> 0.028; dense grids: c2 1.46 -> 1.32, H 0.91 -> 0.73, c4 4.38 -> 4.09, c3 8.8 -> 8.0; one loss: 2e4 in two
 // clusters of five cells 0.46 -> 0.53 (few patches hold everything, and a lone wave per SIMD, which issues an FP64
-// instruction every eight cycles, pays the staging's latency).
+// instruction every eight cycles, pays the staging's latency), 0.48 since the search tries the last round's runs
+// first (locate; spread as a whole, with the sort, 0.64 -> 0.56; 24 systems 0.27 -> 0.25, H 0.73 -> 0.72, c2 1.32 -> 1.34).
 //
 // Staging: 16 particles at a time, four lanes each (two halves of the x weights, the y weights of the
 // patch's lines, and their z weights times f, zero off the footprint), every lane by one recurrence of
@@ -257,33 +258,49 @@ __global__ __launch_bounds__(kWaves * 64, P <= 14 ? 3 : 2) void k_p2g_sweep(cons
         // A particle of the wave's share, from its place in the order of the slabs' run tables
         // (places past the last repeat it): its index, and the stencil offset of this lane's first
         // weight (for z without the cell's offset in its tile).  The four lanes of a particle search
-        // its run together, four ways a step.
+        // its run together, four ways a step; where the last round's particles lay in one run or two
+        // (dense columns), the four runs from its first particle's on are tried before.
         int idx = 0, off = 0;
+        int slab0 = 0, run0 = -1;  // the last round's first particle's; -1: not to be tried
         auto locate = [&](int base) {
             const int flat = min(base + (lane >> 2), all - 1);
-            // its slab: the number of slabs that end at or before it, four ways a step
-            int k = 0;
-            auto slab_step = [&](int s) {
-                int below = slab_end[wid][min(k + s * (role + 1), kWindow) - 1] <= flat ? 1 : 0;
-                below += quad_lane<0xb1>(below);
-                below += quad_lane<0x4e>(below);
-                k += s * below;
-            };
-            slab_step(4);
-            slab_step(1);
-            const int tb = k * (R + 1), t = flat + slab_at[wid][k];
-            int lo = 0;
-            auto step = [&](int s) {
-                int below = run_pre[tb + min(lo + s * (role + 1), R)] <= t ? 1 : 0;
+            int k = 0, lo = 0, tb = 0, t = 0;
+            auto among4 = [](bool is) {  // how many of this lane's four
+                int below = is ? 1 : 0;
                 below += quad_lane<0xb1>(below);  // lane ^ 1
                 below += quad_lane<0x4e>(below);  // lane ^ 2
-                lo += s * below;
+                return below;
             };
-            if (R > 256) step(256);
-            step(64);
-            step(16);
-            step(4);
-            step(1);
+            bool found = false;
+            if (run0 >= 0 && min(base + kBatch, all) <= __builtin_amdgcn_readlane(ends, slab0)) {
+                k = slab0;
+                tb = k * (R + 1);
+                t = flat + slab_at[wid][slab0];
+                lo = among4(run_pre[tb + min(run0 + role + 1, R)] <= t);
+                found = __builtin_amdgcn_readlane(lo, kWave - 1) < 4;
+                lo += run0;
+            }
+            if (!found) {
+                // its slab: the number of slabs that end at or before it, four ways a step
+                k = 0;
+                auto slab_step = [&](int s) {
+                    k += s * among4(slab_end[wid][min(k + s * (role + 1), kWindow) - 1] <= flat);
+                };
+                slab_step(4);
+                slab_step(1);
+                tb = k * (R + 1);
+                t = flat + slab_at[wid][k];
+                lo = 0;
+                auto step = [&](int s) { lo += s * among4(run_pre[tb + min(lo + s * (role + 1), R)] <= t); };
+                if (R > 256) step(256);
+                step(64);
+                step(16);
+                step(4);
+                step(1);
+            }
+            slab0 = __builtin_amdgcn_readlane(k, 0);
+            run0 = __builtin_amdgcn_readlane(lo, 0);
+            if (__builtin_amdgcn_readlane(tb + lo, kWave - 1) - (slab0 * (R + 1) + run0) > 1) run0 = -1;
             idx = run_start[tb + lo] + (t - run_pre[tb + lo]);
             const int iy = (lo * nzs_inv) >> 16, zs = lo - iy * nzs;
             off = role < 2 ? role * (P / 2) : role == 2 ? P - 1 - iy : z0 + P / 2 - 1 - (zt0 + zs) * B;
