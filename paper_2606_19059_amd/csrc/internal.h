@@ -75,6 +75,12 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// P2P: whether a source is a candidate for a chunk's targets, from its squared distance d2 from their
+// bounding box and n2 from their centre.  No source without a position is: fmax, of which d2 is made, passes
+// over a NaN, and the sign bits that the matrix test takes for comparisons are set in half of the NaNs (an
+// accepted one would make its targets' near field NaN too).
+__host__ __device__ inline bool p2p_candidate(double d2, double n2, double rc2) { return (d2 < rc2) & (n2 == n2); }
+
 // One LDS value per instruction: the compiler pairs two loads of one base address into a
 // ds_read2_b64 / ds_read2st64_b64, which occupies the LDS pipeline for 8 cycles per wave on
 // gfx950, twice as long as two ds_read_b64 (2 cycles each).  A volatile access is never

@@ -640,6 +640,8 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
     const int i = first + lane;
     const bool active = i < t_end;
     const Rec64 me = rec[active ? i : first];
+    const double pos = me.x[0] + me.x[1] + me.x[2];
+    const bool live = active && pos == pos;  // else the lane accepts no pair (see p2p_candidate)
 
     // tile t of system sys (the systems of a batch have consecutive tile ranges)
     const int sys = t / g.ntiles, tl = t - sys * g.ntiles, tbase = sys * g.ntiles;
@@ -654,7 +656,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
         blo[d] = uniform_d(wave_min(me.x[d]));
         bhi[d] = uniform_d(wave_max(me.x[d]));
         cen[d] = uniform_d(0.5 * (blo[d] + bhi[d]));
-        tx[d] = active ? me.x[d] - cen[d] : 1e30;  // an inactive lane accepts no pair
+        tx[d] = live ? me.x[d] - cen[d] : 1e30;
         if (kScaled) tx[d] *= a.scale;
         tlim += tx[d] * tx[d];
         tgt[d][lane] = tx[d];
@@ -947,7 +949,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                 for (; base < sb; base += step) {
                     const int s = base + lane_at;
                     bool keep = false;
-                    double sx = 0, sy = 0, sz = 0, f0 = 0, f1 = 0, f2 = 0;
+                    double sx = 0, sy = 0, sz = 0, n2 = 0, f0 = 0, f1 = 0, f2 = 0;
                     if (s < sb) {
                         const Rec64& q = rec[s];
                         sx = q.x[0] + shx;
@@ -959,7 +961,6 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                         const double ex = fmax(0.0, fmax(blo[0] - sx, sx - bhi[0]));
                         const double ey = fmax(0.0, fmax(blo[1] - sy, sy - bhi[1]));
                         const double ez = fmax(0.0, fmax(blo[2] - sz, sz - bhi[2]));
-                        keep = ex * ex + ey * ey + ez * ez < a.rc2;
                         sx -= cen[0];
                         sy -= cen[1];
                         sz -= cen[2];
@@ -968,6 +969,8 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                             sy *= a.scale;
                             sz *= a.scale;
                         }
+                        n2 = sx * sx + sy * sy + sz * sz;
+                        keep = p2p_candidate(ex * ex + ey * ey + ez * ez, n2, a.rc2);
                     }
                     // append in two halves so the 64-slot ring never holds more than 63
 #pragma unroll
@@ -979,7 +982,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
                             ring[0][slot] = sx;
                             ring[1][slot] = sy;
                             ring[2][slot] = sz;
-                            ring[3][slot] = sx * sx + sy * sy + sz * sz;
+                            ring[3][slot] = n2;
                             ringf[0][slot] = (TF)f0;
                             ringf[1][slot] = (TF)f1;
                             ringf[2][slot] = (TF)f2;
@@ -1069,6 +1072,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
     const int i = first + lane;
     const bool active = i < t_end;
     const Rec64 me = rec[active ? i : first];
+    const double pos = me.x[0] + me.x[1] + me.x[2];
+    const bool live = active && pos == pos;  // else the lane accepts no pair (see p2p_candidate)
 
     // tile t of system sys (the systems of a batch have consecutive tile ranges)
     const int sys = t / g.ntiles, tl = t - sys * g.ntiles, tbase = sys * g.ntiles;
@@ -1085,8 +1090,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
         blo[d] = uniform_d(wave_min(me.x[d]));
         bhi[d] = uniform_d(wave_max(me.x[d]));
         cen[d] = uniform_d(0.5 * (blo[d] + bhi[d]) * scale);
-        tx[d] = active ? me.x[d] * scale : 1e30;  // an inactive lane accepts no pair
-        const double tc = tx[d] - cen[d];
+        tx[d] = live ? me.x[d] * scale : 1e30;
+        const double tc = live ? tx[d] - cen[d] : 1e30;
         tlim += tc * tc;
         tgt[d][lane] = tx[d];
         acc[d][lane] = 0.0;
@@ -1203,7 +1208,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
         for (int base = sa; base < sb; base += kWave * NW) {
             const int s = base + lane * NW + wid;
             bool keep = false;
-            double sx = 0, sy = 0, sz = 0, f0 = 0, f1 = 0, f2 = 0;
+            double sx = 0, sy = 0, sz = 0, n2 = 0, f0 = 0, f1 = 0, f2 = 0;
             if (s < sb) {
                 const Rec64& q = rec[s];
                 sx = q.x[0] + shx;
@@ -1215,10 +1220,12 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
                 const double ex = fmax(0.0, fmax(blo[0] - sx, sx - bhi[0]));
                 const double ey = fmax(0.0, fmax(blo[1] - sy, sy - bhi[1]));
                 const double ez = fmax(0.0, fmax(blo[2] - sz, sz - bhi[2]));
-                keep = ex * ex + ey * ey + ez * ez < a.rc2;
                 sx *= scale;
                 sy *= scale;
                 sz *= scale;
+                const double cx = sx - cen[0], cy = sy - cen[1], cz = sz - cen[2];
+                n2 = cx * cx + cy * cy + cz * cz;
+                keep = p2p_candidate(ex * ex + ey * ey + ez * ez, n2, a.rc2);
             }
             // append in two halves so the 64-slot ring never holds more than 63
 #pragma unroll
@@ -1230,8 +1237,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k
                     ring[0][slot] = sx;
                     ring[1][slot] = sy;
                     ring[2][slot] = sz;
-                    const double cx = sx - cen[0], cy = sy - cen[1], cz = sz - cen[2];
-                    ring[3][slot] = cx * cx + cy * cy + cz * cz;
+                    ring[3][slot] = n2;
                     ringf[0][slot] = (TF)f0;
                     ringf[1][slot] = (TF)f1;
                     ringf[2][slot] = (TF)f2;
