@@ -381,12 +381,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_target_order(const Rec64* __r
             at = lines[line * B];
             n = lines[line * B + B] - at;
         }
-        int inc = n;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int v = __shfl_up(inc, o, kWave);
-            if (lane >= o) inc += v;
-        }
+        int inc = wave_scan(n);
         if (lane == kWave - 1) wave_n[wid] = inc;
         __syncthreads();
         for (int k = 0; k < wid; ++k) inc += wave_n[k];

@@ -75,6 +75,21 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+__device__ inline int floor_div(int a, int b) { return (a >= 0) ? a / b : -((-a + b - 1) / b); }
+
+// inclusive scan over the wave, all of whose lanes take part: rows of 16 by row_shr, then the rows' totals by the row broadcasts (DPP
+// operands of six additions; a shuffle form takes six dependent LDS round trips)
+__device__ inline int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2 and 3
+    return v;
+}
+
 // P2P: whether a source is a candidate for a chunk's targets, from its squared distance d2 from their
 // bounding box and n2 from their centre.  No source without a position is: fmax, of which d2 is made, passes
 // over a NaN, and the sign bits that the matrix test takes for comparisons are set in half of the NaNs (an
@@ -151,7 +166,7 @@ struct Work {
     int* start;      // [ncells+1] exclusive scan of count
     int* chunk_off;  // [ntiles+1] P2P wave work-list offsets
     int* part;       // scan partials
-    int* cell_lists; // [cell_list_elems(n)] cells too large for a one-thread sort of their order
+    int* cell_lists; // [cell_list_elems(n)] the cells of more than 16 particles, whose indices are sorted
     void* rec;       // [n] Rec64, sorted order
     double* u_near;  // [3][n] near field, sorted order (cleared by the sort)
     double* srec;    // [n][6] symmetric stresslet tensors (xx, yy, zz, xy, xz, yz), sorted order

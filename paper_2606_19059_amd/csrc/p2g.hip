@@ -63,19 +63,6 @@ __device__ inline int quad_lane(int v)
     return __builtin_amdgcn_update_dpp(0, v, kPerm, 0xf, 0xf, true);
 }
 
-// inclusive scan over the wave: rows of 16 by row_shr, then the rows' totals by the row broadcasts (DPP
-// operands of six additions; a shuffle form takes six dependent LDS round trips)
-__device__ inline int wave_scan(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1 and 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2 and 3
-    return v;
-}
-
 // A block of kWaves waves owns one patch and the x-segment [x0, x0 + seg).  It takes the segment in
 // windows of up to kWindow slabs (their run table in LDS) and a window in passes of kSlabs slabs.  A wave
 // spreads a quarter of each slab's particles into its own register window of kSlabs + P - 1 points; after

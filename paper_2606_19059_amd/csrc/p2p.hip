@@ -59,7 +59,6 @@ constexpr double kLog2e = 1.4426950408889634074;
 struct PairArgs {
     double xi, xi2, rc2;
     double four_xi_over_sqrtpi;
-    double xi2_log2e;
     // FP64 formula of the launched level: z = zc r^2 (zc = -xi^2 log2 e); monic screening (ms,
     // x coefficient g = (2/sqrt(pi))/lead_s) and exponential (me) polynomials; a1 / post =
     // C'/r - h e' with h = (4 xi/sqrt(pi))/lead_s
@@ -94,8 +93,6 @@ __device__ inline double wave_max(double v)
     return v;
 }
 
-__device__ inline int floor_div(int a, int b) { return (a >= 0) ? a / b : -((-a + b - 1) / b); }
-
 // A value every lane of the wave already holds, made provably uniform for the compiler
 // (so that addresses derived from it use scalar loads).
 __device__ inline int uniform_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -118,18 +115,8 @@ __device__ inline int wave_min_small(int v)
     return lo;
 }
 
-// sum of v over the wave, for every lane: six additions with DPP operands (rows of 16, then the row
-// broadcasts), no LDS
-__device__ inline int wave_sum_i(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1 and 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2 and 3
-    return __builtin_amdgcn_readlane(v, kWave - 1);
-}
+// sum of v over the wave, for every lane
+__device__ inline int wave_sum_i(int v) { return __builtin_amdgcn_readlane(wave_scan(v), kWave - 1); }
 
 // position of the k-th (from 0) set bit of m, for k < popcount(m): five halving steps
 __device__ inline int select_bit(unsigned m, int k)
@@ -527,7 +514,8 @@ __global__ __launch_bounds__(64) void k_count_pairs(const Rec64* __restrict__ re
 // 128 with comparisons and ballots); with the weighted polynomials on scaled positions c2 18.3 -> 17.85 ms,
 // c3 165 -> 161 ms when it was made.  The own tile, whose
 // pairs also need r > 0 and the index order, and the last, shorter batch keep the direct test;
-// the direct difference of repeated positions is exactly 0 also in the centred frame.
+// the direct difference of repeated positions is exactly 0 also in the centred frame (and scaled by
+// a power of two, whether or not the compiler contracts the product into the difference).
 constexpr int kSymRing = 64;
 constexpr int kUnit = 8;  // consecutive sources dealt at a time to the waves of a chunk (a cache line of u^N)
 constexpr int kFar = 1 << 30;  // ring key offset of sources outside the targets' own tile
@@ -1313,7 +1301,6 @@ PairArgs pair_args(const Plan& pl, int lv)
     a.xi2 = pl.xi * pl.xi;
     a.rc2 = pl.rc * pl.rc;
     a.four_xi_over_sqrtpi = 4.0 * pl.xi / sqrt(M_PI);
-    a.xi2_log2e = a.xi2 * kLog2e;
     a.six_xi_over_sqrtpi = 6.0 * pl.xi / sqrt(M_PI);
     a.four_xi3_over_sqrtpi = 4.0 * pl.xi * pl.xi * pl.xi / sqrt(M_PI);
     const double* ms = lv == 2 ? kScreenM64f : lv == 1 ? kScreenM64s : kScreenM64;
@@ -1416,19 +1403,30 @@ hipError_t launch_p2p(const Plan& pl, const Work& w, int n, hipStream_t s, bool 
     }
     // Symmetric kernel: waves per chunk.  Three shorten the launch's tail; more fill the chip where the chunks
     // are few, and even out the chunks of clustered inputs, until a wave's own start and end outweigh its
-    // share.  P2P ms at 3 / 5 / 7 / 13 / 21 / 33 / 65 waves per chunk: 24 chunks (1e3 uniform, FP64) 0.061 / 0.046 /
-    // 0.041 / 0.034 / 0.029 / 0.027 / 0.024; 441 (2e4 in 2 clusters, FP32) 1.01 / 0.61 / 0.55 / 0.36 / 0.26 / 0.27 / 0.26;
-    // 533 (3e4 uniform, FP64) 0.23 / 0.19 / 0.16 / 0.16 / 0.16 / 0.19 / 0.26; 1544 (6.6e4, FP32) 0.56 / 0.54 / 0.54 / 0.59 /
-    // 0.67 / 0.76 / 1.08; 3412 (24 systems of 5e3, FP32) 0.16 / 0.17 / 0.19 / 0.25 / 0.31 / 0.40 / 0.66; 3368 (1.5e5, FP64) 0.426 /
-    // 0.418 / 0.449 / 0.54 / 0.69 / 0.83 / 1.26; 40 (2e3) at 33 / 49 / 65 0.039 / 0.032 / 0.033, 62 (3.4e3) 0.042 / 0.051 /
-    // 0.047.  Odd, so that the waves of a chunk, consecutive blocks, spread
-    // over the XCDs (with 8 or 16, all the chunks' first waves, the heaviest, meet on one).
-    // With stresslet sources fewer waves fit a CU (16 KB of LDS each) and the pairs cost more: 1294 chunks
-    // (5e4 at 1e-8) 0.218 / 0.216 / 0.239 / 0.30 / 0.35 / 0.44, 5200 (3e5, FP32) 1.70 / 1.64 / 1.67 / 1.70 / 1.88 / 2.22.
-    // What is dealt: units of kUnit sources below 8192 chunks (see the kernel), neighbour tiles above, where a
-    // wave's compact batches are worth more than even shares (three waves, tiles / units: 5200 chunks 1.36 / 1.24,
-    // 3e5 in 30 clusters, FP64 11.4 / 7.9; 19721 (1e6), 256^3 FP64 3.50 / 3.61, c2 17.6 / 18.4, H 9.47 / 9.93; 78884
-    // (c4) 48.0 / 50.3).
+    // share.  P2P ms by waves per chunk:
+    //                                          3      5      7      13     21     33     49     65
+    //     24 chunks (1e3, FP64)              0.061  0.046  0.041  0.034  0.029  0.027   -    0.024
+    //     40 chunks (2e3)                      -      -      -      -      -    0.039  0.032  0.033
+    //     62 chunks (3.4e3)                    -      -      -      -      -    0.042  0.051  0.047
+    //    441 chunks (2e4 in 2 clusters, FP32) 1.01  0.61   0.55   0.36   0.26   0.27    -    0.26
+    //    533 chunks (3e4, FP64)              0.23   0.19   0.16   0.16   0.16   0.19    -    0.26
+    //   1544 chunks (6.6e4, FP32)            0.56   0.54   0.54   0.59   0.67   0.76    -    1.08
+    //   3368 chunks (1.5e5, FP64)            0.426  0.418  0.449  0.54   0.69   0.83    -    1.26
+    //   3412 chunks (24 systems of 5e3, FP32) 0.16  0.17   0.19   0.25   0.31   0.40    -    0.66
+    // (49 up to 48 chunks: between the two sizes measured on its sides.)  Odd, so that the waves of a chunk,
+    // consecutive blocks, spread over the XCDs (with 8 or 16, all the chunks' first waves, the heaviest,
+    // meet on one).  With stresslet sources fewer waves fit a CU (16 KB of LDS each) and the pairs cost more:
+    //                                          3      5      7      13     21     33
+    //   1294 chunks (5e4 at 1e-8)            0.218  0.216  0.239  0.30   0.35   0.44
+    //   5200 chunks (3e5, FP32)              1.70   1.64   1.67   1.70   1.88   2.22
+    // What is dealt: units of kUnit sources below 8192 chunks (see the kernel), neighbour tiles above, where on
+    // uniform inputs a wave's compact batches are worth more than even shares; three waves, ms by tiles / units:
+    //   uniform    5200 chunks 1.36 / 1.24; 8784 (3e5, FP64) 0.58 / 0.63; 11909 (5e5) 1.12 / 1.16; 19721 (1e6 on 256^3)
+    //              3.50 / 3.61, (c2) 17.6 / 18.4, (H) 9.47 / 9.93; 78884 (c4) 48.0 / 50.3
+    //   clustered  5200 (3e5 in 30, FP64) 11.4 / 7.9; 8784 (3e5 in 30) 7.5-8.5 / 5.6; 11909 (5e5 in 50) 11.0 / 9.4;
+    //              19721 (1e6 in 100) 21.1 / 19.3, FP32 16.0 / 13.5; 189018 (c3) 164.7 / 167.4
+    // Chunks are counted as the launch's bound, tiles and n / 64, before the particles are known, so that
+    // clustered inputs of 3e5 to 1e6 go by tiles, which is the slower side for them.
     const int64_t fill = ((st ? 4608 : 9216) / waves) | 1;
     const int64_t least = st && waves < 8192 ? 5 : 3, most = waves <= 48 ? 49 : 33;
     const int kSplit = (int)std::min<int64_t>(most, std::max(least, fill));

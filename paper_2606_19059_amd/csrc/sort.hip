@@ -297,12 +297,7 @@ __device__ inline int block_exclusive_scan(int v, int* sh, int& total)
     // inclusive scan within each wave
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = threadIdx.x / kWave;
-    int inc = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc += y;
-    }
+    const int inc = wave_scan(v);
     if (lane == kWave - 1) sh[wid] = inc;
     __syncthreads();
     const int nw = blockDim.x / kWave;

@@ -60,7 +60,6 @@ inline WinArgs<T> make_win_args(const Plan& pl)
 
 // periodic wrap of a grid index; grid sizes are powers of two (checked when a plan is made)
 __device__ inline int wrapi(int a, int M) { return a & (M - 1); }
-__device__ inline int floor_div(int a, int b) { return (a >= 0) ? a / b : -((-a + b - 1) / b); }
 
 // Cell, fraction and force of a sorted record, in the kernel's precision T.
 template <typename T>
