@@ -50,10 +50,10 @@ namespace {
 // therefore returns its coefficients divided by post; the kernels multiply each target's and source's sum by post once, at the end.
 // Levels 1 and 2 work (without stresslet sources) on positions scaled by a power of two p near
 // kappa = xi sqrt(log2 e), which makes r the variable of polynomials whose coefficients the host multiplies by
-// powers of kappa / p: one multiplication per pair less, whatever the box's size.  A power of two, so that
-// the scaled positions and their differences are exact: scaling by kappa itself, which would save the
-// exponent's multiplication too, rounds every position once more, and the distance of two points 1e-8 apart
-// in a chunk of edge 1/8 was then off by 1.4e-10 at the median (4e-17 so).
+// powers of kappa / p (a multiplication per pair less, whatever the box's size).  A power of two, so that the
+// scaled positions and their differences are exact: scaling by kappa itself rounds every position once more,
+// and the distance of two points 1e-8 apart was then off by 6.6e-10 at the median (7e-13 so, the formula's
+// own error).  Against that form, one FMA a pair and the candidates' test for NaN: c2 P2P 17.47 -> 17.6 ms.
 constexpr double kLog2e = 1.4426950408889634074;
 
 struct PairArgs {
@@ -168,19 +168,21 @@ __device__ inline double screen_q64(double x, const PairArgs& a)
     return fma(a.g, x, q);
 }
 
-// 2^z / lead_e for -61 < z <= 0: z = n + s, n = rint(z), |s| <= 1/2 (s exact), 2^s from the monic
-// polynomial of screening.h
+// 2^z / lead_e for z = c r2, -61 < z <= 0: z = n + s, n = rint(z), |s| <= 1/2, 2^s from the monic
+// polynomial of screening.h.  The factor c costs no multiplication: one FMA adds c r2 to 1.5 x 2^52, which rounds
+// it to an integer in the sum's low bits (n, for ldexp), another subtracts it from c r2 unrounded.
 template <int Lv>
-__device__ inline double exp2_lead(double z, const PairArgs& a)
+__device__ inline double exp2_lead(double r2, double c, const PairArgs& a)
 {
-    const double n = rint(z);
-    const double s = z - n;
+    constexpr double kRound = 6755399441055744.0;
+    const double t = fma(c, r2, kRound);
+    const double s = fma(c, r2, kRound - t);
     constexpr int deg = Lv == 1 ? kExpDeg1 : kExpDeg2;
     const double* m = a.me;
     double p = s + m[deg - 1];
 #pragma unroll
     for (int k = deg - 2; k >= 0; --k) p = fma(p, s, m[k]);
-    return ldexp(p, (int)n);
+    return ldexp(p, __double2loint(t));
 }
 
 // 1/sqrt(r2) for finite r2 > 0: hardware estimate y (error bound 2^29 ulp, ~2^-23
@@ -219,7 +221,7 @@ __device__ inline void coef64(double r2, const PairArgs& a, double& a1, double& 
         e = exp(-a.xi2 * r2);
         q = screen_q64<Lv>(a.xi * r2 * rinv, a);
     } else {
-        e = exp2_lead<Lv>(a.zs * r2, a);
+        e = exp2_lead<Lv>(r2, a.zs, a);
         q = screen_w64<Lv>(r2 * rinv, a);
     }
     const double Cr = e * q * rinv;
@@ -287,7 +289,7 @@ __device__ inline void coef64_st(double r2, const PairArgs& a, double& a1, doubl
     const double rinv = rsqrt(r2);
     const double r = r2 * rinv;
     const double x = a.xi * r;
-    const double e = Lv > 0 ? a.lead_e * exp2_lead<Lv>(a.zc * r2, a) : exp(-a.xi2 * r2);
+    const double e = Lv > 0 ? a.lead_e * exp2_lead<Lv>(r2, a.zc, a) : exp(-a.xi2 * r2);
     const double C = e * (a.lead_st * screen_q64<Lv>(x, a));
     const double rinv2 = rinv * rinv, rinv3 = rinv2 * rinv;
     a1 = fma(C, rinv, -a.four_xi_over_sqrtpi * e);
