@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(64) void k_p2p_sym(int n, const Rec64* __restrict__
 // Sources are dealt one by one along a row of tiles, so that the waves of a chunk get alike shares of
 // every region around it (by batches of 64 in the order of the sort, the largest share of eight waves was
 // 1.39 times the mean at 3e4, and the block waits for it: 0.36 -> 0.31 ms at 3e4, 31.5 -> 29.2 at 1e6).
-// Bound by FP64 issue, and at small sizes by the waves in flight: 1e6 uniform at 1e-8, 128^3, 25.3 ms (33.9
+// Bound by FP64 issue, and at small sizes by the waves in flight: 1e6 uniform at 1e-8, 128^3, 25.8 ms (33.9
 // with every pair through an LDS queue and its three LDS atomics); 3e4, KB, 0.31 (0.48).
 template <typename TF, int Lv, int NW>
 __global__ __launch_bounds__(64 * NW, sizeof(TF) == 8 && Lv == 0 ? 4 : 5) void k_p2p_one(int n, const Rec64* __restrict__ rec,
