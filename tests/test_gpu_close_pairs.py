@@ -48,3 +48,22 @@ def test_close_pairs_match_oracle(xi, n_max, precision, tol, bound):
 def test_close_pairs_deterministic_match_oracle(xi, n_max, precision, tol, bound):
     sep = 1e-12 if precision == "fp32" else 1e-10
     assert np.max(pair_errors(sep, 1500, n_max, xi, True, precision, tol)) < bound
+
+
+@pytest.mark.parametrize("deterministic", [False, True])
+@pytest.mark.parametrize("tol,bound", [(1e-9, 1e-10), (1e-7, 1e-9)])
+@pytest.mark.parametrize("side", [3e-9, 1e-3, 7e8])
+def test_power_of_two_scale_of_any_box(side, tol, bound, deterministic):
+    """The reduced-cost levels scale positions by a power of two near xi (log2 e)^1/2: boxes of any size, with
+    the bounds of the sweep over unit boxes."""
+    import paper_2606_19059_amd as E
+
+    rng = np.random.default_rng(59)
+    box, xi, rc = (side, side, side), 11.0 / side, 0.35 * side
+    x, f = rng.random((3, 700)) * side, rng.standard_normal((3, 700))
+    pl = E.Plan(box, tol, xi=xi, r_c=rc, grid=(32, 32, 32), P=8, window_shape=4.8, n_max=700,
+                deterministic=deterministic)
+    dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to("cuda")
+    un = pl.eval_parts(dev(x), dev(f))[0].cpu().numpy()
+    ref = oracle.real_space(x, f, box, xi, rc)
+    assert np.max(np.abs(un - ref)) < bound * np.max(np.abs(ref))
